@@ -97,13 +97,21 @@ enum Buf { B_KEYS_A, B_KEYS_B, B_VALS_A, B_VALS_B, B_HIST, B_TOTALS, B_SP, B_UF4
 struct ScratchPlan {
     size_t bytes[B_COUNT];
     int64_t part_stride;
+    int64_t max_tiles;   // sort tiles the histograms hold
+    size_t total() const {
+        size_t t = 0;
+        for (size_t b : bytes) t += (b + 255) / 256 * 256;
+        return t;
+    }
 };
 
-static ScratchPlan scratch_plan(const couple_config &c, int64_t nmax) {
+// `tight`: histograms for the fewest tiles a sort can take (the sort then uses
+// its largest tiles) instead of the most.
+static ScratchPlan scratch_plan(const couple_config &c, int64_t nmax, bool tight = false) {
     ScratchPlan p{};
     const int64_t ncell = (int64_t)c.nb[0] * c.nb[1] * c.nb[2];
     const size_t fsz = (c.precision == COUPLE_FP64) ? sizeof(double) : sizeof(float);
-    const int64_t ntile = sort_tiles(nmax > 0 ? nmax : 1);
+    const int64_t ntile = p.max_tiles = tight ? sort_tiles_min(nmax) : sort_tiles_max(nmax);
     const int64_t pblk = (nmax + kBlock - 1) / kBlock, cblk = (ncell + kBlock - 1) / kBlock;
     // one FP64 partial per workgroup and slot: the stride covers the largest
     // grid of any kernel that writes partials
@@ -171,6 +179,7 @@ extern "C" int couple_init(const couple_config *cfg, couple_handle **out) {
     h->nfine = h->ncell * cfg->ratio * cfg->ratio * cfg->ratio;
     const ScratchPlan plan = scratch_plan(*cfg, cfg->max_particles);
     h->part_stride = plan.part_stride;
+    h->sort.max_tiles = plan.max_tiles;
     bool ok = true;
     for (int b = 0; b < B_COUNT && ok; ++b)
         if (plan.bytes[b] > 0 || b < B_FGRID) ok = dev_alloc(buf_slot(h, b), plan.bytes[b]);
@@ -255,6 +264,7 @@ static int step_impl(couple_handle *h, const couple_inputs *in, couple_outputs *
     a.dep_partial = (T *)h->dep;
     a.part = h->part;
     a.part_stride = h->part_stride;
+    a.bin_tiles = sort_tiles(a.n, h->sort.max_tiles);
     a.mk = &h->mk;
     a.uf_out = (T *)out->uf;
     a.net = MlpNet{};
@@ -382,9 +392,9 @@ extern "C" int couple_step_noalloc(const couple_config *cfg, const couple_inputs
         return COUPLE_EINVAL;
     }
     // scratch for exactly these n particles, carved in 256-byte aligned pieces
-    const ScratchPlan plan = scratch_plan(*cfg, in->n);
-    size_t total = 0;
-    for (int b = 0; b < B_COUNT; ++b) total += (plan.bytes[b] + 255) / 256 * 256;
+    ScratchPlan plan = scratch_plan(*cfg, in->n);
+    if (plan.total() > (size_t)COUPLE_NOALLOC_SCRATCH_BYTES) plan = scratch_plan(*cfg, in->n, true);
+    const size_t total = plan.total();
     if (total > (size_t)COUPLE_NOALLOC_SCRATCH_BYTES) {
         snprintf(g_err, sizeof(g_err),
                  "couple_step_noalloc: this step needs %zu bytes of scratch, more than the %lld of the static "
@@ -410,6 +420,7 @@ extern "C" int couple_step_noalloc(const couple_config *cfg, const couple_inputs
     h.ncell = (int64_t)cfg->nb[0] * cfg->nb[1] * cfg->nb[2];
     h.nfine = h.ncell * cfg->ratio * cfg->ratio * cfg->ratio;
     h.part_stride = plan.part_stride;
+    h.sort.max_tiles = plan.max_tiles;
     size_t off = 0;
     for (int b = 0; b < B_COUNT; ++b) {
         *buf_slot(&h, b) = plan.bytes[b] ? base + off : nullptr;

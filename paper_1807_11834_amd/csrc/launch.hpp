@@ -32,9 +32,15 @@ struct SortScratch {
     uint32_t *vals_a, *vals_b;   // [max_particles]
     uint32_t *hist;              // [256 * max_tiles]
     uint32_t *totals;            // [256]
+    int64_t max_tiles;           // tiles the histograms hold
 };
 
-int sort_tiles(int64_t n);
+// Tiles of a sort of n keys whose histograms hold max_tiles tiles; the fewest
+// and the most that any sort of up to n keys takes (the histograms hold at least
+// the former, and the latter where memory is not short).
+int sort_tiles(int64_t n, int64_t max_tiles);
+int64_t sort_tiles_min(int64_t n);
+int64_t sort_tiles_max(int64_t n);
 
 // One stable radix pass over keys < 2^bits (1 <= bits <= 8) from the identity
 // order: keys_out / ids_out in ascending key, ties by id; s.totals[d] receives
@@ -95,6 +101,7 @@ template <typename T> struct StepArgs {
     T *dep_partial;  // [4][nc][ncell] per-source-group partial sums of the CIC deposition (nc <= 4)
     double *part;    // [SL_COUNT][max_blocks]
     int64_t part_stride;
+    int bin_tiles;   // tiles of the binning (one SL_NOUT partial each)
     Marker *mk;      // per-kernel event recording (never null)
     // optional output: fluid velocity used by the drag, [n][3] (input order)
     T *uf_out;

@@ -276,7 +276,7 @@ extern "C" int couple_part_init(const couple_config *cfg, int32_t nparts, couple
                  palloc(p, &s.fKU, 3 * f * s.nfl);
     }
     const int64_t nmax = cfg->max_particles > 0 ? cfg->max_particles : 1;
-    const int ntile = sort_tiles(nmax);
+    const int64_t ntile = p->sort.max_tiles = sort_tiles_max(nmax);
     const size_t f = p->fsz;
     ok = ok && palloc(p, &p->sort.hist, 4 * 256 * (size_t)ntile) && palloc(p, &p->sort.totals, 4 * 256) &&
          palloc(p, &p->owner, 4 * nmax) && palloc(p, &p->okey, 4 * nmax) && palloc(p, &p->oid, 4 * nmax) &&

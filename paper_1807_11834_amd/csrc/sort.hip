@@ -22,25 +22,26 @@
 // starting from the identity order gives ascending (cell, id).  Integer atomics
 // are used only on LDS histogram bins (exact counts); no float atomics anywhere.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "launch.hpp"
 
 namespace cpl {
 
-constexpr int kItems = 16;                         // keys per thread per tile
-constexpr int kTile = kBlock * kItems;             // 4096 keys per tile
-constexpr int kWaveSpan = kWave * kItems;          // keys handled by one wave
+constexpr int kMaxItems = 16;                      // most keys per thread of a tile (the kernels' ITEMS)
 constexpr int kMaxDigits = 256;                    // radix <= 8 bits per pass
 
 // A start entry not yet known: k_bin marks every entry so, k_segment_starts sets
 // all but those inside long runs of empty cells, k_segment_counts the rest.
 constexpr int32_t kUnset = -1;
 
-// Workgroups [0, ntile) bin the particles of their tile; every workgroup of the
-// grid (which may be larger, to cover the cells) also marks a share of
-// start[0 .. nstart) unset.
-template <typename T>
+// Workgroups [0, ntile) bin the particles of their tile of kBlock x ITEMS; every
+// workgroup of the grid (which may be larger, to cover the cells) also marks a
+// share of start[0 .. nstart) unset.  The particles are taken kBinBatch per
+// thread at a time, all their loads issued before the first is used.
+constexpr int kBinBatch = 4;
+template <typename T, int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_bin(const T *__restrict__ pos, const T *__restrict__ diam, int64_t n,
                                                 Geo<T> g, int32_t *__restrict__ cell, vec4<T> *__restrict__ pk,
                                                 uint32_t *__restrict__ hist,
@@ -54,25 +55,37 @@ __global__ __launch_bounds__(kBlock) void k_bin(const T *__restrict__ pos, const
     const int ndig = 1 << bits0;
     for (int d = threadIdx.x; d < ndig; d += kBlock) h[d] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kTile;
+    const int64_t base = (int64_t)blockIdx.x * kBlock * ITEMS + threadIdx.x;
     double nout = 0.0;
-    for (int it = 0; it < kItems; ++it) {
-        int64_t p = base + (int64_t)it * kBlock + threadIdx.x;
-        if (p < n) {
+    constexpr int NB = ITEMS < kBinBatch ? ITEMS : kBinBatch;
+    for (int it0 = 0; it0 < ITEMS; it0 += NB) {
+        T xs[NB][3], ds[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            int64_t p = base + (int64_t)(it0 + u) * kBlock;
+            p = p < n ? p : n - 1;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) xs[u][k] = pos[3 * p + k];
+            ds[u] = diam[p];
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int64_t p = base + (int64_t)(it0 + u) * kBlock;
+            if (p >= n) continue;
             int outside = 0;
-            T x = clamp_coord(pos[3 * p + 0], g.L[0], outside);
-            T y = clamp_coord(pos[3 * p + 1], g.L[1], outside);
-            T z = clamp_coord(pos[3 * p + 2], g.L[2], outside);
-            int ix = cell_axis(x, g.sb[0], g.nb[0]);
-            int iy = cell_axis(y, g.sb[1], g.nb[1]);
-            int iz = cell_axis(z, g.sb[2], g.nb[2]);
-            int32_t c = ix + g.nb[0] * (iy + g.nb[1] * iz);
+            const T x = clamp_coord(xs[u][0], g.L[0], outside);
+            const T y = clamp_coord(xs[u][1], g.L[1], outside);
+            const T z = clamp_coord(xs[u][2], g.L[2], outside);
+            const int ix = cell_axis(x, g.sb[0], g.nb[0]);
+            const int iy = cell_axis(y, g.sb[1], g.nb[1]);
+            const int iz = cell_axis(z, g.sb[2], g.nb[2]);
+            const int32_t c = ix + g.nb[0] * (iy + g.nb[1] * iz);
             cell[p] = c;
             vec4<T> q;
             q.x = x;
             q.y = y;
             q.z = z;
-            q.w = diam[p];
+            q.w = ds[u];
             pk[p] = q;
             atomicAdd(&h[(uint32_t)c & (ndig - 1)], 1u);
             nout += outside;
@@ -84,60 +97,70 @@ __global__ __launch_bounds__(kBlock) void k_bin(const T *__restrict__ pos, const
     if (threadIdx.x == 0) part_nout[blockIdx.x] = t;
 }
 
+template <int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t *__restrict__ keys, int64_t n, int shift,
                                                        int bits, uint32_t *__restrict__ hist, int ntile) {
     __shared__ uint32_t h[kMaxDigits];
     const int ndig = 1 << bits;
     for (int d = threadIdx.x; d < ndig; d += kBlock) h[d] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kTile;
-    for (int it = 0; it < kItems; ++it) {
-        int64_t p = base + (int64_t)it * kBlock + threadIdx.x;
-        if (p < n) atomicAdd(&h[(keys[p] >> shift) & (ndig - 1)], 1u);
+    const int64_t base = (int64_t)blockIdx.x * kBlock * ITEMS + threadIdx.x;
+    uint32_t k[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t p = base + (int64_t)it * kBlock;
+        k[it] = keys[p < n ? p : n - 1];
     }
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it)
+        if (base + (int64_t)it * kBlock < n) atomicAdd(&h[(k[it] >> shift) & (ndig - 1)], 1u);
     __syncthreads();
     for (int d = threadIdx.x; d < ndig; d += kBlock) hist[(int64_t)d * ntile + blockIdx.x] = h[d];
 }
 
 // One workgroup per digit: exclusive prefix over the tiles (in place) and the
-// digit's total.
+// digit's total.  Each thread takes a contiguous run of tiles: its sum, one
+// scan over the workgroup, then the run's prefixes (two barriers whatever the
+// number of tiles).
 __global__ __launch_bounds__(kBlock) void k_radix_prefix(uint32_t *__restrict__ hist, int ntile,
                                                          uint32_t *__restrict__ totals) {
     __shared__ uint32_t wsum[kWavesPerBlock];
-    __shared__ uint32_t carry;
     uint32_t *row = hist + (int64_t)blockIdx.x * ntile;
     const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int base = 0; base < ntile; base += kBlock) {
-        int i = base + threadIdx.x;
-        uint32_t v = i < ntile ? row[i] : 0u;
-        // inclusive wave scan
-        uint32_t s = v;
-        for (int o = 1; o < kWave; o <<= 1) {
-            uint32_t u = __shfl_up(s, o, kWave);
-            if (lane >= o) s += u;
-        }
-        if (lane == kWave - 1) wsum[w] = s;
-        __syncthreads();
-        uint32_t off = carry;
-        for (int k = 0; k < w; ++k) off += wsum[k];
-        if (i < ntile) row[i] = off + s - v;
-        __syncthreads();
-        if (threadIdx.x == kBlock - 1) carry = off + s;
-        __syncthreads();
+    const int per = (ntile + kBlock - 1) / kBlock;
+    const int i0 = (int)threadIdx.x * per, i1 = i0 + per < ntile ? i0 + per : ntile;
+    uint32_t v = 0;
+    for (int i = i0; i < i1; ++i) v += row[i];
+    uint32_t s = v;   // inclusive wave scan
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t u = __shfl_up(s, o, kWave);
+        if (lane >= o) s += u;
     }
-    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+    if (lane == kWave - 1) wsum[w] = s;
+    __syncthreads();
+    uint32_t off = s - v;
+    for (int k = 0; k < w; ++k) off += wsum[k];
+    if (threadIdx.x == kBlock - 1) totals[blockIdx.x] = off + v;
+    for (int i = i0; i < i1; ++i) {
+        const uint32_t c = row[i];
+        row[i] = off;
+        off += c;
+    }
 }
 
 // Stable tile ranking and scatter.  FIRST: values are the input positions (ids).
-template <bool FIRST>
+// Every key and value of a thread is loaded before the first is ranked: the
+// ranking is a serial chain through the LDS counters, and a load inside it
+// would add a memory round trip per key (10,000 keys: 13.4 us with the loads
+// in the chain).
+template <bool FIRST, int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t *__restrict__ keys_in,
                                                           const uint32_t *__restrict__ vals_in, int64_t n,
                                                           int shift, int bits, const uint32_t *__restrict__ hist,
                                                           const uint32_t *__restrict__ totals, int ntile,
                                                           uint32_t *__restrict__ keys_out,
                                                           uint32_t *__restrict__ vals_out) {
+    constexpr int kTile = kBlock * ITEMS, kWaveSpan = kWave * ITEMS;   // keys of a workgroup, of a wave
     __shared__ uint32_t digit_base[kMaxDigits];       // global start of each digit's run
     __shared__ uint32_t local_start[kMaxDigits];      // start of each digit inside the tile
     __shared__ uint32_t wave_cnt[kWavesPerBlock][kMaxDigits];
@@ -157,14 +180,19 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t *__rest
     __syncthreads();
 
     // ---- rank: wave w owns keys [w*kWaveSpan, (w+1)*kWaveSpan) of the tile ----
-    uint32_t key[kItems], val[kItems], rank[kItems];
+    uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-    for (int it = 0; it < kItems; ++it) {
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
         int li = w * kWaveSpan + it * kWave + lane;   // position inside the tile
-        bool valid = li < tile_n;
-        uint32_t k = valid ? keys_in[tile0 + li] : 0u;
-        uint32_t v = valid ? (FIRST ? (uint32_t)(tile0 + li) : vals_in[tile0 + li]) : 0u;
-        uint32_t d = (k >> shift) & dmask;
+        li = li < tile_n ? li : tile_n - 1;
+        key[it] = keys_in[tile0 + li];
+        val[it] = FIRST ? (uint32_t)(tile0 + li) : vals_in[tile0 + li];
+    }
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const bool valid = w * kWaveSpan + it * kWave + lane < tile_n;
+        const uint32_t d = (key[it] >> shift) & dmask;
         uint64_t peers = __ballot(valid);
         for (int b = 0; b < bits; ++b) {
             bool bit = (d >> b) & 1u;
@@ -178,8 +206,6 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t *__rest
         __builtin_amdgcn_wave_barrier();
         if (leader) wave_cnt[w][d] = cnt + (uint32_t)__popcll(peers);
         __builtin_amdgcn_wave_barrier();
-        key[it] = k;
-        val[it] = v;
         rank[it] = valid ? cnt + before : 0xffffffffu;
     }
     __syncthreads();
@@ -225,7 +251,8 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t *__rest
     }
 
     // ---- stage the tile in digit order in LDS --------------------------------
-    for (int it = 0; it < kItems; ++it) {
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
         if (rank[it] != 0xffffffffu) {
             uint32_t d = (key[it] >> shift) & dmask;
             uint32_t lp = local_start[d] + wave_cnt[w][d] + rank[it];
@@ -317,7 +344,23 @@ __global__ __launch_bounds__(kBlock) void k_segment_counts(int32_t *start, int64
 // Host side
 // ---------------------------------------------------------------------------
 
-int sort_tiles(int64_t n) { return (int)((n + kTile - 1) / kTile); }
+// Keys per thread of a tile: the fewest that leave at most kTilesWanted tiles.
+// A tile's ranking is a serial chain of ITEMS keys per wave, so fewer keys per
+// tile shorten a launch that cannot fill the chip (four tiles per compute unit
+// fill it); more tiles than that only lengthen the per-digit prefix.
+constexpr int64_t kTilesWanted = 1024;
+static int64_t tiles_of(int64_t n, int items) { return (n + (int64_t)kBlock * items - 1) / ((int64_t)kBlock * items); }
+static int sort_items(int64_t n, int64_t max_tiles) {
+    for (int items : {4, 8})
+        if (tiles_of(n, items) <= kTilesWanted && tiles_of(n, items) <= max_tiles) return items;
+    return kMaxItems;
+}
+
+int64_t sort_tiles_min(int64_t n) { return tiles_of(n > 0 ? n : 1, kMaxItems); }
+int64_t sort_tiles_max(int64_t n) {
+    return std::max(sort_tiles_min(n), std::min(tiles_of(n > 0 ? n : 1, 4), kTilesWanted));
+}
+int sort_tiles(int64_t n, int64_t max_tiles) { return (int)tiles_of(n, sort_items(n, max_tiles)); }
 
 void sort_plan(int64_t ncell, int *npass, int widths[4]) {
     int bits = 1;
@@ -328,47 +371,66 @@ void sort_plan(int64_t ncell, int *npass, int widths[4]) {
     *npass = p;
 }
 
+// f(integral_constant) for the tile size of `items` keys per thread.
+template <typename F> static void with_items(int items, F f) {
+    if (items == 4) f(std::integral_constant<int, 4>{});
+    else if (items == 8) f(std::integral_constant<int, 8>{});
+    else f(std::integral_constant<int, kMaxItems>{});
+}
+
+// One radix pass (its histograms are there already unless `hist`); vin NULL: the
+// values are the positions.
+static void radix_pass(const uint32_t *kin, const uint32_t *vin, int64_t n, int shift, int bits, bool hist, int items,
+                       const SortScratch &s, uint32_t *kout, uint32_t *vout, Marker *mk, hipStream_t st) {
+    const int ntile = (int)tiles_of(n, items);
+    with_items(items, [&](auto ic) {
+        constexpr int I = decltype(ic)::value;
+        if (hist) {
+            mk->mark("radix_hist", st);
+            hipLaunchKernelGGL(k_radix_hist<I>, dim3(ntile), dim3(kBlock), 0, st, kin, n, shift, bits, s.hist, ntile);
+        }
+        mk->mark("radix_prefix", st);
+        hipLaunchKernelGGL(k_radix_prefix, dim3(1 << bits), dim3(kBlock), 0, st, s.hist, ntile, s.totals);
+        mk->mark("radix_scatter", st);
+        if (vin)
+            hipLaunchKernelGGL((k_radix_scatter<false, I>), dim3(ntile), dim3(kBlock), 0, st, kin, vin, n, shift, bits,
+                               s.hist, s.totals, ntile, kout, vout);
+        else
+            hipLaunchKernelGGL((k_radix_scatter<true, I>), dim3(ntile), dim3(kBlock), 0, st, kin, vin, n, shift, bits,
+                               s.hist, s.totals, ntile, kout, vout);
+    });
+}
+
 template <typename T>
 hipError_t launch_bin_sort(const T *pos, const T *diam, int64_t n, const Geo<T> &g, int32_t *cell, vec4<T> *pk,
                            int32_t *perm, int32_t *start, int32_t *count, const SortScratch &s, double *part_nout,
                            const uint32_t **sorted_keys, Marker *mk, hipStream_t st) {
     int npass, widths[4];
     sort_plan(g.ncell, &npass, widths);
-    const int ntile = n > 0 ? sort_tiles(n) : 0;
+    const int items = sort_items(n, s.max_tiles);
+    const int ntile = n > 0 ? (int)tiles_of(n, items) : 0;
     // the binning grid also covers start[0 .. ncell] (marked unset)
     const int64_t nstart = g.ncell + 1;
-    const int bin_blocks = std::max<int64_t>(ntile, (nstart + kTile - 1) / kTile);
+    const int bin_blocks = (int)std::max<int64_t>(ntile, tiles_of(nstart, kMaxItems));
     mk->mark("bin", st);
-    hipLaunchKernelGGL(k_bin<T>, dim3(bin_blocks), dim3(kBlock), 0, st, pos, diam, n, g, cell, pk, s.hist, ntile,
-                       widths[0], part_nout, start, nstart);
+    with_items(items, [&](auto ic) {
+        hipLaunchKernelGGL((k_bin<T, decltype(ic)::value>), dim3(bin_blocks), dim3(kBlock), 0, st, pos, diam, n, g,
+                           cell, pk, s.hist, ntile, widths[0], part_nout, start, nstart);
+    });
+    *sorted_keys = s.keys_a;
     if (n > 0) {
         int shift = 0;
         const uint32_t *kin = (const uint32_t *)cell;
         const uint32_t *vin = nullptr;
         for (int p = 0; p < npass; ++p) {
-            const bool last = (p == npass - 1);
             uint32_t *kout = (p % 2 == 0) ? s.keys_a : s.keys_b;
-            uint32_t *vout = last ? (uint32_t *)perm : ((p % 2 == 0) ? s.vals_a : s.vals_b);
-            if (p > 0) mk->mark("radix_hist", st);
-            if (p > 0)
-                hipLaunchKernelGGL(k_radix_hist, dim3(ntile), dim3(kBlock), 0, st, kin, n, shift, widths[p], s.hist,
-                                   ntile);
-            mk->mark("radix_prefix", st);
-            hipLaunchKernelGGL(k_radix_prefix, dim3(1 << widths[p]), dim3(kBlock), 0, st, s.hist, ntile, s.totals);
-            mk->mark("radix_scatter", st);
-            if (p == 0)
-                hipLaunchKernelGGL(k_radix_scatter<true>, dim3(ntile), dim3(kBlock), 0, st, kin, vin, n, shift,
-                                   widths[p], s.hist, s.totals, ntile, kout, vout);
-            else
-                hipLaunchKernelGGL(k_radix_scatter<false>, dim3(ntile), dim3(kBlock), 0, st, kin, vin, n, shift,
-                                   widths[p], s.hist, s.totals, ntile, kout, vout);
+            uint32_t *vout = p == npass - 1 ? (uint32_t *)perm : ((p % 2 == 0) ? s.vals_a : s.vals_b);
+            radix_pass(kin, vin, n, shift, widths[p], p > 0, items, s, kout, vout, mk, st);
             kin = kout;
             vin = vout;
             shift += widths[p];
         }
         *sorted_keys = kin;
-    } else {
-        *sorted_keys = s.keys_a;
     }
     const int sblk = (int)((n + 1 + kBlock - 1) / kBlock), cblk = (int)((g.ncell + 1 + kBlock - 1) / kBlock);
     mk->mark("segments", st);
@@ -380,11 +442,8 @@ hipError_t launch_bin_sort(const T *pos, const T *diam, int64_t n, const Geo<T> 
 hipError_t launch_stable_partition(const uint32_t *keys, int64_t n, int bits, const SortScratch &s, uint32_t *keys_out,
                                    uint32_t *ids_out, hipStream_t st) {
     if (n <= 0) return hipGetLastError();
-    const int ntile = sort_tiles(n);
-    hipLaunchKernelGGL(k_radix_hist, dim3(ntile), dim3(kBlock), 0, st, keys, n, 0, bits, s.hist, ntile);
-    hipLaunchKernelGGL(k_radix_prefix, dim3(1 << bits), dim3(kBlock), 0, st, s.hist, ntile, s.totals);
-    hipLaunchKernelGGL(k_radix_scatter<true>, dim3(ntile), dim3(kBlock), 0, st, keys, (const uint32_t *)nullptr, n, 0,
-                       bits, s.hist, s.totals, ntile, keys_out, ids_out);
+    Marker off;
+    radix_pass(keys, nullptr, n, 0, bits, true, sort_items(n, s.max_tiles), s, keys_out, ids_out, &off, st);
     return hipGetLastError();
 }
 

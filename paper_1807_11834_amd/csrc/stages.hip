@@ -1021,7 +1021,7 @@ template <typename T> hipError_t launch_stages(const StepArgs<T> &a, hipStream_t
     spec.nblk[SL_MAXPHI] = db;
     for (int k = 0; k < 3; ++k) spec.nblk[SL_FB + k] = db;
     spec.nblk[SL_VTOT] = a.n > 0 ? (int)pb : 0;
-    spec.nblk[SL_NOUT] = a.n > 0 ? sort_tiles(a.n) : 0;
+    spec.nblk[SL_NOUT] = a.n > 0 ? a.bin_tiles : 0;
     const int npart = a.n > 0 ? (int)pb : 0;   // k_drag
     for (int k = 0; k < 3; ++k) spec.nblk[SL_FP + k] = npart;
     spec.nblk[SL_NCLAMP] = npart;
