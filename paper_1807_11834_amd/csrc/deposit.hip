@@ -10,6 +10,7 @@
 // CIC: two passes through partial sums per group of source rows (see below);
 // every particle is staged once per pass.  NGP: one thread per cell sums its
 // own segment.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -76,81 +77,132 @@ __device__ __forceinline__ void write_gradient(const GradLoads<T> &v, int64_t c,
     }
 }
 
+// The values one particle deposits: V_p / V_b from its record (kPhi), its drag
+// (kForce) or (beta_p, beta_p u_p) (kSemi).  The solid fraction comes first in a
+// step, so its pass also makes the sorted copy of the particles that the later
+// stages read: it takes the record from the input-order copy pk through the
+// permutation (a random read that its arithmetic hides) and stores it at the
+// sorted position.
+template <typename T, int MODE>
+__device__ __forceinline__ void load_values(int64_t id, const vec4<T> &q, const T *__restrict__ drag,
+                                            const vec4<T> *__restrict__ src4, T inv_vb, T (&val)[DepNc<MODE>::value]) {
+    if constexpr (MODE == kForce) {
+        for (int c = 0; c < 3; ++c) val[c] = drag[3 * id + c];
+    } else if constexpr (MODE == kSemi) {
+        const vec4<T> b = src4[id];
+        val[0] = b.x;
+        val[1] = b.y;
+        val[2] = b.z;
+        val[3] = b.w;
+    } else {
+        val[0] = vol_over_vb(q.w, inv_vb);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // NGP (containing cell)
 // ---------------------------------------------------------------------------
+// A workgroup takes 64 consecutive cells at a time, whose particles are one run
+// of the sorted order.  The run passes through LDS in chunks, every load of a
+// chunk in flight together; lane (cell) of wave (component) then sums its
+// cell's part of the chunk in canonical order.  One thread per cell that loads
+// and adds particle by particle waits for two dependent loads per particle: 512
+// cells of 20 particles in FP64 took 3 + 12 us (sorted copy, solid fraction)
+// and 19 us (source), on two compute units.
+constexpr int kNgpCells = kWave, kNgpItems = 4, kNgpChunk = kBlock * kNgpItems;
+
 template <typename T, int SM, int MODE>
 __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restrict__ start,
-                                                        const vec4<T> *__restrict__ sp,
+                                                        const vec4<T> *__restrict__ pk, vec4<T> *__restrict__ sp,
                                                         const int32_t *__restrict__ perm,
-                                                        const T *__restrict__ drag,
-                                                        const vec4<T> *__restrict__ src4, int64_t n, Geo<T> g,
+                                                        const T *__restrict__ drag, int64_t n, Geo<T> g,
                                                         const T *__restrict__ P, const T *__restrict__ Plo,
                                                         T *__restrict__ out, T *__restrict__ out2, T *__restrict__ G,
                                                         double *__restrict__ part, int64_t ps) {
-    __shared__ double red[kWavesPerBlock];
-    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (c < g.ncell) {
-        const int32_t s = seg_clamp(start[c], n), e = seg_clamp(start[c + 1], n);
-        if constexpr (MODE == kSemi) {
-            CellSum<T, SM> acc[4];
-            for (int32_t p = s; p < e; ++p) {
-                int64_t id = perm[p];
-                if (id < 0 || id >= n) id = 0;
-                const vec4<T> b = src4[id];
-                acc[0].add(b.x);
-                acc[1].add(b.y);
-                acc[2].add(b.z);
-                acc[3].add(b.w);
-            }
-            out[c] = acc[0].value() * g.inv_vb;
-            for (int k = 0; k < 3; ++k) out2[k * g.ncell + c] = acc[k + 1].value() * g.inv_vb;
-            for (int k = 0; k < 4; ++k) v[k] = (double)(acc[k].value() * g.inv_vb);
-        } else if constexpr (MODE == kPhi) {
-            CellSum<T, SM> acc;
-            for (int32_t p = s; p < e; ++p) acc.add(vol_over_vb(sp[p].w, g.inv_vb));
-            out[c] = acc.value();
-            v[0] = (double)acc.value();
-        } else {
-            CellSum<T, SM> ax, ay, az;
-            for (int32_t p = s; p < e; ++p) {
-                int64_t id = perm[p];
-                if (id < 0 || id >= n) id = 0;
-                ax.add(drag[3 * id + 0]);
-                ay.add(drag[3 * id + 1]);
-                az.add(drag[3 * id + 2]);
-            }
-            const T fx = -ax.value() * g.inv_vb, fy = -ay.value() * g.inv_vb, fz = -az.value() * g.inv_vb;
-            out[c] = fx;
-            out[g.ncell + c] = fy;
-            out[2 * g.ncell + c] = fz;
-            v[0] = fx; v[1] = fy; v[2] = fz;
-            int cx, cy, cz;
-            decode_cell(c, g.nb, cx, cy, cz);
-            write_gradient(load_gradient(c, cx, cy, cz, g, P, Plo), c, cx, cy, cz, g, G);
+    constexpr int NC = DepNc<MODE>::value;
+    static_assert(NC <= kWavesPerBlock, "a wave per component");
+    __shared__ T val[NC][kNgpChunk];
+    const int lane = threadIdx.x % kWave, comp = threadIdx.x / kWave;
+    double vsum = 0.0, vmax = 0.0;
+    for (int64_t c0 = (int64_t)blockIdx.x * kNgpCells; c0 < g.ncell; c0 += (int64_t)gridDim.x * kNgpCells) {
+        const int64_t c = c0 + lane;
+        const int64_t c1 = c0 + kNgpCells < g.ncell ? c0 + kNgpCells : g.ncell;
+        const bool mine = c < g.ncell && comp < NC;
+        const int32_t rs = seg_clamp(start[c0], n), re = seg_clamp(start[c1], n);
+        int32_t s = 0, e = 0;
+        if (mine) {
+            s = seg_clamp(start[c], n);
+            e = seg_clamp(start[c + 1], n);
         }
+        GradLoads<T> gl;
+        int cx = 0, cy = 0, cz = 0;
+        const bool grad = MODE == kForce && comp == kWavesPerBlock - 1 && c < g.ncell;   // the wave with no component
+        if (grad) {
+            decode_cell(c, g.nb, cx, cy, cz);
+            gl = load_gradient(c, cx, cy, cz, g, P, Plo);
+        }
+        CellSum<T, SM> acc;
+        for (int64_t cs = rs; cs < re; cs += kNgpChunk) {   // uniform over the workgroup
+            const int m = (int)(re - cs < kNgpChunk ? re - cs : kNgpChunk);
+            int64_t id[kNgpItems];
+            vec4<T> q[kNgpItems];
+            T v[kNgpItems][NC];
+#pragma unroll
+            for (int u = 0; u < kNgpItems; ++u) {
+                const int k = (int)threadIdx.x + u * kBlock;
+                const int64_t i = perm[cs + (k < m ? k : 0)];
+                id[u] = (i < 0 || i >= n) ? 0 : i;   // perm is a permutation of [0, n)
+            }
+#pragma unroll
+            for (int u = 0; u < kNgpItems; ++u) {
+                if constexpr (MODE == kPhi) q[u] = pk[id[u]];
+                load_values<T, MODE>(id[u], q[u], drag, pk, g.inv_vb, v[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kNgpItems; ++u) {
+                const int k = (int)threadIdx.x + u * kBlock;
+                if (k >= m) continue;
+                if constexpr (MODE == kPhi) sp[cs + k] = q[u];
+#pragma unroll
+                for (int j = 0; j < NC; ++j) val[j][k] = v[u][j];
+            }
+            __syncthreads();
+            if (mine) {
+                const int32_t b0 = (int32_t)((s > cs ? s : cs) - cs), b1 = (int32_t)((e < cs + m ? e : cs + m) - cs);
+                for (int32_t k = b0; k < b1; ++k) acc.add(val[comp][k]);
+            }
+            __syncthreads();
+        }
+        if (mine) {
+            const T t = acc.value();
+            if constexpr (MODE == kPhi) {
+                out[c] = t;
+                vsum += (double)t;
+                vmax = fmax(vmax, (double)t);
+            } else if constexpr (MODE == kForce) {
+                const T f = -t * g.inv_vb;
+                out[comp * g.ncell + c] = f;
+                vsum += (double)f;
+            } else {
+                const T f = t * g.inv_vb;
+                if (comp == 0) out[c] = f;
+                else out2[(comp - 1) * g.ncell + c] = f;
+                vsum += (double)f;
+            }
+        }
+        if (grad) write_gradient(gl, c, cx, cy, cz, g, G);
+    }
+    const double t = wave_sum(vsum);
+    if (lane == 0 && comp < NC) {
+        const int slot = MODE == kPhi ? SL_PHISUM : (MODE == kForce ? SL_FB + comp : SL_KB + comp);
+        part[slot * ps + blockIdx.x] = t;
     }
     if constexpr (MODE == kPhi) {
-        const double t = block_sum(v[0], red);
-        const double m = block_max(v[0], red);
-        if (threadIdx.x == 0) {
-            part[SL_PHISUM * ps + blockIdx.x] = t;
-            part[SL_MAXPHI * ps + blockIdx.x] = m;
-        }
-    } else if constexpr (MODE == kForce) {
-        for (int k = 0; k < 3; ++k) {
-            const double t = block_sum(v[k], red);
-            if (threadIdx.x == 0) part[(SL_FB + k) * ps + blockIdx.x] = t;
-        }
-    } else {
-        const int slots[4] = {SL_KB, SL_KUB, SL_KUB + 1, SL_KUB + 2};
-        for (int k = 0; k < 4; ++k) {
-            const double t = block_sum(v[k], red);
-            if (threadIdx.x == 0) part[slots[k] * ps + blockIdx.x] = t;
-        }
+        const double m = wave_max(vmax);
+        if (lane == 0 && comp == 0) part[SL_MAXPHI * ps + blockIdx.x] = m;
     }
 }
+static_assert(SL_KUB == SL_KB + 1, "the semi-implicit sums are consecutive");
 
 // ---------------------------------------------------------------------------
 // CIC (trilinear to the 8 nearest bulk cell centres, folded at the walls)
@@ -171,13 +223,23 @@ __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restric
 // With GS = 2 a target row receives from 2 x 2 groups rather than from 3 x 3
 // source rows: the partial sums written and read back are 4/9 of one slot per
 // source row; GS = 1 trades that for four times the waves.
+//
+// The staged values of a particle are read by three lanes (its cell's and the
+// two neighbours'), each lane at a place of its own, so the reads conflict on
+// the LDS banks and bound the pass.  They are kept as 16-byte records, one read
+// for four values: with one 4-byte array per value the bed's solid fraction took
+// 128 us and its source 270 us.
 template <typename T, int MODE> struct RowStage {
-    int node[kWavesPerBlock][kChunk];                  // x-stencil nodes lo | hi << 16
-    T tx[kWavesPerBlock][kChunk];                      // weight of hi
-    T wy[3][kWavesPerBlock][kChunk];                   // weight on target rows y'-1, y', y'+1
-    T wz[3][kWavesPerBlock][kChunk];                   // weight on target layers z'-1, z', z'+1
-    T val[DepNc<MODE>::value][kWavesPerBlock][kChunk]; // V_p / V_b, F_p, or (beta_p, beta_p u_p)
+    vec4<T> wy[kWavesPerBlock][kChunk];   // weights on target rows y'-1, y', y'+1; weight of the upper x node
+    vec4<T> wz[kWavesPerBlock][kChunk];   // weights on target layers z'-1, z', z'+1; x nodes lo | hi << 16 (bits)
+    // V_p / V_b, F_p (and a word unused), or (beta_p, beta_p u_p)
+    typename std::conditional<MODE == kPhi, T, vec4<T>>::type val[kWavesPerBlock][kChunk];
 };
+
+__device__ __forceinline__ float as_value(int32_t b, float) { return __int_as_float(b); }
+__device__ __forceinline__ double as_value(int32_t b, double) { return __longlong_as_double((long long)b); }
+__device__ __forceinline__ int32_t as_bits(float v) { return __float_as_int(v); }
+__device__ __forceinline__ int32_t as_bits(double v) { return (int32_t)__double_as_longlong(v); }
 
 // Row-pass sums s += w v under the step's sum mode: FP32 with Kahan
 // compensation (the product w v formed by an FMA against the running
@@ -214,9 +276,9 @@ template <int G> struct GroupSlots { static constexpr int value = G == 1 ? 3 : 2
 template <typename T, int SM, int MODE, int JY, int KZ, int A>
 __device__ __forceinline__ void deposit_source_row(RowSum<T, SM> (&acc)[A][A][DepNc<MODE>::value],
                                                    RowStage<T, MODE> &st, int w, int lane, int x0, int ys, int zs,
-                                                   const int32_t *__restrict__ start, const vec4<T> *__restrict__ sp,
-                                                   const int32_t *__restrict__ perm, const T *__restrict__ drag,
-                                                   const vec4<T> *__restrict__ src4, int64_t n, const Geo<T> &g) {
+                                                   const int32_t *__restrict__ start, const vec4<T> *__restrict__ pk,
+                                                   vec4<T> *__restrict__ sp, const int32_t *__restrict__ perm,
+                                                   const T *__restrict__ drag, int64_t n, const Geo<T> &g) {
     constexpr int NC = DepNc<MODE>::value;
     using W = typename RowSum<T, SM>::W;
     const int nbx = g.nb[0], nby = g.nb[1], nbz = g.nb[2];
@@ -225,6 +287,11 @@ __device__ __forceinline__ void deposit_source_row(RowSum<T, SM> (&acc)[A][A][De
     const int xa = x0 > 0 ? x0 - 1 : 0;
     const int xb = (x0 + kWave < nbx ? x0 + kWave : nbx - 1);
     const int32_t rs = seg_clamp(start[srow + xa], n), re = seg_clamp(start[srow + xb + 1], n);
+    int32_t os = 0, oe = 0;   // the segment's own particles (its neighbours' waves store theirs)
+    if constexpr (MODE == kPhi) {
+        os = seg_clamp(start[srow + x0], n);
+        oe = seg_clamp(start[srow + (x0 + kWave < nbx ? x0 + kWave : nbx)], n);
+    }
     int32_t ls = 0, le = 0;
     if (x < nbx) {
         ls = seg_clamp(start[srow + (x > 0 ? x - 1 : 0)], n);
@@ -234,8 +301,8 @@ __device__ __forceinline__ void deposit_source_row(RowSum<T, SM> (&acc)[A][A][De
         const int32_t m = ((cs + kChunk < re) ? cs + kChunk : re) - cs;
         const int32_t ce = cs + m;
         // Staging: every load of the chunk is issued before any is used, so the
-        // random-access value gather through perm costs one round trip per
-        // chunk rather than one per 64 particles.
+        // random-access gathers through perm cost one round trip per chunk
+        // rather than one per 64 particles.
         constexpr int KS = kChunk / kWave;
         vec4<T> q[KS];
         int64_t id[KS];
@@ -244,28 +311,17 @@ __device__ __forceinline__ void deposit_source_row(RowSum<T, SM> (&acc)[A][A][De
             const int k = lane + u * kWave;
             id[u] = 0;
             if (k < m) {
-                q[u] = sp[cs + k];
-                if constexpr (MODE != kPhi) {
-                    const int64_t i = perm[cs + k];
-                    id[u] = (i < 0 || i >= n) ? 0 : i;   // perm is a permutation of [0, n)
-                }
+                if constexpr (MODE != kPhi) q[u] = sp[cs + k];
+                const int64_t i = perm[cs + k];
+                id[u] = (i < 0 || i >= n) ? 0 : i;   // perm is a permutation of [0, n)
             }
         }
         T val[KS][NC];
 #pragma unroll
         for (int u = 0; u < KS; ++u) {
             if (lane + u * kWave < m) {
-                if constexpr (MODE == kForce) {
-                    for (int c = 0; c < 3; ++c) val[u][c] = drag[3 * id[u] + c];
-                } else if constexpr (MODE == kSemi) {
-                    const vec4<T> b = src4[id[u]];
-                    val[u][0] = b.x;
-                    val[u][1] = b.y;
-                    val[u][2] = b.z;
-                    val[u][3] = b.w;
-                } else {
-                    val[u][0] = vol_over_vb(q[u].w, g.inv_vb);
-                }
+                if constexpr (MODE == kPhi) q[u] = pk[id[u]];
+                load_values<T, MODE>(id[u], q[u], drag, pk, g.inv_vb, val[u]);
             }
         }
 #pragma unroll
@@ -275,16 +331,30 @@ __device__ __forceinline__ void deposit_source_row(RowSum<T, SM> (&acc)[A][A][De
                 const Axis<T> ax = cic_axis(q[u].x, g.sb[0], nbx);
                 const Axis<T> ay = cic_axis(q[u].y, g.sb[1], nby);
                 const Axis<T> az = cic_axis(q[u].z, g.sb[2], nbz);
-                st.node[w][k] = ax.lo | (ax.hi << 16);
-                st.tx[w][k] = ax.t;
                 T wy[3], wz[3];
                 row_weights(ay, ys, wy);
                 row_weights(az, zs, wz);
-                for (int j = 0; j < 3; ++j) {
-                    st.wy[j][w][k] = wy[j];
-                    st.wz[j][w][k] = wz[j];
+                vec4<T> r;
+                r.x = wy[0];
+                r.y = wy[1];
+                r.z = wy[2];
+                r.w = ax.t;
+                st.wy[w][k] = r;
+                r.x = wz[0];
+                r.y = wz[1];
+                r.z = wz[2];
+                r.w = as_value(ax.lo | (ax.hi << 16), T(0));
+                st.wz[w][k] = r;
+                if constexpr (MODE == kPhi) {
+                    st.val[w][k] = val[u][0];
+                    if (cs + k >= os && cs + k < oe) sp[cs + k] = q[u];
+                } else {
+                    r.x = val[u][0];
+                    r.y = val[u][1];
+                    r.z = val[u][2];
+                    r.w = NC > 3 ? val[u][NC - 1] : T(0);
+                    st.val[w][k] = r;
                 }
-                for (int c = 0; c < NC; ++c) st.val[c][w][k] = val[u][c];
             }
         }
         wave_sync();
@@ -293,20 +363,23 @@ __device__ __forceinline__ void deposit_source_row(RowSum<T, SM> (&acc)[A][A][De
         // of the zero weights (5 of the 9 target rows, a third of the x
         // visits) would diverge and save nothing; their terms add zeros.
         for (int32_t k = b0; k < b1; ++k) {
-            const int nd = st.node[w][k];
-            const T t = st.tx[w][k];
+            const vec4<T> ry = st.wy[w][k], rz = st.wz[w][k];
+            const int nd = as_bits(rz.w);
+            const T t = ry.w;
             T wx = T(0);
             if ((nd & 0xffff) == x) wx += T(1) - t;
             if ((nd >> 16) == x) wx += t;
             W v[NC];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) v[c] = W(wx) * W(st.val[c][w][k]);
-            W wy[3], wz[3];
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                wy[j] = W(st.wy[j][w][k]);
-                wz[j] = W(st.wz[j][w][k]);
+            if constexpr (MODE == kPhi) {
+                v[0] = W(wx) * W(st.val[w][k]);
+            } else {
+                const vec4<T> rv = st.val[w][k];
+                v[0] = W(wx) * W(rv.x);
+                v[1] = W(wx) * W(rv.y);
+                v[2] = W(wx) * W(rv.z);
+                if constexpr (NC > 3) v[NC - 1] = W(wx) * W(rv.w);
             }
+            const W wy[3] = {W(ry.x), W(ry.y), W(ry.z)}, wz[3] = {W(rz.x), W(rz.y), W(rz.z)};
 #pragma unroll
             for (int kz = 0; kz < 3; ++kz) {
 #pragma unroll
@@ -323,10 +396,9 @@ __device__ __forceinline__ void deposit_source_row(RowSum<T, SM> (&acc)[A][A][De
 
 template <typename T, int SM, int MODE, int GS>
 __global__ __launch_bounds__(kBlock) void k_deposit_rows(const int32_t *__restrict__ start,
-                                                         const vec4<T> *__restrict__ sp,
+                                                         const vec4<T> *__restrict__ pk, vec4<T> *__restrict__ sp,
                                                          const int32_t *__restrict__ perm,
-                                                         const T *__restrict__ drag,
-                                                         const vec4<T> *__restrict__ src4, int64_t n, Geo<T> g,
+                                                         const T *__restrict__ drag, int64_t n, Geo<T> g,
                                                          T *__restrict__ partial) {
     constexpr int NC = DepNc<MODE>::value, A = GS + 2, S = GroupSlots<GS>::value;
     __shared__ RowStage<T, MODE> st;
@@ -344,17 +416,17 @@ __global__ __launch_bounds__(kBlock) void k_deposit_rows(const int32_t *__restri
     const int x = x0 + lane;
     const int y0 = GS * gy, z0 = GS * gz;
     RowSum<T, SM> acc[A][A][NC];   // [target z - (z0 - 1)][target y - (y0 - 1)][component]
-    deposit_source_row<T, SM, MODE, 0, 0, A>(acc, st, w, lane, x0, y0, z0, start, sp, perm, drag, src4, n, g);
+    deposit_source_row<T, SM, MODE, 0, 0, A>(acc, st, w, lane, x0, y0, z0, start, pk, sp, perm, drag, n, g);
     if constexpr (GS == 2) {
         if (y0 + 1 < nby)
-            deposit_source_row<T, SM, MODE, 1, 0, A>(acc, st, w, lane, x0, y0 + 1, z0, start, sp, perm, drag, src4, n,
+            deposit_source_row<T, SM, MODE, 1, 0, A>(acc, st, w, lane, x0, y0 + 1, z0, start, pk, sp, perm, drag, n,
                                                      g);
         if (z0 + 1 < nbz) {
-            deposit_source_row<T, SM, MODE, 0, 1, A>(acc, st, w, lane, x0, y0, z0 + 1, start, sp, perm, drag, src4, n,
+            deposit_source_row<T, SM, MODE, 0, 1, A>(acc, st, w, lane, x0, y0, z0 + 1, start, pk, sp, perm, drag, n,
                                                      g);
             if (y0 + 1 < nby)
-                deposit_source_row<T, SM, MODE, 1, 1, A>(acc, st, w, lane, x0, y0 + 1, z0 + 1, start, sp, perm, drag,
-                                                         src4, n, g);
+                deposit_source_row<T, SM, MODE, 1, 1, A>(acc, st, w, lane, x0, y0 + 1, z0 + 1, start, pk, sp, perm, drag,
+                                                         n, g);
         }
     }
     if (x >= nbx) return;
@@ -448,10 +520,10 @@ __global__ __launch_bounds__(kBlock) void k_deposit_sum(const T *__restrict__ pa
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-int deposit_blocks(const int nb[3], int64_t ncell, int cic) {
-    (void)nb;
-    (void)cic;
-    return (int)((ncell + kBlock - 1) / kBlock);   // NGP kernel and CIC pass 2
+int deposit_blocks(int64_t ncell, int cic, int64_t part_stride) {
+    if (cic) return (int)((ncell + kBlock - 1) / kBlock);   // pass 2
+    // as many workgroups as there are partials for, each looping over its groups of cells
+    return (int)std::min((ncell + kNgpCells - 1) / kNgpCells, part_stride);
 }
 
 static int64_t row_waves(const int nb[3], int G) {
@@ -470,13 +542,14 @@ static int row_blocks(const int nb[3], int G) {
 
 template <typename T, int SM, int MODE>
 static int launch_deposit(const StepArgs<T> &a, T *out, T *out2, hipStream_t st, const char *sum_mark) {
-    const int nblk = deposit_blocks(a.g.nb, a.g.ncell, a.cic);
-    const vec4<T> *src4 = a.uf4;   // (beta, beta u_p) per particle once the drag has run
+    const int nblk = deposit_blocks(a.g.ncell, a.cic, a.part_stride);
+    // the packed particles until the velocity is sampled; (beta, beta u_p) once the drag has run
+    const vec4<T> *pk = a.uf4;
     if (a.cic) {
         auto rows_and_sums = [&](auto gc) {
             constexpr int GS = decltype(gc)::value;
             hipLaunchKernelGGL((k_deposit_rows<T, SM, MODE, GS>), dim3(row_blocks(a.g.nb, GS)), dim3(kBlock), 0, st,
-                               a.start, a.sp, a.perm, a.drag, src4, a.n, a.g, a.dep_partial);
+                               a.start, pk, a.sp, a.perm, a.drag, a.n, a.g, a.dep_partial);
             a.mk->mark(sum_mark, st);
             hipLaunchKernelGGL((k_deposit_sum<T, SM, MODE, GS>), dim3(nblk), dim3(kBlock), 0, st, a.dep_partial, a.g,
                                a.P, a.Plo, out, out2, a.G, a.part, a.part_stride);
@@ -484,8 +557,8 @@ static int launch_deposit(const StepArgs<T> &a, T *out, T *out2, hipStream_t st,
         if (deposit_group(a.g.nb) == 1) rows_and_sums(std::integral_constant<int, 1>{});
         else rows_and_sums(std::integral_constant<int, 2>{});
     } else {
-        hipLaunchKernelGGL((k_deposit_ngp<T, SM, MODE>), dim3(nblk), dim3(kBlock), 0, st, a.start, a.sp, a.perm,
-                           a.drag, src4, a.n, a.g, a.P, a.Plo, out, out2, a.G, a.part, a.part_stride);
+        hipLaunchKernelGGL((k_deposit_ngp<T, SM, MODE>), dim3(nblk), dim3(kBlock), 0, st, a.start, pk,
+                           a.sp, a.perm, a.drag, a.n, a.g, a.P, a.Plo, out, out2, a.G, a.part, a.part_stride);
     }
     return nblk;
 }

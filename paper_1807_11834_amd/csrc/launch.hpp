@@ -95,7 +95,7 @@ template <typename T> struct StepArgs {
     // scratch
     vec4<T> *sp;     // sorted particles (x, y, z, d)
     vec4<T> *uf4;    // per particle (input order): packed (x, y, z, d) from binning until the
-                     // gather has read it, then fluid velocity and void fraction until the
+                     // solid-fraction pass has read it, then fluid velocity and void fraction until the
                      // drag has read it, then (beta, beta u_p) when semi
     T *Plo;          // [ncell] low word of the restricted pressure (Kahan compensation)
     T *dep_partial;  // [4][nc][ncell] per-source-group partial sums of the CIC deposition (nc <= 4)
@@ -139,7 +139,7 @@ int64_t bricks_of(const int nb[3]);
 template <typename T, int SM> int launch_deposit_phi(const StepArgs<T> &a, hipStream_t st);
 template <typename T, int SM> int launch_deposit_force(const StepArgs<T> &a, hipStream_t st);
 template <typename T, int SM> int launch_deposit_semi(const StepArgs<T> &a, hipStream_t st);
-int deposit_blocks(const int nb[3], int64_t ncell, int cic);
+int deposit_blocks(int64_t ncell, int cic, int64_t part_stride);
 // Source rows per group of the CIC row pass (1 or 2 in y and z): the partial
 // buffer holds (G == 1 ? 9 : 4) slots per cell and component.
 int deposit_group(const int nb[3]);

@@ -3,10 +3,9 @@
 //
 // Kernel order on the caller's stream (after binning/sorting, sort.hip):
 //
-//   k_gather       sorted copy sp = (x, y, z, d) of the particles: the packed
-//                  input-order copy that binning wrote (clamped into the box),
-//                  permuted, one 16-byte (FP32) read per particle.
-//   deposit phi    (deposit.hip)
+//   deposit phi    (deposit.hip), which also makes the sorted copy sp = (x, y,
+//                  z, d) of the particles from the packed input-order copy that
+//                  binning wrote (clamped into the box).
 //   k_restrict     one thread per bulk cell streams its r^3 fine children of
 //                  u, v, w, p (one 16-byte row load per (z, y) child row for
 //                  r = 4) and writes the compensated averages U, P.
@@ -92,20 +91,6 @@ template <typename T, int R> __device__ __forceinline__ void store_row(T *__rest
         __builtin_nontemporal_store(q, reinterpret_cast<NtVec<double, 2> *>(p));
     } else {
         for (int k = 0; k < R; ++k) __builtin_nontemporal_store(v[k], p + k);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// k_gather: sorted particle copies
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_gather(const int32_t *__restrict__ perm, const vec4<T> *__restrict__ pk,
-                                                   int64_t n, vec4<T> *__restrict__ sp) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) {
-        int64_t p = perm[i];
-        if (p < 0 || p >= n) p = 0;   // perm is a permutation of [0, n); guards the load
-        sp[i] = pk[p];
     }
 }
 
@@ -1016,7 +1001,7 @@ template <typename T> hipError_t launch_stages(const StepArgs<T> &a, hipStream_t
         spec.nblk[s] = (int)cb;
         spec.scale[s] = 1.0;
     }
-    const int db = deposit_blocks(a.g.nb, a.g.ncell, a.cic);
+    const int db = deposit_blocks(a.g.ncell, a.cic, a.part_stride);
     spec.nblk[SL_PHISUM] = db;
     spec.nblk[SL_MAXPHI] = db;
     for (int k = 0; k < 3; ++k) spec.nblk[SL_FB + k] = db;
@@ -1050,9 +1035,6 @@ template <typename T> hipError_t launch_stages(const StepArgs<T> &a, hipStream_t
         if (spec.nblk[s] > a.part_stride) return hipErrorInvalidValue;   // partials would not fit
 
     if (phases & kPhaseDeposit) {
-        if (a.n > 0) a.mk->mark("gather", st);
-        if (a.n > 0)
-            hipLaunchKernelGGL(k_gather<T>, dim3(pb), dim3(kBlock), 0, st, a.perm, a.uf4, a.n, a.sp);
         a.mk->mark("deposit_phi", st);
         if constexpr (std::is_same<T, float>::value) {
             if (sm == kSumKahan) launch_deposit_phi<T, kSumKahan>(a, st);
