@@ -40,19 +40,17 @@ def kernel_alg_bytes(name, n, ncell, nfine, fsz):
         (4 fsz).
     restrict: u, v, w, p read, U, P written (the other velocity sources).
     restrict_p: the pressure alone (beside the fused kernel).
-    prolong: F_fpi written on the fine grid (3 fsz per fine cell) and read on
-        the bulk grid (3 fsz per bulk cell); prolong_eps: the porosity
-        (1 + 1); prolong_semi: K and KU (4 + 4).
+    prolong: the porosity and F_fpi written on the fine grid (4 fsz per fine
+        cell) and read on the bulk grid (4 fsz per bulk cell); twice that with
+        the semi-implicit split, whose K and KU are prolonged with them.
     """
     if name == "restrict_lookup":
         return 3 * fsz * nfine + 3 * fsz * ncell + n * 8 * fsz
     if name == "restrict":
         return 4 * fsz * nfine + 4 * fsz * ncell
-    if name in ("restrict_p", "prolong_eps"):
+    if name == "restrict_p":
         return fsz * nfine + fsz * ncell
     if name == "prolong":
-        return 3 * fsz * nfine + 3 * fsz * ncell
-    if name == "prolong_semi":
         return 4 * fsz * nfine + 4 * fsz * ncell
     return None
 
@@ -73,7 +71,7 @@ PROFILE_NAMES = {
     "restrict_lookup": "cpl::k_restrict_brick<float, 4, 2>",
     "restrict_p": "cpl::k_restrict_planes<float, 2, 3, 4, false>",
     "restrict": "cpl::k_restrict_planes<float, 2, 0, 4, false>",
-    "prolong": "cpl::k_prolong<float, 4, 3>",
+    "prolong": "cpl::k_prolong<float, 4>",
     "mlp_infer": "cpl::mlp::k_infer",
 }
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "traffic_bed128.json")
@@ -514,14 +512,14 @@ def semi_leg(args, cfg, pos, vel, diam, fine, plain_ms, n, g, fsz, dev):
     prolonged in addition): time per step, the extra kernels and the prolongation
     roofline of K, KU, and the conservation of their sums."""
     ms, kt, d = _time_variant(args, dataclasses.replace(cfg, semi_implicit=1), pos, vel, diam, fine, n, dev)
-    kern = {k: v for k, v in kt.items() if k in ("deposit_semi", "deposit_semi_sum", "prolong_semi")}
-    ab = kernel_alg_bytes("prolong_semi", n, g.n_bulk, g.n_fine, fsz)
-    pr = kern.get("prolong_semi")
+    kern = {k: v for k, v in kt.items() if k in ("deposit_semi", "deposit_semi_sum", "prolong")}
+    ab = 2 * kernel_alg_bytes("prolong", n, g.n_bulk, g.n_fine, fsz)   # eps, F_fpi, K, KU
+    pr = kern.get("prolong")
     print(f"# semi-implicit split: {ms:.3f} ms/step", file=sys.stderr, flush=True)
     return {"ms_per_step": ms, "value": n / (ms * 1e-3), "extra_ms_vs_plain": ms - plain_ms,
             "kernels_avg_ms": {k: round(v, 4) for k, v in kern.items()},
-            "prolong_semi_GBps": round(ab / (pr * 1e-3) / 1e9, 1) if pr else None,
-            "prolong_semi_frac_hbm": round(ab / (pr * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4) if pr else None,
+            "prolong_GBps": round(ab / (pr * 1e-3) / 1e9, 1) if pr else None,
+            "prolong_frac_hbm": round(ab / (pr * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4) if pr else None,
             "conservation": {"K_b/K_p-1": d["K_b"] / d["K_p"] - 1 if d["K_p"] else 0.0,
                              "K_f/K_b-1": d["K_f"] / d["K_b"] - 1 if d["K_b"] else 0.0}}
 

@@ -1,4 +1,5 @@
 // api.hip -- C ABI of the coupling library (see include/couple.h).
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -105,8 +106,8 @@ struct ScratchPlan {
     }
 };
 
-// `tight`: histograms for the fewest tiles a sort can take (the sort then uses
-// its largest tiles) instead of the most.
+// `tight`: the least scratch a step runs in (histograms for the fewest tiles a
+// sort can take, diagnostic partials for fewer workgroups of the prolongation).
 static ScratchPlan scratch_plan(const couple_config &c, int64_t nmax, bool tight = false) {
     ScratchPlan p{};
     const int64_t ncell = (int64_t)c.nb[0] * c.nb[1] * c.nb[2];
@@ -114,9 +115,10 @@ static ScratchPlan scratch_plan(const couple_config &c, int64_t nmax, bool tight
     const int64_t ntile = p.max_tiles = tight ? sort_tiles_min(nmax) : sort_tiles_max(nmax);
     const int64_t pblk = (nmax + kBlock - 1) / kBlock, cblk = (ncell + kBlock - 1) / kBlock;
     // one FP64 partial per workgroup and slot: the stride covers the largest
-    // grid of any kernel that writes partials
+    // grid of any kernel that writes partials (the prolongation and the NGP
+    // deposition take no more workgroups than that)
     const int64_t mblk = mlp_check_blocks(bricks_of(c.nb));
-    const int64_t prblk = prolong_tiles(c.nb);
+    const int64_t prblk = tight ? 1 : std::min<int64_t>(prolong_items(c.nb, c.ratio), 1024);
     p.part_stride = 1;
     for (int64_t b : {pblk, cblk, ntile, mblk, prblk})
         if (b > p.part_stride) p.part_stride = b;

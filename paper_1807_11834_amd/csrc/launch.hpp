@@ -144,8 +144,8 @@ int deposit_blocks(int64_t ncell, int cic, int64_t part_stride);
 // buffer holds (G == 1 ? 9 : 4) slots per cell and component.
 int deposit_group(const int nb[3]);
 
-// Workgroups of a prolongation launch (stages.hip), one FP64 partial each per
-// prolonged field.
-int64_t prolong_tiles(const int nb[3]);
+// Work items per field of a prolongation (stages.hip), which takes as many
+// workgroups per field, one FP64 partial each, or as many as the partials allow.
+int64_t prolong_items(const int nb[3], int ratio);
 
 }  // namespace cpl

@@ -22,9 +22,9 @@
 //                  with the semi-implicit split also (beta, beta u_p).
 //   deposit force  (deposit.hip), with the bulk pressure gradient; then the
 //                  semi-implicit K, KU when requested.
-//   k_prolong      one thread per bulk cell writes its r^3 fine children of
-//                  eps and F_fpi (a second launch: K and KU): conservative
-//                  trilinear T_f + D_c with the 27-neighbour values in registers.
+//   k_prolong      one fine plane of a tile of 256 bulk cells per work item, one
+//                  launch for eps, F_fpi (and K, KU): conservative trilinear
+//                  T_f + D_c from the tile staged in LDS.
 //   k_diag         fixed-order reduction of the per-workgroup FP64 partials.
 #include <type_traits>
 
@@ -710,145 +710,154 @@ __device__ __forceinline__ T wsum3(int l, T a0, T a1, T a2) {
     return s;
 }
 
-// The bulk fields a prolongation launch transfers (nf <= 4), their fine outputs
-// and the diagnostic slots of their fine sums; field 0 is optionally
-// complemented (the solid fraction phi is prolonged as the porosity 1 - phi).
+// The bulk fields a prolongation launch transfers (blockIdx.y), their fine
+// outputs and the diagnostic slots of their fine sums; field 0 is the solid
+// fraction, prolonged as the porosity 1 - phi.
+constexpr int kMaxProlong = 8;
 template <typename T> struct ProlongSet {
-    const T *B[4];
-    T *out[4];
-    int slot[4];
-    int complement0;
-    int nf;
+    const T *B[kMaxProlong];
+    T *out[kMaxProlong];
+    int slot[kMaxProlong];
 };
 
-// One workgroup per tile of kPTX x kPTY bulk cells of one layer (a wave per
-// bulk row).  The bulk values of the tile's 3 x 3 x 3 neighbourhoods (the tile
-// with a one-cell halo, indices clamped at the walls) are staged in LDS for all
-// NF fields at once: one memory round trip per workgroup, and each cell reads
-// its 27 values at fixed offsets from one LDS address.  Each thread then
-// writes its cell's r^3 fine children of every field, one r-wide row at a
-// time (a wave's store covers kPTX cells' children on one fine row).
-constexpr int kPTX = kWave, kPTY = kBlock / kWave;
-constexpr int kPHX = kPTX + 2, kPHY = kPTY + 2, kPHalo = 3 * kPHY * kPHX;   // staged values per field
+// The fine-grid writes bound this kernel, and the rate of writing depends on
+// which addresses are written together: bare 16-byte stores over 512 x 512 x
+// 1024 fine cells run at 6.7 TB/s in address order, at 5.5 TB/s when a workgroup
+// writes all r planes of a tile of 64 x 4 bulk cells and at 6.5 TB/s when it
+// writes one fine plane of a tile of 128 x 2.  So a work item is one fine plane
+// of a tile of 256 bulk cells (one layer, 2^xs wide), items in the order of the
+// planes, and one launch takes every field (blockIdx.y).
+//
+// A work item stages the tile and its one-cell halo (indices clamped at the
+// walls) in LDS, combined over the three layers on the way: the trilinear value
+// at the item's plane and the children's mean along z.  Each thread then
+// interpolates along y and x and writes its cell's r rows of the plane, with the
+// defect D from the means (see above).  Workgroups loop over the items, as many
+// workgroups as there are diagnostic partials for.
+constexpr int kPMaxX = 7, kPMinX = 4;   // tiles of 128 x 2 ... 16 x 16 cells
+constexpr int kPStage = ((1 << kPMaxX) + 2) * ((kBlock >> kPMaxX) + 2);   // staged values of the widest tile
+static_assert(((1 << kPMinX) + 2) * ((kBlock >> kPMinX) + 2) <= kPStage, "the widest tile has the most halo");
 
-int64_t prolong_tiles(const int nb[3]) {
-    return (int64_t)((nb[0] + kPTX - 1) / kPTX) * ((nb[1] + kPTY - 1) / kPTY) * nb[2];
+// Tile width: the widest that pads x by at most a quarter, else the widest of
+// those that pad it least.
+static int prolong_shift(int nx) {
+    auto padded = [&](int xs) { return (((int64_t)nx + (1 << xs) - 1) >> xs) << xs; };
+    for (int xs = kPMaxX; xs >= kPMinX; --xs)
+        if (4 * padded(xs) <= 5 * (int64_t)nx) return xs;
+    for (int xs = kPMaxX; xs > kPMinX; --xs)
+        if (padded(xs) == padded(kPMinX)) return xs;
+    return kPMinX;
+}
+int64_t prolong_items(const int nb[3], int ratio) {
+    const int xs = prolong_shift(nb[0]), ys = 8 - xs;
+    return (((int64_t)nb[0] + (1 << xs) - 1) >> xs) * (((int64_t)nb[1] + (1 << ys) - 1) >> ys) * nb[2] * ratio;
+}
+static_assert(kBlock == 256, "a tile has 2^8 cells");
+
+// Workgroups per field: one per item, or as many as there are partials (a
+// multiple of the XCDs, so that each keeps its share of the items).
+static int64_t prolong_blocks(const int nb[3], int ratio, int64_t part_stride) {
+    const int64_t items = prolong_items(nb, ratio);
+    if (items <= part_stride) return items;
+    return part_stride >= 8 ? part_stride / 8 * 8 : part_stride;
 }
 
-template <typename T, int R, int NF>
-__global__ __launch_bounds__(kBlock) void k_prolong(StepArgs<T> a, ProlongSet<T> fs) {
-    __shared__ T sb[NF][3][kPHY][kPHX];
+template <typename T, int R>
+__global__ __launch_bounds__(kBlock) void k_prolong(StepArgs<T> a, ProlongSet<T> fs, int xs, int64_t items) {
+    __shared__ T szi[kPStage], szm[kPStage], sbc[kPStage];   // plane value, mean along z, centre layer
     __shared__ double red[kWavesPerBlock];
     const Geo<T> &g = a.g;
-    const int tnx = (g.nb[0] + kPTX - 1) / kPTX, tny = (g.nb[1] + kPTY - 1) / kPTY;
-    const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int cx0 = (int)(tile % tnx) * kPTX, cy0 = (int)((tile / tnx) % tny) * kPTY;
-    const int cz = (int)(tile / ((int64_t)tnx * tny));
+    const int f = blockIdx.y, ys = 8 - xs;
+    const int W = 1 << xs, H = 1 << ys, pitch = W + 2;
+    const T *__restrict__ B = fs.B[f];
+    T *__restrict__ out = fs.out[f];
+    const int tnx = (g.nb[0] + W - 1) >> xs, tny = (g.nb[1] + H - 1) >> ys;
     const int64_t nx = g.nb[0], nxy = (int64_t)g.nb[0] * g.nb[1];
-    // staging: every load is issued before the first LDS write
-    constexpr int kIt = (kPHalo + kBlock - 1) / kBlock;
-    T v[NF][kIt];
+    const int64_t nfx = g.nf[0], nfxy = (int64_t)g.nf[0] * g.nf[1];
+    const int i = (int)threadIdx.x & (W - 1), j = (int)threadIdx.x >> xs;
+    double sum = 0.0;
+    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+        const int64_t item = xcd_tile(it, items);
+        const int cx0 = (int)(item % tnx) << xs, cy0 = (int)((item / tnx) % tny) << ys;
+        const int fz = (int)(item / ((int64_t)tnx * tny)), cz = fz / R, lz = fz % R;
+        // staging: the H + 2 rows of the tile in two rounds of H, and the two
+        // halo columns, every load issued before the first LDS write
+        const int64_t zl = (cz > 0 ? cz - 1 : 0) * nxy, zc = cz * nxy, zh = (cz + 1 < g.nb[2] ? cz + 1 : cz) * nxy;
+        const int hr = (int)threadIdx.x >> 1;   // halo column: row hr, left or right
+        int si[3], sj[3];
+        bool on[3] = {true, j + H < H + 2, (int)threadIdx.x < 2 * (H + 2)};
+        si[0] = si[1] = i + 1;
+        sj[0] = j;
+        sj[1] = j + H;
+        si[2] = (threadIdx.x & 1) ? W + 1 : 0;
+        sj[2] = hr;
+        T v[3][3];
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            const int e = it * kBlock + (int)threadIdx.x;
-            v[f][it] = T(0);
-            if (e < kPHalo) {
-                const int i = e % kPHX, j = (e / kPHX) % kPHY, k = e / (kPHX * kPHY);
-                const int gx = clampi(cx0 - 1 + i, g.nb[0]), gy = clampi(cy0 - 1 + j, g.nb[1]),
-                          gz = clampi(cz - 1 + k, g.nb[2]);
-                v[f][it] = fs.B[f][gz * nxy + gy * nx + gx];
+        for (int u = 0; u < 3; ++u) {
+            const int64_t o = clampi(cy0 - 1 + sj[u], g.nb[1]) * nx + clampi(cx0 - 1 + si[u], g.nb[0]);
+            if (on[u]) {
+                v[u][0] = B[zl + o];
+                v[u][1] = B[zc + o];
+                v[u][2] = B[zh + o];
             }
         }
+        // weights of the plane on the layers below, at and above (wsum3 with the
+        // plane known at run time)
+        const T oz = (T(lz) + T(0.5)) / T(R) - T(0.5);
+        const T w0 = oz < T(0) ? -oz : T(0), w1 = T(1) - (oz < T(0) ? -oz : oz), w2 = oz > T(0) ? oz : T(0);
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
+        for (int u = 0; u < 3; ++u) {
+            if (!on[u]) continue;
+            if (f == 0)
 #pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            const int e = it * kBlock + (int)threadIdx.x;
-            if (e < kPHalo) (&sb[f][0][0][0])[e] = (f == 0 && fs.complement0) ? T(1) - v[f][it] : v[f][it];
+                for (int k = 0; k < 3; ++k) v[u][k] = T(1) - v[u][k];
+            const int e = sj[u] * pitch + si[u];
+            szi[e] = w1 * v[u][1] + (w0 * v[u][0] + w2 * v[u][2]);
+            szm[e] = T(ChildW<R>::mean(0)) * v[u][0] + T(ChildW<R>::mean(1)) * v[u][1] +
+                     T(ChildW<R>::mean(2)) * v[u][2];
+            sbc[e] = v[u][1];
         }
-    __syncthreads();
-
-    const int lane = (int)threadIdx.x % kWave, w = (int)threadIdx.x / kWave;
-    const int cx = cx0 + lane, cy = cy0 + w;
-    const bool inside = cx < g.nb[0] && cy < g.nb[1];
-    const int64_t c = cz * nxy + cy * nx + cx;
-    const bool counted = inside && c >= a.own_c0 && c < a.own_c1;   // owned cells enter the fine-grid sums
-    double sums[NF];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) sums[f] = 0.0;
-    if (inside) {
-        const int64_t nfx = g.nf[0], nfxy = (int64_t)g.nf[0] * g.nf[1];
-        const int64_t fbase = (int64_t)R * cz * nfxy + (int64_t)R * cy * nfx + (int64_t)R * cx;
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            T *__restrict__ out = fs.out[f];
-            T b[3][3][3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) b[k][j][i] = sb[f][k][w + j][lane + i];
+        __syncthreads();
+        const int cx = cx0 + i, cy = cy0 + j;
+        if (cx < g.nb[0] && cy < g.nb[1]) {
+            const int e = j * pitch + i;   // the cell's lower halo corner
             // defect of the parent: B_c - (1/R^3) sum of the trilinear children
             T D = T(0);
             if constexpr (R > 1) {
-                T mz[3];
+                T my[3];
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    T my[3];
-#pragma unroll
-                    for (int j = 0; j < 3; ++j)
-                        my[j] = T(ChildW<R>::mean(0)) * b[k][j][0] + T(ChildW<R>::mean(1)) * b[k][j][1] +
-                                T(ChildW<R>::mean(2)) * b[k][j][2];
-                    mz[k] = T(ChildW<R>::mean(0)) * my[0] + T(ChildW<R>::mean(1)) * my[1] +
-                            T(ChildW<R>::mean(2)) * my[2];
-                }
-                T mean = T(ChildW<R>::mean(0)) * mz[0] + T(ChildW<R>::mean(1)) * mz[1] +
-                         T(ChildW<R>::mean(2)) * mz[2];
-                D = b[1][1][1] - mean;
+                for (int k = 0; k < 3; ++k)
+                    my[k] = T(ChildW<R>::mean(0)) * szm[e + k] + T(ChildW<R>::mean(1)) * szm[e + pitch + k] +
+                            T(ChildW<R>::mean(2)) * szm[e + 2 * pitch + k];
+                D = sbc[e + pitch + 1] - (T(ChildW<R>::mean(0)) * my[0] + T(ChildW<R>::mean(1)) * my[1] +
+                                          T(ChildW<R>::mean(2)) * my[2]);
             }
-            // separable trilinear: x, then y, then z
-            T X[3][3][R];
+            T b[3][3];
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
+            for (int r = 0; r < 3; ++r)
 #pragma unroll
-                for (int j = 0; j < 3; ++j)
-#pragma unroll
-                    for (int lx = 0; lx < R; ++lx) X[k][j][lx] = wsum3<T, R>(lx, b[k][j][0], b[k][j][1], b[k][j][2]);
-            // one child row y at a time (its y-interpolated values only are
-            // live), all its planes z
+                for (int k = 0; k < 3; ++k) b[r][k] = szi[e + r * pitch + k];
+            T *__restrict__ o = out + (int64_t)fz * nfxy + (int64_t)R * cy * nfx + (int64_t)R * cx;
             double s = 0.0;
 #pragma unroll
             for (int ly = 0; ly < R; ++ly) {
-                T Y[3][R];
+                T Y[3], q[R];
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
+                for (int k = 0; k < 3; ++k) Y[k] = wsum3<T, R>(ly, b[0][k], b[1][k], b[2][k]);
 #pragma unroll
-                    for (int lx = 0; lx < R; ++lx) Y[k][lx] = wsum3<T, R>(ly, X[k][0][lx], X[k][1][lx], X[k][2][lx]);
-#pragma unroll
-                for (int lz = 0; lz < R; ++lz) {
-                    T o[R];
-#pragma unroll
-                    for (int lx = 0; lx < R; ++lx) {
-                        o[lx] = wsum3<T, R>(lz, Y[0][lx], Y[1][lx], Y[2][lx]) + D;
-                        s += (double)o[lx];
-                    }
-                    store_row<T, R>(out + fbase + lz * nfxy + ly * nfx, o);
-                    // keeps the scheduler from computing every row before the
-                    // first store (all r^3 values live at once)
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int lx = 0; lx < R; ++lx) {
+                    q[lx] = wsum3<T, R>(lx, Y[0], Y[1], Y[2]) + D;
+                    s += (double)q[lx];
                 }
+                store_row<T, R>(o + ly * nfx, q);
             }
-            sums[f] = counted ? s : 0.0;
+            const int64_t c = cz * nxy + cy * nx + cx;   // owned cells enter the fine-grid sums
+            if (c >= a.own_c0 && c < a.own_c1) sum += s;
         }
+        if (it + gridDim.x < items) __syncthreads();   // the stage is used again (uniform over the workgroup)
     }
-#pragma unroll
-    for (int k = 0; k < NF; ++k) {
-        const double t = block_sum(sums[k], red);
-        if (threadIdx.x == 0) a.part[fs.slot[k] * a.part_stride + blockIdx.x] = t;
-    }
+    const double t = block_sum(sum, red);
+    if (threadIdx.x == 0) a.part[fs.slot[f] * a.part_stride + blockIdx.x] = t;
 }
 
 // ---------------------------------------------------------------------------
@@ -909,8 +918,6 @@ static void launch_grid_stages(const StepArgs<T> &a, hipStream_t st, int phases)
     const int64_t cb = (a.g.ncell + kBlock - 1) / kBlock;
     const int64_t pb = (a.n + kBlock - 1) / kBlock;
     const int64_t nc = a.g.ncell, nf = a.g.nfine;
-    const ProlongSet<T> eps{{a.phi, nullptr, nullptr, nullptr}, {a.fine_eps, nullptr, nullptr, nullptr},
-                            {SL_EPSF, 0, 0, 0}, 1, 1};
     if (phases & kPhaseVelocity) {
     if (a.vel_source == 0) {
         // the pressure (for the gradient only), then u, v, w with the lookup
@@ -961,23 +968,22 @@ static void launch_grid_stages(const StepArgs<T> &a, hipStream_t st, int phases)
     }
     }
     if (phases & kPhaseProlong) {
-    const int64_t ptiles = prolong_tiles(a.g.nb);
-    a.mk->mark("prolong_eps", st);
-    hipLaunchKernelGGL((k_prolong<T, R, 1>), dim3(ptiles), dim3(kBlock), 0, st, a, eps);
-    const ProlongSet<T> src{{a.F, a.F + nc, a.F + 2 * nc, nullptr},
-                            {a.fine_F, a.fine_F + nf, a.fine_F + 2 * nf, nullptr},
-                            {SL_FF, SL_FF + 1, SL_FF + 2, 0},
-                            0, 3};
-    a.mk->mark("prolong", st);
-    hipLaunchKernelGGL((k_prolong<T, R, 3>), dim3(ptiles), dim3(kBlock), 0, st, a, src);
+    ProlongSet<T> fs;
+    int m = 0;
+    auto add = [&](const T *B, T *out, int slot) {
+        fs.B[m] = B;
+        fs.out[m] = out;
+        fs.slot[m++] = slot;
+    };
+    add(a.phi, a.fine_eps, SL_EPSF);
+    for (int k = 0; k < 3; ++k) add(a.F + k * nc, a.fine_F + k * nf, SL_FF + k);
     if (a.semi) {
-        const ProlongSet<T> semi{{a.K, a.KU, a.KU + nc, a.KU + 2 * nc},
-                                 {a.fine_K, a.fine_KU, a.fine_KU + nf, a.fine_KU + 2 * nf},
-                                 {SL_KF, SL_KUF, SL_KUF + 1, SL_KUF + 2},
-                                 0, 4};
-        a.mk->mark("prolong_semi", st);
-        hipLaunchKernelGGL((k_prolong<T, R, 4>), dim3(ptiles), dim3(kBlock), 0, st, a, semi);
+        add(a.K, a.fine_K, SL_KF);
+        for (int k = 0; k < 3; ++k) add(a.KU + k * nc, a.fine_KU + k * nf, SL_KUF + k);
     }
+    a.mk->mark("prolong", st);
+    hipLaunchKernelGGL((k_prolong<T, R>), dim3((unsigned)prolong_blocks(a.g.nb, R, a.part_stride), (unsigned)m),
+                       dim3(kBlock), 0, st, a, fs, prolong_shift(a.g.nb[0]), prolong_items(a.g.nb, R));
     }
 }
 
@@ -1015,7 +1021,7 @@ template <typename T> hipError_t launch_stages(const StepArgs<T> &a, hipStream_t
     spec.nblk[SL_MLPERR] = nmlp;
     spec.nblk[SL_MLPREF] = nmlp;
     spec.nblk[SL_MLPSAMP] = nmlp;
-    const int ptiles = (int)prolong_tiles(a.g.nb);   // k_prolong
+    const int ptiles = (int)prolong_blocks(a.g.nb, a.ratio, a.part_stride);   // k_prolong
     spec.nblk[SL_EPSF] = ptiles;
     for (int k = 0; k < 3; ++k) spec.nblk[SL_FF + k] = ptiles;
     for (int k = 0; k < 4; ++k) {
