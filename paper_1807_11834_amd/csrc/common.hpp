@@ -188,18 +188,18 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // Workgroup -> logical tile.  Workgroups are dealt round-robin over the 8 XCDs
-// (each with its own L2).  XCD x takes chunks of kXcdChunk consecutive tiles,
+// (each with its own L2).  XCD x takes chunks of `chunk` consecutive tiles,
 // and the chunks of the 8 XCDs interleave over the domain: neighbouring tiles
 // share an L2, while a dense region (the packed bed) is spread over all XCDs.
 // The final partial round of chunks keeps the identity mapping (a bijection).
 constexpr int64_t kXcdChunk = 16;
-__device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t nblk) {
-    const int64_t nx = 8, round = nx * kXcdChunk;
+__device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t nblk, int64_t chunk = kXcdChunk) {
+    const int64_t nx = 8, round = nx * chunk;
     const int64_t full = (nblk / round) * round;
     if (b >= full) return b;
     const int64_t x = b % nx, k = b / nx;          // k-th workgroup dealt to XCD x
-    const int64_t q = k / kXcdChunk, r = k % kXcdChunk;
-    return (q * nx + x) * kXcdChunk + r;
+    const int64_t q = k / chunk, r = k % chunk;
+    return (q * nx + x) * chunk + r;
 }
 
 // ---- wave / block reductions (fixed tree order -> deterministic) -----------

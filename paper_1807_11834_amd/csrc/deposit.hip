@@ -26,9 +26,8 @@ static_assert(kChunk % kWave == 0, "a chunk is staged in whole waves");
 enum DepMode { kPhi = 0, kForce = 1, kSemi = 2 };
 template <int MODE> struct DepNc { static constexpr int value = MODE == kPhi ? 1 : (MODE == kForce ? 3 : 4); };
 
-template <typename T> __device__ __forceinline__ T vol_over_vb(T d, T inv_vb) {
-    return (T(kPi / 6.0) * d * d * d) * inv_vb;
-}
+template <typename T> __device__ __forceinline__ T sphere_volume(T d) { return T(kPi / 6.0) * d * d * d; }
+template <typename T> __device__ __forceinline__ T vol_over_vb(T d, T inv_vb) { return sphere_volume(d) * inv_vb; }
 
 // Bulk pressure gradient of cell c written to G ([3][ncell]), in the arithmetic
 // of gradient_at(): the cell's and its six neighbours' (hi, lo) pressure are
@@ -109,6 +108,17 @@ __device__ __forceinline__ void load_values(int64_t id, const vec4<T> &q, const 
 // and adds particle by particle waits for two dependent loads per particle: 512
 // cells of 20 particles in FP64 took 3 + 12 us (sorted copy, solid fraction)
 // and 19 us (source), on two compute units.
+// A cell's sum of v, or for the solid fraction of v / V_b: the product rounded
+// before it is widened, otherwise one FMA with the running sum.
+template <typename T, int SM, int MODE> struct NgpSum {
+    static constexpr bool kFma = MODE == kPhi && SM != kSumWide;
+    typename std::conditional<kFma, FmaSum<T, SM>, CellSum<T, SM>>::type acc;
+    __device__ __forceinline__ void add(T v, T inv_vb) {
+        if constexpr (kFma) acc.add(v, inv_vb);
+        else acc.add(MODE == kPhi ? v * inv_vb : v);
+    }
+    __device__ __forceinline__ T value() const { return acc.value(); }
+};
 constexpr int kNgpCells = kWave, kNgpItems = 4, kNgpChunk = kBlock * kNgpItems;
 
 template <typename T, int SM, int MODE>
@@ -141,7 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restric
             decode_cell(c, g.nb, cx, cy, cz);
             gl = load_gradient(c, cx, cy, cz, g, P, Plo);
         }
-        CellSum<T, SM> acc;
+        NgpSum<T, SM, MODE> acc;
         for (int64_t cs = rs; cs < re; cs += kNgpChunk) {   // uniform over the workgroup
             const int m = (int)(re - cs < kNgpChunk ? re - cs : kNgpChunk);
             int64_t id[kNgpItems];
@@ -156,20 +166,23 @@ __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restric
 #pragma unroll
             for (int u = 0; u < kNgpItems; ++u) {
                 if constexpr (MODE == kPhi) q[u] = pk[id[u]];
-                load_values<T, MODE>(id[u], q[u], drag, pk, g.inv_vb, v[u]);
+                else load_values<T, MODE>(id[u], q[u], drag, pk, g.inv_vb, v[u]);
             }
 #pragma unroll
             for (int u = 0; u < kNgpItems; ++u) {
                 const int k = (int)threadIdx.x + u * kBlock;
                 if (k >= m) continue;
-                if constexpr (MODE == kPhi) sp[cs + k] = q[u];
+                if constexpr (MODE == kPhi) {
+                    sp[cs + k] = q[u];
+                    v[u][0] = sphere_volume(q[u].w);
+                }
 #pragma unroll
                 for (int j = 0; j < NC; ++j) val[j][k] = v[u][j];
             }
             __syncthreads();
             if (mine) {
                 const int32_t b0 = (int32_t)((s > cs ? s : cs) - cs), b1 = (int32_t)((e < cs + m ? e : cs + m) - cs);
-                for (int32_t k = b0; k < b1; ++k) acc.add(val[comp][k]);
+                for (int32_t k = b0; k < b1; ++k) acc.add(val[comp][k], g.inv_vb);
             }
             __syncthreads();
         }

@@ -22,8 +22,8 @@
 //                  with the semi-implicit split also (beta, beta u_p).
 //   deposit force  (deposit.hip), with the bulk pressure gradient; then the
 //                  semi-implicit K, KU when requested.
-//   k_prolong      one fine plane of a tile of 256 bulk cells per work item, one
-//                  launch for eps, F_fpi (and K, KU): conservative trilinear
+//   k_prolong      a tile of 256 bulk cells per work item, one launch for eps,
+//                  F_fpi (and K, KU): conservative trilinear
 //                  T_f + D_c from the tile staged in LDS.
 //   k_diag         fixed-order reduction of the per-workgroup FP64 partials.
 #include <type_traits>
@@ -705,8 +705,8 @@ template <typename T, int R>
 __device__ __forceinline__ T wsum3(int l, T a0, T a1, T a2) {
     // sum_k w(l,k) a_k, skipping structurally zero weights
     T s = T(ChildW<R>::w(l, 1)) * a1;
-    if (ChildW<R>::w(l, 0) != 0.0) s += T(ChildW<R>::w(l, 0)) * a0;
-    if (ChildW<R>::w(l, 2) != 0.0) s += T(ChildW<R>::w(l, 2)) * a2;
+    if (ChildW<R>::w(l, 0) != 0.0) s = dfma(T(ChildW<R>::w(l, 0)), a0, s);
+    if (ChildW<R>::w(l, 2) != 0.0) s = dfma(T(ChildW<R>::w(l, 2)), a2, s);
     return s;
 }
 
@@ -722,18 +722,19 @@ template <typename T> struct ProlongSet {
 
 // The fine-grid writes bound this kernel, and the rate of writing depends on
 // which addresses are written together: bare 16-byte stores over 512 x 512 x
-// 1024 fine cells run at 6.7 TB/s in address order, at 5.5 TB/s when a workgroup
-// writes all r planes of a tile of 64 x 4 bulk cells and at 6.5 TB/s when it
-// writes one fine plane of a tile of 128 x 2.  So a work item is one fine plane
-// of a tile of 256 bulk cells (one layer, 2^xs wide), items in the order of the
-// planes, and one launch takes every field (blockIdx.y).
+// 1024 fine cells run at 6.7 TB/s in address order; a workgroup that writes the
+// r planes of a tile of 64 x 4 bulk cells, sixteen tiles to an XCD at a time,
+// reaches 5.5 TB/s, with the planes one after the other, tiles of 128 x 2 and
+// whole layers to an XCD 6.1 TB/s.  (One plane per workgroup reaches 6.5 TB/s
+// but interpolates along x and y once per plane: its arithmetic then bounds it.)
 //
-// A work item stages the tile and its one-cell halo (indices clamped at the
-// walls) in LDS, combined over the three layers on the way: the trilinear value
-// at the item's plane and the children's mean along z.  Each thread then
-// interpolates along y and x and writes its cell's r rows of the plane, with the
-// defect D from the means (see above).  Workgroups loop over the items, as many
-// workgroups as there are diagnostic partials for.
+// A work item is a tile of 256 bulk cells of one layer, 2^xs wide, or where
+// that leaves few workgroups one fine plane of such a tile; one launch takes
+// every field (blockIdx.y).  The tile's 3 x 3 x 3 neighbourhoods (the tile with a
+// one-cell halo, indices clamped at the walls) are staged in LDS in one memory
+// round trip, and each thread writes its cell's children plane by plane.
+// Workgroups loop over the items, as many workgroups as there are diagnostic
+// partials for.
 constexpr int kPMaxX = 7, kPMinX = 4;   // tiles of 128 x 2 ... 16 x 16 cells
 constexpr int kPStage = ((1 << kPMaxX) + 2) * ((kBlock >> kPMaxX) + 2);   // staged values of the widest tile
 static_assert(((1 << kPMinX) + 2) * ((kBlock >> kPMinX) + 2) <= kPStage, "the widest tile has the most halo");
@@ -748,9 +749,15 @@ static int prolong_shift(int nx) {
         if (padded(xs) == padded(kPMinX)) return xs;
     return kPMinX;
 }
-int64_t prolong_items(const int nb[3], int ratio) {
+static int64_t prolong_layer(const int nb[3]) {   // tiles of a layer
     const int xs = prolong_shift(nb[0]), ys = 8 - xs;
-    return (((int64_t)nb[0] + (1 << xs) - 1) >> xs) * (((int64_t)nb[1] + (1 << ys) - 1) >> ys) * nb[2] * ratio;
+    return (((int64_t)nb[0] + (1 << xs) - 1) >> xs) * (((int64_t)nb[1] + (1 << ys) - 1) >> ys);
+}
+// Fine planes per item: all r of them (x and y interpolated once), or one where
+// whole tiles would leave the four or more fields fewer than 1024 workgroups.
+static int prolong_planes(const int nb[3], int ratio) { return prolong_layer(nb) * nb[2] * 4 < 1024 ? 1 : ratio; }
+int64_t prolong_items(const int nb[3], int ratio) {
+    return prolong_layer(nb) * nb[2] * (ratio / prolong_planes(nb, ratio));
 }
 static_assert(kBlock == 256, "a tile has 2^8 cells");
 
@@ -763,8 +770,8 @@ static int64_t prolong_blocks(const int nb[3], int ratio, int64_t part_stride) {
 }
 
 template <typename T, int R>
-__global__ __launch_bounds__(kBlock) void k_prolong(StepArgs<T> a, ProlongSet<T> fs, int xs, int64_t items) {
-    __shared__ T szi[kPStage], szm[kPStage], sbc[kPStage];   // plane value, mean along z, centre layer
+__global__ __launch_bounds__(kBlock) void k_prolong(StepArgs<T> a, ProlongSet<T> fs, int xs, int planes, int64_t items) {
+    __shared__ T sb[3][kPStage];
     __shared__ double red[kWavesPerBlock];
     const Geo<T> &g = a.g;
     const int f = blockIdx.y, ys = 8 - xs;
@@ -772,84 +779,95 @@ __global__ __launch_bounds__(kBlock) void k_prolong(StepArgs<T> a, ProlongSet<T>
     const T *__restrict__ B = fs.B[f];
     T *__restrict__ out = fs.out[f];
     const int tnx = (g.nb[0] + W - 1) >> xs, tny = (g.nb[1] + H - 1) >> ys;
+    const int64_t layer = (int64_t)tnx * tny;
     const int64_t nx = g.nb[0], nxy = (int64_t)g.nb[0] * g.nb[1];
     const int64_t nfx = g.nf[0], nfxy = (int64_t)g.nf[0] * g.nf[1];
     const int i = (int)threadIdx.x & (W - 1), j = (int)threadIdx.x >> xs;
     double sum = 0.0;
     for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-        const int64_t item = xcd_tile(it, items);
+        const int64_t item = xcd_tile(it, items, layer < kXcdChunk ? kXcdChunk : layer);
         const int cx0 = (int)(item % tnx) << xs, cy0 = (int)((item / tnx) % tny) << ys;
-        const int fz = (int)(item / ((int64_t)tnx * tny)), cz = fz / R, lz = fz % R;
+        const int pz = (int)(item / layer) * planes, cz = pz / R, lz0 = pz % R;   // first fine plane
         // staging: the H + 2 rows of the tile in two rounds of H, and the two
         // halo columns, every load issued before the first LDS write
-        const int64_t zl = (cz > 0 ? cz - 1 : 0) * nxy, zc = cz * nxy, zh = (cz + 1 < g.nb[2] ? cz + 1 : cz) * nxy;
-        const int hr = (int)threadIdx.x >> 1;   // halo column: row hr, left or right
-        int si[3], sj[3];
-        bool on[3] = {true, j + H < H + 2, (int)threadIdx.x < 2 * (H + 2)};
-        si[0] = si[1] = i + 1;
-        sj[0] = j;
-        sj[1] = j + H;
-        si[2] = (threadIdx.x & 1) ? W + 1 : 0;
-        sj[2] = hr;
+        const int64_t zo[3] = {(cz > 0 ? cz - 1 : 0) * nxy, cz * nxy, (cz + 1 < g.nb[2] ? cz + 1 : cz) * nxy};
+        const int si[3] = {i + 1, i + 1, (threadIdx.x & 1) ? W + 1 : 0};
+        const int sj[3] = {j, j + H, (int)threadIdx.x >> 1};
+        const bool on[3] = {true, j < 2, (int)threadIdx.x < 2 * (H + 2)};
         T v[3][3];
 #pragma unroll
         for (int u = 0; u < 3; ++u) {
             const int64_t o = clampi(cy0 - 1 + sj[u], g.nb[1]) * nx + clampi(cx0 - 1 + si[u], g.nb[0]);
-            if (on[u]) {
-                v[u][0] = B[zl + o];
-                v[u][1] = B[zc + o];
-                v[u][2] = B[zh + o];
-            }
-        }
-        // weights of the plane on the layers below, at and above (wsum3 with the
-        // plane known at run time)
-        const T oz = (T(lz) + T(0.5)) / T(R) - T(0.5);
-        const T w0 = oz < T(0) ? -oz : T(0), w1 = T(1) - (oz < T(0) ? -oz : oz), w2 = oz > T(0) ? oz : T(0);
+            if (on[u])
 #pragma unroll
-        for (int u = 0; u < 3; ++u) {
-            if (!on[u]) continue;
-            if (f == 0)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) v[u][k] = T(1) - v[u][k];
-            const int e = sj[u] * pitch + si[u];
-            szi[e] = w1 * v[u][1] + (w0 * v[u][0] + w2 * v[u][2]);
-            szm[e] = T(ChildW<R>::mean(0)) * v[u][0] + T(ChildW<R>::mean(1)) * v[u][1] +
-                     T(ChildW<R>::mean(2)) * v[u][2];
-            sbc[e] = v[u][1];
+                for (int k = 0; k < 3; ++k) v[u][k] = B[zo[k] + o];
         }
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+            if (on[u])
+#pragma unroll
+                for (int k = 0; k < 3; ++k) sb[k][sj[u] * pitch + si[u]] = f == 0 ? T(1) - v[u][k] : v[u][k];
         __syncthreads();
         const int cx = cx0 + i, cy = cy0 + j;
         if (cx < g.nb[0] && cy < g.nb[1]) {
-            const int e = j * pitch + i;   // the cell's lower halo corner
+            T b[3][3][3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) b[k][r][c] = sb[k][(j + r) * pitch + i + c];
             // defect of the parent: B_c - (1/R^3) sum of the trilinear children
             T D = T(0);
             if constexpr (R > 1) {
-                T my[3];
+                T mz[3];
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
-                    my[k] = T(ChildW<R>::mean(0)) * szm[e + k] + T(ChildW<R>::mean(1)) * szm[e + pitch + k] +
-                            T(ChildW<R>::mean(2)) * szm[e + 2 * pitch + k];
-                D = sbc[e + pitch + 1] - (T(ChildW<R>::mean(0)) * my[0] + T(ChildW<R>::mean(1)) * my[1] +
-                                          T(ChildW<R>::mean(2)) * my[2]);
+                for (int k = 0; k < 3; ++k) {
+                    T my[3];
+#pragma unroll
+                    for (int r = 0; r < 3; ++r)
+                        my[r] = T(ChildW<R>::mean(0)) * b[k][r][0] + T(ChildW<R>::mean(1)) * b[k][r][1] +
+                                T(ChildW<R>::mean(2)) * b[k][r][2];
+                    mz[k] = T(ChildW<R>::mean(0)) * my[0] + T(ChildW<R>::mean(1)) * my[1] +
+                            T(ChildW<R>::mean(2)) * my[2];
+                }
+                T mean = T(ChildW<R>::mean(0)) * mz[0] + T(ChildW<R>::mean(1)) * mz[1] +
+                         T(ChildW<R>::mean(2)) * mz[2];
+                D = b[1][1][1] - mean;
             }
-            T b[3][3];
+            // separable trilinear: x, then y (every child row), then z plane by
+            // plane, each plane's rows stored together
+            T Y[R][3][R];
 #pragma unroll
-            for (int r = 0; r < 3; ++r)
+            for (int k = 0; k < 3; ++k) {
+                T X[3][R];
 #pragma unroll
-                for (int k = 0; k < 3; ++k) b[r][k] = szi[e + r * pitch + k];
-            T *__restrict__ o = out + (int64_t)fz * nfxy + (int64_t)R * cy * nfx + (int64_t)R * cx;
+                for (int r = 0; r < 3; ++r)
+#pragma unroll
+                    for (int lx = 0; lx < R; ++lx) X[r][lx] = wsum3<T, R>(lx, b[k][r][0], b[k][r][1], b[k][r][2]);
+#pragma unroll
+                for (int ly = 0; ly < R; ++ly)
+#pragma unroll
+                    for (int lx = 0; lx < R; ++lx) Y[ly][k][lx] = wsum3<T, R>(ly, X[0][lx], X[1][lx], X[2][lx]);
+            }
+            T *__restrict__ o = out + (int64_t)R * cz * nfxy + (int64_t)R * cy * nfx + (int64_t)R * cx;
             double s = 0.0;
 #pragma unroll
-            for (int ly = 0; ly < R; ++ly) {
-                T Y[3], q[R];
+            for (int lz = 0; lz < R; ++lz) {
+                if (lz < lz0 || lz >= lz0 + planes) continue;   // uniform over the workgroup
 #pragma unroll
-                for (int k = 0; k < 3; ++k) Y[k] = wsum3<T, R>(ly, b[0][k], b[1][k], b[2][k]);
+                for (int ly = 0; ly < R; ++ly) {
+                    T q[R];
 #pragma unroll
-                for (int lx = 0; lx < R; ++lx) {
-                    q[lx] = wsum3<T, R>(lx, Y[0], Y[1], Y[2]) + D;
-                    s += (double)q[lx];
+                    for (int lx = 0; lx < R; ++lx) {
+                        q[lx] = wsum3<T, R>(lz, Y[ly][0][lx], Y[ly][1][lx], Y[ly][2][lx]) + D;
+                        s += (double)q[lx];
+                    }
+                    store_row<T, R>(o + lz * nfxy + ly * nfx, q);
+                    // keeps the scheduler from computing every row before the
+                    // first store (all r^3 values live at once)
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                store_row<T, R>(o + ly * nfx, q);
             }
             const int64_t c = cz * nxy + cy * nx + cx;   // owned cells enter the fine-grid sums
             if (c >= a.own_c0 && c < a.own_c1) sum += s;
@@ -983,7 +1001,8 @@ static void launch_grid_stages(const StepArgs<T> &a, hipStream_t st, int phases)
     }
     a.mk->mark("prolong", st);
     hipLaunchKernelGGL((k_prolong<T, R>), dim3((unsigned)prolong_blocks(a.g.nb, R, a.part_stride), (unsigned)m),
-                       dim3(kBlock), 0, st, a, fs, prolong_shift(a.g.nb[0]), prolong_items(a.g.nb, R));
+                       dim3(kBlock), 0, st, a, fs, prolong_shift(a.g.nb[0]), prolong_planes(a.g.nb, R),
+                       prolong_items(a.g.nb, R));
     }
 }
 
