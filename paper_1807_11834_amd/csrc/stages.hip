@@ -26,6 +26,7 @@
 //                  F_fpi (and K, KU): conservative trilinear
 //                  T_f + D_c from the tile staged in LDS.
 //   k_diag         fixed-order reduction of the per-workgroup FP64 partials.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -375,9 +376,11 @@ template <typename T> struct BrickGrid {
     }
 };
 
-// Fill the brick at (ox, oy, oz) into L and write its U; thread t in [0, 256).
+// Fill the brick at (ox, oy, oz) into L and (if write_u) write its U; thread t in
+// [0, 256).
 template <typename T, int R, int SM>
-__device__ __forceinline__ void brick_fill(const StepArgs<T> &a, BrickLds<T, R> &L, int t, int ox, int oy, int oz) {
+__device__ __forceinline__ void brick_fill(const StepArgs<T> &a, BrickLds<T, R> &L, int t, int ox, int oy, int oz,
+                                           bool write_u) {
     constexpr int HX = kBrickX + 2, HY = kBrickY + 2;
     const Geo<T> &g = a.g;
     const int lane = t % kWave;
@@ -448,14 +451,16 @@ __device__ __forceinline__ void brick_fill(const StepArgs<T> &a, BrickLds<T, R> 
             const auto ck = ChildSum<T, SM>::kComp ? __shfl(plane.acc.c, l0 + k, kWave) : plane.acc.c;
             acc.add_plane(sk, ck);
         }
-        if (inside && rz == 0) a.U[f * g.ncell + (cx + nx * cy + nxy * cz)] = acc.hi(inv);
+        if (write_u && inside && rz == 0) a.U[f * g.ncell + (cx + nx * cy + nxy * cz)] = acc.hi(inv);
     }
 }
 
-// The particles of the filled brick at (ox, oy, oz): thread t of nt.
+// The particles of the filled brick at (ox, oy, oz): thread t of nt, batches
+// first, first + step, ... of kBrickBatch particles per thread.
+constexpr int kBrickBatch = 2;
 template <typename T, int R>
-__device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const BrickLds<T, R> &L, int t, int nt, int ox,
-                                                int oy, int oz) {
+__device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const BrickLds<T, R> &L, int t, int nt, int first,
+                                                int step, int ox, int oy, int oz) {
     constexpr int FX = kBrickX * R, FY = kBrickY * R, FZ = kBrickZ * R;
     const Geo<T> &g = a.g;
     int32_t pre[kBrickRows + 1];   // particles before each row
@@ -465,8 +470,8 @@ __device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const Bric
     const int total = pre[kBrickRows];
     const int fx0 = ox * R, fy0 = oy * R, fz0 = oz * R;
     // up to kPB particles per thread at a time: their loads are issued together
-    constexpr int kPB = 2;
-    for (int j0 = t; j0 < total; j0 += kPB * nt) {
+    constexpr int kPB = kBrickBatch;
+    for (int j0 = t + first * kPB * nt; j0 < total; j0 += step * kPB * nt) {
         vec4<T> qs[kPB];
         int64_t ps[kPB];
 #pragma unroll
@@ -549,6 +554,10 @@ __device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const Bric
     }
 }
 
+// One workgroup per brick, or where there are few bricks of many particles
+// (gridDim.y = 1 otherwise) several that fill the same brick and share its
+// particles: a batch of 512 is a chain of dependent loads (10,000 particles in 8
+// bricks, FP64: 19 us for three batches by one workgroup each).
 template <typename T, int R, int SM>
 __global__ __launch_bounds__(kBrickThreads) void k_restrict_brick(StepArgs<T> a, BrickGrid<T> bg) {
     static_assert(R <= 4, "one thread per fine child plane");
@@ -556,9 +565,9 @@ __global__ __launch_bounds__(kBrickThreads) void k_restrict_brick(StepArgs<T> a,
     __shared__ BrickLds<T, R> L;
     int ox, oy, oz;
     bg.origin(xcd_tile(blockIdx.x, gridDim.x), ox, oy, oz);
-    brick_fill<T, R, SM>(a, L, threadIdx.x, ox, oy, oz);
+    brick_fill<T, R, SM>(a, L, threadIdx.x, ox, oy, oz, blockIdx.y == 0);
     __syncthreads();
-    brick_particles<T, R>(a, L, threadIdx.x, kBrickThreads, ox, oy, oz);
+    brick_particles<T, R>(a, L, threadIdx.x, kBrickThreads, blockIdx.y, gridDim.y, ox, oy, oz);
 }
 
 template <typename T, int R> int64_t brick_blocks(const Geo<T> &g) {
@@ -944,7 +953,12 @@ static void launch_grid_stages(const StepArgs<T> &a, hipStream_t st, int phases)
         a.mk->mark("restrict_lookup", st);
         const int64_t nbk = brick_blocks<T, R>(a.g);
         const BrickGrid<T> bg{(a.g.nb[0] + kBrickX - 1) / kBrickX, (a.g.nb[1] + kBrickY - 1) / kBrickY};
-        hipLaunchKernelGGL((k_restrict_brick<T, R, SM>), dim3((unsigned)nbk), dim3(kBrickThreads), 0, st, a, bg);
+        // bricks alone that fill the chip (two per compute unit) take one workgroup each; fewer share the
+        // mean number of particles in batches
+        const int64_t batch = nbk * kBrickBatch * kBrickThreads;
+        const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(512 / nbk, (a.n + batch - 1) / batch));
+        hipLaunchKernelGGL((k_restrict_brick<T, R, SM>), dim3((unsigned)nbk, (unsigned)parts), dim3(kBrickThreads), 0,
+                           st, a, bg);
     } else if (a.vel_source == 3) {
         if constexpr (std::is_same<T, float>::value) {
             a.mk->mark("restrict", st);
