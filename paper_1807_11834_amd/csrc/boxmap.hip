@@ -18,30 +18,74 @@
 
 namespace cpl {
 
-// One thread per receiver row: sum_j w_j src[col_j] for up to NF fields at a
-// time, under the map's sum mode (SumMode).
+// One thread per receiver row: sum_j w_j src[col_j] for NF fields at a time, under the map's sum mode (SumMode).  The entries of a workgroup's rows
+// are one run of the CSR arrays; it passes through LDS in windows, read with
+// 16-byte loads.  A thread then takes kBatch entries of its row together: their
+// values of every field are loaded at once and added in order.  Bound by the
+// address rate of the gathers (one per entry and field).
+constexpr int kBatch = 8;
+constexpr int kWindow = 2048;   // entries in LDS: the 8 per row that a 2 x 2 x 2 overlap has
+
+// Entries [c0, c0 + kWindow) of p into s, 16 bytes per load; c0 a multiple of 4,
+// entries from nnz on left alone.
+template <typename X>
+__device__ __forceinline__ void stage_window(const X *__restrict__ p, int64_t c0, int64_t nnz, X *s) {
+    constexpr int V = 16 / sizeof(X);
+    typedef X Vec __attribute__((ext_vector_type(V)));
+#pragma unroll
+    for (int it = 0; it < kWindow / V / kBlock; ++it) {
+        const int k = V * (it * kBlock + (int)threadIdx.x);
+        if (c0 + k + V <= nnz) *reinterpret_cast<Vec *>(s + k) = *reinterpret_cast<const Vec *>(p + c0 + k);
+        else
+            for (int q = 0; q < V; ++q)
+                if (c0 + k + q < nnz) s[k + q] = p[c0 + k + q];
+    }
+}
+
+// Fields NF blockIdx.y .. NF blockIdx.y + NF - 1.
 template <typename T, int SM, int NF>
 __global__ __launch_bounds__(kBlock) void k_boxmap(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
-                                                   const T *__restrict__ w, int64_t nr, int64_t ns,
-                                                   const T *__restrict__ src, T *__restrict__ dst, int nfields) {
+                                                   const T *__restrict__ w, int64_t nr, int64_t ns, int64_t nnz,
+                                                   const T *__restrict__ src, T *__restrict__ dst) {
     using S = typename FmaSum<T, SM>::W;
-    const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int64_t r = tile * kBlock + threadIdx.x;
-    if (r >= nr) return;
-    const int64_t b = rowptr[r], e = rowptr[r + 1];
-    for (int f0 = 0; f0 < nfields; f0 += NF) {
-        FmaSum<T, SM> acc[NF];
-        for (int64_t j = b; j < e; ++j) {
-            const int64_t c = col[j];
-            const S wj = S(w[j]);
+    __shared__ __align__(16) int32_t scol[kWindow];
+    __shared__ __align__(16) T sw[kWindow];
+    src += (int64_t)NF * blockIdx.y * ns;
+    dst += (int64_t)NF * blockIdx.y * nr;
+    const int64_t r0 = xcd_tile(blockIdx.x, gridDim.x) * kBlock, r = r0 + threadIdx.x;
+    const int64_t r1 = r0 + kBlock < nr ? r0 + kBlock : nr;
+    const bool mine = r < nr;
+    const int64_t b = mine ? rowptr[r] : 0, e = mine ? rowptr[r + 1] : 0;
+    const int64_t w0 = rowptr[r0] & ~(int64_t)3, w1 = rowptr[r1];
+    FmaSum<T, SM> acc[NF];
+    for (int64_t c0 = w0; c0 < w1; c0 += kWindow) {   // uniform over the workgroup
+        if (c0 != w0) __syncthreads();                // the previous window has been read
+        stage_window(col, c0, nnz, scol);
+        stage_window(w, c0, nnz, sw);
+        __syncthreads();
+        const int j0 = (int)((b > c0 ? b : c0) - c0);
+        const int j1 = (int)((e < c0 + kWindow ? e : c0 + kWindow) - c0);
+        for (int j = j0; j < j1; j += kBatch) {
+            T v[kBatch][NF];
 #pragma unroll
-            for (int k = 0; k < NF; ++k)
-                if (f0 + k < nfields) acc[k].add(wj, S(src[(int64_t)(f0 + k) * ns + c]));
+            for (int u = 0; u < kBatch; ++u) {
+                const int64_t c = scol[j + u < j1 ? j + u : j];
+#pragma unroll
+                for (int k = 0; k < NF; ++k) v[u][k] = src[k * ns + c];
+            }
+            __builtin_amdgcn_sched_barrier(0);   // every load of the batch before the first sum
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u)
+                if (j + u < j1) {
+                    const S wj = S(sw[j + u]);
+#pragma unroll
+                    for (int k = 0; k < NF; ++k) acc[k].add(wj, S(v[u][k]));
+                }
         }
-#pragma unroll
-        for (int k = 0; k < NF; ++k)
-            if (f0 + k < nfields) dst[(int64_t)(f0 + k) * nr + r] = acc[k].value();
     }
+    if (mine)
+#pragma unroll
+        for (int k = 0; k < NF; ++k) dst[k * nr + r] = acc[k].value();
 }
 
 }  // namespace cpl
@@ -260,11 +304,20 @@ extern "C" int couple_boxmap_init(int64_t ns, const double *sender_boxes, int64_
     return COUPLE_OK;
 }
 
+// Groups of four fields, and the rest (a group reads the map once).
 template <typename T, int SM>
 static void launch_boxmap(const couple_boxmap *m, const void *src, void *dst, int nf, hipStream_t st) {
-    const int64_t blocks = (m->nr + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL((k_boxmap<T, SM, 4>), dim3((unsigned)blocks), dim3(kBlock), 0, st, m->rowptr, m->col,
-                       (const T *)m->w, m->nr, m->ns, (const T *)src, (T *)dst, nf);
+    const unsigned blocks = (unsigned)((m->nr + kBlock - 1) / kBlock);
+    auto group = [&](auto nc, int first, int groups) {
+        hipLaunchKernelGGL((k_boxmap<T, SM, decltype(nc)::value>), dim3(blocks, (unsigned)groups), dim3(kBlock), 0, st,
+                           m->rowptr, m->col, (const T *)m->w, m->nr, m->ns, m->nnz, (const T *)src + first * m->ns,
+                           (T *)dst + first * m->nr);
+    };
+    const int rest = nf % 4;
+    if (nf >= 4) group(std::integral_constant<int, 4>{}, 0, nf / 4);
+    if (rest == 1) group(std::integral_constant<int, 1>{}, nf - rest, 1);
+    else if (rest == 2) group(std::integral_constant<int, 2>{}, nf - rest, 1);
+    else if (rest == 3) group(std::integral_constant<int, 3>{}, nf - rest, 1);
 }
 
 extern "C" int couple_boxmap_apply(couple_boxmap *m, const void *src, void *dst, int32_t nfields, void *stream) {
