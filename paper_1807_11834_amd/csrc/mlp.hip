@@ -24,8 +24,8 @@
 // The training pass chains forward and backward the same way, a 16-row tile
 // per pair of waves, and writes transposed copies of the layer inputs and
 // output gradients for the weight-gradient products, whose contraction runs
-// over the batch.  Batch inference on given features runs layer by layer over HBM in
-// the natural slot order (rows k = 32q + 8g + i).  Every reduction has a fixed
+// over the batch.  Batch inference on given features chains the layers in
+// registers too, in the natural slot order (rows k = 32q + 8g + i).  Every reduction has a fixed
 // order.
 #include <type_traits>
 
@@ -140,65 +140,165 @@ __global__ __launch_bounds__(kBlock) void k_adam(const float *__restrict__ grads
 // ---------------------------------------------------------------------------
 // Batch inference on given features
 // ---------------------------------------------------------------------------
-// X0[b][k] = bf16((feat[b][k] - mean[k]) / std[k]) for k < 193, 0 up to 224.
-// A workgroup takes 64 rows: their features are read row by row (consecutive
-// threads, consecutive features) and standardised into an LDS tile, from which
-// the rows leave as 16-byte stores.
-constexpr int kStdRows = 64;
-constexpr int kStdPitch = kK1 + 2;   // BF16 elements per LDS row
-__global__ __launch_bounds__(kBlock) void k_standardise(const float *__restrict__ feat, int64_t B,
-                                                        const float *__restrict__ mean_inv, uint16_t *__restrict__ x0) {
-    __shared__ uint16_t tile[kStdRows * kStdPitch];
-    const int64_t b0 = (int64_t)blockIdx.x * kStdRows;
-    const int nr = (int)(B - b0 < kStdRows ? B - b0 : kStdRows);
-    for (int e = threadIdx.x; e < nr * kK1; e += kBlock) {
-        const int r = e / kK1, k = e % kK1;
-        float v = 0.f;
-        if (k < kFeat) v = (feat[(b0 + r) * kFeat + k] - mean_inv[k]) * mean_inv[kK1 + k];
-        tile[r * kStdPitch + k] = (uint16_t)bf16_bits(v);
+// The four layers in one pass over the features, which is all the memory traffic
+// (layer by layer through memory, 50,001 rows took 108 us of kernels).  A
+// workgroup of eight waves keeps the weights in LDS as product fragments (124
+// KB) and loops over groups of 256 rows; a wave takes two 16-row tiles, whose
+// activations stay in registers.  Slots are in the natural order (k = 32q + 8g +
+// i), so a layer's result (lane group g: rows 4g .. 4g + 3 of a 16-row block)
+// moves to the lane group that holds it in the next operand by two lane-swap
+// instructions per word: see next_operand().
+constexpr int kFwdWaves = 8, kFwdTiles = 2, kFwdRows = 16 * kFwdTiles * kFwdWaves;
+constexpr int kFwdFrag1 = 8 * 7, kFwdFragH = 8 * 4, kFwdFrags = kFwdFrag1 + 2 * kFwdFragH + 4;
+
+struct ForwardLds {
+    uint4 frag[kFwdFrags][kWave];   // [neuron block][contraction block] of layers 1, 2, 3, then 4
+    float bias[3 * kHid + 16];      // b1, b2, b3, b4 (padded)
+    float mean[kK1], inv[kK1];
+};
+
+// Eight consecutive floats at any 4-byte address.
+typedef float float4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Contraction block q of the next layer's operand from blocks 2q (a) and 2q + 1
+// (b) of a result, two packed words each: lane group g takes rows 8g .. 8g + 7
+// of the 32, rows 4g' .. 4g' + 3 of a 16-row block being in lane group g'.
+// Swapping the upper 32 lanes of a with the lower 32 of b, then the odd 16-lane
+// rows of the first with the even ones of the second, leaves the lower and the
+// upper half of that run.
+__device__ __forceinline__ uint4 next_operand(const uint32_t (&a)[2], const uint32_t (&b)[2]) {
+    uint32_t lo[2], hi[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const auto h = __builtin_amdgcn_permlane32_swap(a[s], b[s], false, false);
+        const auto r = __builtin_amdgcn_permlane16_swap(h[0], h[1], false, false);
+        lo[s] = r[0];
+        hi[s] = r[1];
     }
-    __syncthreads();
-    for (int e = threadIdx.x; e < nr * (kK1 / 8); e += kBlock) {
-        const int r = e / (kK1 / 8), k0 = 8 * (e % (kK1 / 8));
-        const uint16_t *t = tile + r * kStdPitch + k0;
-        const uint4 pk = make_uint4(t[0] | ((uint32_t)t[1] << 16), t[2] | ((uint32_t)t[3] << 16),
-                                    t[4] | ((uint32_t)t[5] << 16), t[6] | ((uint32_t)t[7] << 16));
-        *reinterpret_cast<uint4 *>(x0 + (b0 + r) * kK1 + k0) = pk;
-    }
+    return make_uint4(lo[0], lo[1], hi[0], hi[1]);
 }
 
-// One dense layer of the batch forward pass for 16-row tiles, one wave per tile:
-//   Z = X W + b (X [B][32 KB] BF16, W^T [16 MB][32 KB] BF16), then
-//   hidden: gelu(Z) -> H (BF16 [B][16 MB]); output (MB = 1): Z -> Y [B][16].
-template <int KB, int MB, bool OUT>
-__global__ __launch_bounds__(kBlock) void k_dense(const uint16_t *__restrict__ X, const uint16_t *__restrict__ WT,
-                                                  const float *__restrict__ bias, int M, int64_t B,
-                                                  float *__restrict__ Y, uint16_t *__restrict__ H) {
-    constexpr int KP = 32 * KB, MP = 16 * MB;
-    const int lane = lane_id(), n = lane & 15, g = lane >> 4;
-    const int64_t ntile = (B + 15) / 16;
-    const int64_t tile = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (tile >= ntile) return;   // whole wave
-    const int64_t b = tile * 16 + n;
-    const bool valid = b < B;
-    bf16x8 xb[KB];
+// A hidden layer: in[t][kb] -> gelu(W in + b) -> out[t][4], natural slot order.
+template <int KB>
+__device__ __forceinline__ void forward_layer(const ForwardLds &L, int frag0, const float *bias,
+                                              const uint4 (&in)[kFwdTiles][KB], uint4 (&out)[kFwdTiles][4], int lane,
+                                              int g) {
+    f32x4 acc[8][kFwdTiles];
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) xb[kb] = valid ? load8(X + b * KP + 32 * kb + 8 * g) : zero8();
+    for (int mb = 0; mb < 8; ++mb)
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < kFwdTiles; ++t) acc[mb][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) acc = mma(load8(WT + (int64_t)(16 * mb + n) * KP + 32 * kb + 8 * g), xb[kb], acc);
-        const int m0 = 16 * mb + 4 * g;
-        float z[4];
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) z[j] = acc[j] + ((m0 + j < M) ? bias[m0 + j] : 0.f);
-        if (!valid) continue;
-        if constexpr (OUT) {
-            *reinterpret_cast<float4 *>(Y + b * MP + m0) = make_float4(z[0], z[1], z[2], z[3]);
-        } else {
-            *reinterpret_cast<uint2 *>(H + b * MP + m0) =
-                make_uint2(pack2(gelu(z[0]), gelu(z[1])), pack2(gelu(z[2]), gelu(z[3])));
+        for (int mb = 0; mb < 8; ++mb) {
+            const bf16x8 w = as_bf16x8(L.frag[frag0 + mb * KB + kb][lane]);
+#pragma unroll
+            for (int t = 0; t < kFwdTiles; ++t) acc[mb][t] = mma(w, as_bf16x8(in[t][kb]), acc[mb][t]);
+        }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int t = 0; t < kFwdTiles; ++t) {
+            uint32_t h[2][2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const int mb = 2 * q + s;
+                const float *bj = bias + 16 * mb + 4 * g;
+                float z[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) z[j] = acc[mb][t][j] + bj[j];
+                h[s][0] = pack2(gelu(z[0]), gelu(z[1]));
+                h[s][1] = pack2(gelu(z[2]), gelu(z[3]));
+            }
+            out[t][q] = next_operand(h[0], h[1]);
+        }
+}
+
+struct ForwardNet {
+    const uint16_t *wt[4];
+    const float *params, *mean_inv;
+};
+
+__global__ __launch_bounds__(kFwdWaves * kWave) void k_forward(const float *__restrict__ feat, int64_t B, ForwardNet net,
+                                                               float *__restrict__ y) {
+    __shared__ ForwardLds L;
+    constexpr int NT = kFwdTiles, kThreads = kFwdWaves * kWave;
+    const int lane = lane_id(), n = lane & 15, g = lane >> 4, wave = threadIdx.x >> 6;
+    for (int e = threadIdx.x; e < kFwdFrags * kWave; e += kThreads) {
+        const int f = e >> 6, r = e & 15, gg = (e >> 4) & 3;
+        const int l = f < kFwdFrag1 ? 0 : (f < kFwdFrag1 + kFwdFragH ? 1 : (f < kFwdFrag1 + 2 * kFwdFragH ? 2 : 3));
+        const int ff = f - (l == 0 ? 0 : kFwdFrag1 + (l - 1) * kFwdFragH), kbs = l == 0 ? 7 : 4;
+        const int mb = ff / kbs, kb = ff % kbs;
+        L.frag[f][e & 63] =
+            *reinterpret_cast<const uint4 *>(net.wt[l] + (16 * mb + r) * (32 * kbs) + 32 * kb + 8 * gg);
+    }
+    for (int e = threadIdx.x; e < 3 * kHid + 16; e += kThreads) {
+        const int l = e / kHid, m = e % kHid;
+        constexpr int64_t kB0 = off_b(0), kB1 = off_b(1), kB2 = off_b(2), kB3 = off_b(3);
+        L.bias[e] = l < 3 ? net.params[(l == 0 ? kB0 : (l == 1 ? kB1 : kB2)) + m] : (m < kOut ? net.params[kB3 + m] : 0.f);
+    }
+    for (int e = threadIdx.x; e < kK1; e += kThreads) {
+        L.mean[e] = net.mean_inv[e];
+        L.inv[e] = net.mean_inv[kK1 + e];
+    }
+    __syncthreads();
+    for (int64_t b0 = (int64_t)blockIdx.x * kFwdRows + wave * 16 * NT; b0 < B; b0 += (int64_t)gridDim.x * kFwdRows) {
+        // keeps the LDS reads below inside the loop (held in registers across
+        // it, they would spill)
+        wave_sync();
+        // the rows' features (a row past the end: the last row, not stored), then
+        // standardised into the layer-1 operand
+        float v[NT][7][8];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int64_t b = b0 + 16 * t + n;
+            const float *fr = feat + (b < B ? b : B - 1) * kFeat;
+#pragma unroll
+            for (int kb = 0; kb < 6; ++kb)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float4_u q = *reinterpret_cast<const float4_u *>(fr + 32 * kb + 8 * g + 4 * h);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[t][kb][4 * h + i] = q[i];
+                }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[t][6][i] = 0.f;
+            if (g == 0) v[t][6][0] = fr[192];   // the one feature of the last block
+        }
+        static_assert(kFeat == 193, "six whole contraction blocks and one feature");
+        __builtin_amdgcn_sched_barrier(0);
+        uint4 x[NT][7], h1[NT][4], h2[NT][4];
+#pragma unroll
+        for (int kb = 0; kb < 7; ++kb) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                float s[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int k = 32 * kb + 8 * g + i;
+                    s[i] = kb < 6 || k < kFeat ? (v[t][kb][i] - L.mean[k]) * L.inv[k] : 0.f;
+                }
+                x[t][kb] = make_uint4(pack2(s[0], s[1]), pack2(s[2], s[3]), pack2(s[4], s[5]), pack2(s[6], s[7]));
+            }
+            __builtin_amdgcn_sched_barrier(0);   // a block at a time: the raw values go as the operand comes
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        forward_layer<7>(L, 0, L.bias, x, h1, lane, g);
+        __builtin_amdgcn_sched_barrier(0);
+        forward_layer<4>(L, kFwdFrag1, L.bias + kHid, h1, h2, lane, g);
+        __builtin_amdgcn_sched_barrier(0);
+        forward_layer<4>(L, kFwdFrag1 + kFwdFragH, L.bias + 2 * kHid, h2, h1, lane, g);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+                acc = mma(as_bf16x8(L.frag[kFwdFrag1 + 2 * kFwdFragH + kb][lane]), as_bf16x8(h1[t][kb]), acc);
+            const int64_t b = b0 + 16 * t + n;
+            if (g == 0 && b < B)
+#pragma unroll
+                for (int j = 0; j < kOut; ++j) y[3 * b + j] = acc[j] + L.bias[3 * kHid + j];
         }
     }
 }
@@ -756,11 +856,6 @@ __global__ __launch_bounds__(kBlock) void k_sum_loss(const double *__restrict__ 
     if (threadIdx.x == 0) out[0] = (float)v;
 }
 
-__global__ __launch_bounds__(kBlock) void k_output(const float *__restrict__ y16, int64_t B, float *__restrict__ y) {
-    const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e < B * 3) y[e] = y16[(e / 3) * 16 + e % 3];
-}
-
 // Column statistics: pass 0 sums x, pass 1 sums (x - mean)^2, per chunk of rows.
 __global__ __launch_bounds__(kBlock) void k_colsum(const float *__restrict__ x, int64_t n, int cols, int64_t rows_per,
                                                    const double *__restrict__ mean, double *__restrict__ part) {
@@ -1245,21 +1340,23 @@ int64_t bricks_of(const int nb[3]) {
 }
 int64_t mlp_check_blocks(int64_t n_bricks) { return (n_bricks + kWavesPerBlock - 1) / kWavesPerBlock; }
 
+// Workgroups of a persistent kernel: one per compute unit, or fewer.
+static unsigned persistent_grid(int64_t items) {
+    int dev = 0, ncu = 256;
+    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (ncu < 1) ncu = 1;
+    return (unsigned)(items < ncu ? (items > 0 ? items : 1) : ncu);
+}
+
 void launch_mlp_pack(const StepArgs<float> &a, hipStream_t st) {
     hipLaunchKernelGGL(mlp::k_pack, dim3((unsigned)((a.g.ncell + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, a);
 }
 
 void launch_mlp_infer(const StepArgs<float> &a, hipStream_t st) {
     if (a.n <= 0) return;
-    int dev = 0, ncu = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (ncu < 1) ncu = 1;
-    // one workgroup per compute unit, or fewer for small inputs
     const int64_t rounds = (a.n + mlp::kInfRows - 1) / mlp::kInfRows;
-    int64_t grid = ncu;
-    if (grid * mlp::kInfWaves > rounds) grid = (rounds + mlp::kInfWaves - 1) / mlp::kInfWaves;
-    if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(mlp::k_infer, dim3((unsigned)grid), dim3(mlp::kInfWaves * kWave), 0, st, a);
+    hipLaunchKernelGGL(mlp::k_infer, dim3(persistent_grid((rounds + mlp::kInfWaves - 1) / mlp::kInfWaves)),
+                       dim3(mlp::kInfWaves * kWave), 0, st, a);
 }
 
 void launch_mlp_check(const StepArgs<float> &a, hipStream_t st) {
@@ -1293,23 +1390,14 @@ hipError_t launch_adam(const NetBufs &net, const float *grads, float lr, float b
     return hipGetLastError();
 }
 
-hipError_t launch_standardise(const float *feat, int64_t B, const float *mean_inv, uint16_t *x0, hipStream_t st) {
+hipError_t launch_forward(const NetBufs &net, const float *feat, int64_t B, float *y, hipStream_t st) {
     if (B <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_standardise, dim3((unsigned)((B + kStdRows - 1) / kStdRows)), dim3(kBlock), 0, st, feat, B,
-                       mean_inv, x0);
-    return hipGetLastError();
-}
-
-static unsigned tile_blocks(int64_t B) { return (unsigned)(((B + 15) / 16 + kWavesPerBlock - 1) / kWavesPerBlock); }
-
-hipError_t launch_forward(const NetBufs &net, const TrainBufs &tb, int64_t B, hipStream_t st) {
-    if (B <= 0) return hipSuccess;
-    const dim3 gr(tile_blocks(B)), bl(kBlock);
-    const float *p = net.params;
-    hipLaunchKernelGGL((k_dense<7, 8, false>), gr, bl, 0, st, tb.x0, net.wt[0], p + off_b(0), kHid, B, nullptr, tb.h[0]);
-    hipLaunchKernelGGL((k_dense<4, 8, false>), gr, bl, 0, st, tb.h[0], net.wt[1], p + off_b(1), kHid, B, nullptr, tb.h[1]);
-    hipLaunchKernelGGL((k_dense<4, 8, false>), gr, bl, 0, st, tb.h[1], net.wt[2], p + off_b(2), kHid, B, nullptr, tb.h[2]);
-    hipLaunchKernelGGL((k_dense<4, 1, true>), gr, bl, 0, st, tb.h[2], net.wt[3], p + off_b(3), kOut, B, tb.y, nullptr);
+    ForwardNet fn;
+    for (int l = 0; l < 4; ++l) fn.wt[l] = net.wt[l];
+    fn.params = net.params;
+    fn.mean_inv = net.mean_inv;
+    hipLaunchKernelGGL(k_forward, dim3(persistent_grid((B + kFwdRows - 1) / kFwdRows)), dim3(kFwdWaves * kWave), 0, st,
+                       feat, B, fn, y);
     return hipGetLastError();
 }
 
@@ -1353,12 +1441,6 @@ hipError_t launch_gradients(const NetBufs &net, const TrainBufs &tb, const float
     hipLaunchKernelGGL(k_reduce_b, dim3((unsigned)((kRedBias + kRedBEntries - 1) / kRedBEntries)), dim3(kRedBThreads), 0,
                        st, parts, (int64_t)nt, grads);
     if (loss) hipLaunchKernelGGL(k_sum_loss, dim3(1), bl, 0, st, tb.loss_part, B / 16, loss);
-    return hipGetLastError();
-}
-
-hipError_t launch_output(const TrainBufs &tb, int64_t B, float *y, hipStream_t st) {
-    if (B <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_output, dim3(blocks(B * 3)), dim3(kBlock), 0, st, tb.y, B, y);
     return hipGetLastError();
 }
 

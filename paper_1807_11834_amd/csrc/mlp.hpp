@@ -41,12 +41,9 @@ __host__ __device__ constexpr int perm_col(int c) {
 }
 constexpr int kK1 = 224;     // padded layer-1 fan-in (and the length of mean/1/std)
 
-// Training and batch-inference buffers, sized for max_batch rows.
+// Training buffers, sized for max_batch rows.
 struct TrainBufs {
     int64_t max_batch = 0;
-    uint16_t *x0 = nullptr;                        // standardised input [B][224] (batch inference)
-    uint16_t *h[3] = {};                           // hidden activations [B][128] (batch inference)
-    float *y = nullptr;                            // output [B][16] (batch inference)
     uint16_t *tr = nullptr;                        // training: BF16 transposed rows, blocked (below)
     float *part_w[4] = {};                         // per-chunk weight gradients [nchunk][MP][KP]
     double *part_b[4] = {};                        // per-workgroup bias gradients [ngroup][MP]
@@ -78,9 +75,8 @@ struct NetBufs {
 
 // Kernel launchers (mlp.hip).  All enqueue on `st` and return the launch status.
 hipError_t launch_cast(const NetBufs &net, hipStream_t st);
-// Batch inference: standardise B rows of feat into x0, then the four layers into y.
-hipError_t launch_standardise(const float *feat, int64_t B, const float *mean_inv, uint16_t *x0, hipStream_t st);
-hipError_t launch_forward(const NetBufs &net, const TrainBufs &tb, int64_t B, hipStream_t st);
+// Batch inference: the network's output y [B][3] of the raw features feat [B][193].
+hipError_t launch_forward(const NetBufs &net, const float *feat, int64_t B, float *y, hipStream_t st);
 // Gradient of the mean loss over a batch of B rows (a multiple of 32): rows
 // idx[b] (or b) of feat [nrows][193] and resid [nrows][3]; grads [kNParam] and
 // (if loss) the loss.
@@ -91,7 +87,6 @@ hipError_t launch_gradients(const NetBufs &net, const TrainBufs &tb, const float
 // double (0.999f alone would leave 1 - b2 off by 1e-5 relative).
 hipError_t launch_adam(const NetBufs &net, const float *grads, float lr, float b1, float omb1, float b2, float omb2,
                        float eps, float c1, float c2, hipStream_t st);
-hipError_t launch_output(const TrainBufs &tb, int64_t B, float *y, hipStream_t st);
 // Per-column mean and population standard deviation (two passes, FP64, fixed
 // order) of a row-major [n][cols] matrix, cols <= 256; part holds nchunk * cols.
 hipError_t launch_column_stats(const float *x, int64_t n, int cols, double *part, int64_t nchunk, double *mean,

@@ -35,8 +35,8 @@ template <typename X> static bool alloc0(X **p, size_t bytes) {
 }
 
 static void mlp_release(couple_mlp *m) {
-    std::vector<void *> ptrs = {m->net.params, m->net.m, m->net.v, m->net.mean_inv, m->tb.x0, m->tb.tr,
-                                m->tb.y, m->tb.loss_part, m->tb.grads, m->stats};
+    std::vector<void *> ptrs = {m->net.params, m->net.m, m->net.v, m->net.mean_inv, m->tb.tr,
+                                m->tb.loss_part, m->tb.grads, m->stats};
     for (int l = 0; l < 4; ++l) {
         ptrs.push_back(m->net.wt[l]);
         ptrs.push_back(m->net.wn[l]);
@@ -44,9 +44,6 @@ static void mlp_release(couple_mlp *m) {
         ptrs.push_back(m->net.wnp[l]);
         ptrs.push_back(m->tb.part_w[l]);
         ptrs.push_back(m->tb.part_b[l]);
-    }
-    for (int l = 0; l < 3; ++l) {
-        ptrs.push_back(m->tb.h[l]);
     }
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -100,11 +97,8 @@ extern "C" int couple_mlp_init(const couple_mlp_config *cfg, couple_mlp **out) {
              alloc0(&tb.part_w[l], sizeof(float) * nc * mpad(l) * kpad(l)) &&
              alloc0(&tb.part_b[l], sizeof(double) * ng * mpad(l));
     }
-    for (int l = 0; l < 3 && ok; ++l)
-        ok = alloc0(&tb.h[l], sizeof(uint16_t) * B * kHid);
     m->stats_chunks = 256;
-    ok = ok && alloc0(&tb.x0, sizeof(uint16_t) * B * kK1) && alloc0(&tb.tr, sizeof(uint16_t) * B * kTrRows) &&
-         alloc0(&tb.y, sizeof(float) * B * 16) &&
+    ok = ok && alloc0(&tb.tr, sizeof(uint16_t) * B * kTrRows) &&
          alloc0(&tb.loss_part, sizeof(double) * ((B + 15) / 16)) && alloc0(&tb.grads, sizeof(float) * kNParam) &&
          alloc0(&m->stats, sizeof(double) * (m->stats_chunks * 256 + 4 * 256));
     if (!ok) {
@@ -281,8 +275,11 @@ extern "C" int couple_mlp_forward(couple_mlp *m, const float *feat, int64_t n, f
     if (n == 0) return COUPLE_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     (void)hipGetLastError();
-    if (launch_standardise(feat, n, m->net.mean_inv, m->tb.x0, st) != hipSuccess ||
-        launch_forward(m->net, m->tb, n, st) != hipSuccess || launch_output(m->tb, n, y, st) != hipSuccess)
+    // an output that overlaps the features is formed in the training rows' buffer first
+    const bool overlap = y < feat + n * kFeat && feat < y + n * kOut;
+    float *out = overlap ? reinterpret_cast<float *>(m->tb.tr) : y;
+    if (launch_forward(m->net, feat, n, out, st) != hipSuccess ||
+        (overlap && hipMemcpyAsync(y, out, sizeof(float) * kOut * n, hipMemcpyDeviceToDevice, st) != hipSuccess))
         return mfail(m, COUPLE_EHIP, "couple_mlp_forward: launch failed");
     return COUPLE_OK;
 }
