@@ -117,7 +117,7 @@ static ScratchPlan scratch_plan(const couple_config &c, int64_t nmax, bool tight
     // one FP64 partial per workgroup and slot: the stride covers the largest
     // grid of any kernel that writes partials (the prolongation and the NGP
     // deposition take no more workgroups than that)
-    const int64_t mblk = mlp_check_blocks(bricks_of(c.nb));
+    const int64_t mblk = c.vel_source == COUPLE_VEL_MLP ? mlp_check_blocks(bricks_of(c.nb)) : 1;
     const int64_t prblk = tight ? 1 : std::min<int64_t>(prolong_items(c.nb, c.ratio), 1024);
     p.part_stride = 1;
     for (int64_t b : {pblk, cblk, ntile, mblk, prblk})
@@ -270,7 +270,7 @@ static int step_impl(couple_handle *h, const couple_inputs *in, couple_outputs *
     a.uf_out = (T *)out->uf;
     a.net = MlpNet{};
     if (h->mlp) {
-        for (int l = 0; l < 4; ++l) a.net.wt[l] = h->mlp->net.wt[l];
+        for (int l = 0; l < 4; ++l) a.net.wtp[l] = h->mlp->net.wtp[l];
         a.net.params = h->mlp->net.params;
         a.net.mean_inv = h->mlp->net.mean_inv;
         for (int k = 0; k < 3; ++k) a.net.scale[k] = (float)h->mlp->scale[k];

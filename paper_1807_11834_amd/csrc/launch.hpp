@@ -56,7 +56,7 @@ hipError_t launch_bin_sort(const T *pos, const T *diam, int64_t n, const Geo<T> 
 
 // Device state of the learned surrogate as the step kernels read it.
 struct MlpNet {
-    const uint16_t *wt[4];   // BF16 W^T of each layer, [padded fan-out][padded fan-in]
+    const uint16_t *wtp[4];  // BF16 W^T of each layer in slot order, [padded fan-out][padded fan-in]
     const float *params;     // FP32 master parameters (biases are read from here)
     const float *mean_inv;   // [2][224] feature mean, then 1/std (0 in the padding)
     float scale[3];          // per-component scale of the residual

@@ -101,9 +101,9 @@ struct WPtrs {
 __device__ __forceinline__ void write_bf16_copies(const WPtrs &w, int l, int k, int m, float p) {
     const uint16_t b = (uint16_t)bf16_bits(p);
     w.wt[l][(int64_t)m * kpad(l) + k] = b;
+    w.wtp[l][(int64_t)m * kpad(l) + (l == 0 ? slot_of_feature(k) : perm_col(k))] = b;
     if (l > 0) {
         w.wn[l][(int64_t)k * cpad(l) + m] = b;
-        w.wtp[l][(int64_t)m * kpad(l) + perm_col(k)] = b;
         w.wnp[l][(int64_t)k * cpad(l) + perm_col(m)] = b;
     }
 }
@@ -965,18 +965,6 @@ struct InferLds {
     float mean[kK1], inv[kK1];    // standardisation per feature (0 in the padding)
 };
 
-// Layer-1 slot (kb, g, i) -> feature index: unit u = 4 kb + g is stencil cell u
-// (its 7 channels in slots 0-6) or, for u = 27, the offsets and diameter.
-__device__ __forceinline__ int slot_feature(int kb, int g, int i) {
-    const int u = 4 * kb + g;
-    if (u < 27) return i < 7 ? 7 * u + i : -1;
-    return i < 4 ? 189 + i : -1;
-}
-// Hidden-layer slot (kb, g, i) -> input neuron (result-layout pairing).
-__device__ __forceinline__ int slot_hidden(int kb, int g, int i) {
-    return 32 * kb + (i < 4 ? 4 * g + i : 16 + 4 * g + (i - 4));
-}
-
 // One layer of the chain for NT tiles: in[t][kb] (KB slot groups) -> 8 row
 // blocks (accumulators start at the bias) -> gelu -> out[t][4] in the paired
 // slot order.  The slot-group loop is outermost so that the 8 NT accumulators
@@ -1130,25 +1118,14 @@ __global__ __launch_bounds__(kInfWaves * kWave) void k_infer(StepArgs<float> a) 
     constexpr int NT = kInfTiles;
     const int lane = lane_id(), n = lane & 15, g = lane >> 4, wave = threadIdx.x >> 6;
     const MlpNet &net = a.net;
-    // weights into LDS in slot order
-    for (int e = threadIdx.x; e < kFrags * kWave * 8; e += kInfWaves * kWave) {
-        const int f = e >> 9, ln = (e >> 3) & 63, i = e & 7;
-        const int r = ln & 15, gg = ln >> 4;
-        uint16_t v = 0;
-        if (f < kFrag1) {
-            const int mb = f / 7, kb = f % 7;
-            const int k = slot_feature(kb, gg, i);
-            if (k >= 0) v = net.wt[0][(16 * mb + r) * kpad(0) + k];
-        } else if (f < kFrag1 + 2 * kFragH) {
-            const int l = (f < kFrag1 + kFragH) ? 1 : 2;
-            const int ff = f - kFrag1 - (l - 1) * kFragH;
-            const int mb = ff / 4, kb = ff % 4;
-            v = net.wt[l][(16 * mb + r) * kpad(l) + slot_hidden(kb, gg, i)];
-        } else {
-            const int kb = f - kFrag1 - 2 * kFragH;
-            v = net.wt[3][r * kpad(3) + slot_hidden(kb, gg, i)];
-        }
-        reinterpret_cast<uint16_t *>(&L.frag[f][ln])[i] = v;
+    // weights into LDS, 16 bytes at a time from the copies in slot order
+    for (int e = threadIdx.x; e < kFrags * kWave; e += kInfWaves * kWave) {
+        const int f = e >> 6, r = e & 15, gg = (e >> 4) & 3;
+        const int l = f < kFrag1 ? 0 : (f < kFrag1 + kFragH ? 1 : (f < kFrag1 + 2 * kFragH ? 2 : 3));
+        const int ff = f - (l == 0 ? 0 : kFrag1 + (l - 1) * kFragH), kbs = l == 0 ? 7 : 4;
+        const int mb = ff / kbs, kb = ff % kbs;
+        L.frag[f][e & 63] =
+            *reinterpret_cast<const uint4 *>(net.wtp[l] + (16 * mb + r) * (32 * kbs) + 32 * kb + 8 * gg);
     }
     for (int e = threadIdx.x; e < 3 * kHid + 16; e += kInfWaves * kWave) {
         const int l = e / kHid, m = e % kHid;
@@ -1225,106 +1202,108 @@ __global__ __launch_bounds__(kInfWaves * kWave) void k_infer(StepArgs<float> a) 
     }
 }
 
-// Bricks of 8x8x8 bulk cells, one wave each.  The checked sample is every
+// Bricks of 8x8x8 bulk cells, one workgroup each.  The checked sample is every
 // particle with id mod period = step mod period; where its relative L2 error
 // against the fine lookup exceeds tol, every particle of the brick takes the
 // fine lookup.  The brick's 64 (z, y) rows are one lane each: their sorted
-// ranges are loaded at once and prefix-summed across the wave, and the brick's
-// particles are then processed 64 at a time in that flattened order.  Per
-// workgroup: fallback count, sampled squared error and reference, sample count
-// (FP64 partials, fixed order).
+// ranges are loaded at once and prefix-summed across the wave (by every wave),
+// and the brick's particles are then processed 256 at a time in that flattened
+// order.  Bound by the chain of dependent loads (id, sampled particle, fine
+// nodes): a dense brick's 3,400 particles took one wave 13 rounds, 118 us for
+// 1024 bricks.  Per workgroup: fallback count, sampled squared error and
+// reference, sample count (FP64 partials, fixed order).
 constexpr int kBrick = 8;
 
 __global__ __launch_bounds__(kBlock) void k_check(StepArgs<float> a) {
     static_assert(kBrick * kBrick == kWave, "one lane per (z, y) row of a brick");
     __shared__ double red[kWavesPerBlock];
-    __shared__ int32_t pre[kWavesPerBlock][kWave + 1];   // particles before each row (exclusive prefix)
-    __shared__ int64_t row0[kWavesPerBlock][kWave];      // first sorted position of each row
+    __shared__ int32_t pre[kWave + 1];   // particles before each row (exclusive prefix)
+    __shared__ int64_t row0[kWave];      // first sorted position of each row
     const int lane = lane_id(), wave = threadIdx.x >> 6;
-    const int64_t brick = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+    const int64_t brick = blockIdx.x;
     const Geo<float> &geo = a.g;
+    const int bx = (geo.nb[0] + kBrick - 1) / kBrick, by = (geo.nb[1] + kBrick - 1) / kBrick;
+    const int ox = (int)(brick % bx) * kBrick, oy = (int)((brick / bx) % by) * kBrick,
+              oz = (int)(brick / ((int64_t)bx * by)) * kBrick;
+    const int wx = (ox + kBrick < geo.nb[0]) ? kBrick : geo.nb[0] - ox;
+    // lane r owns row (dz, dy) = (r / 8, r % 8): its particles are the
+    // contiguous sorted range of cells ox .. ox + wx - 1 of that row
+    const int dz = lane / kBrick, dy = lane % kBrick;
+    int64_t s0 = 0, s1 = 0;
+    if (oz + dz < geo.nb[2] && oy + dy < geo.nb[1]) {
+        const int64_t c0 = ox + (int64_t)geo.nb[0] * ((oy + dy) + (int64_t)geo.nb[1] * (oz + dz));
+        s0 = seg_clamp(a.start[c0], a.n);
+        s1 = seg_clamp(a.start[c0 + wx], a.n);
+    }
+    int32_t incl = (int32_t)(s1 - s0);   // inclusive prefix over the lanes (rows in order)
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int32_t v = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += v;
+    }
+    const int32_t total = __shfl(incl, kWave - 1, kWave);
+    if (wave == 0) {
+        pre[lane + 1] = incl;
+        if (lane == 0) pre[0] = 0;
+        row0[lane] = s0;
+    }
+    __syncthreads();
+    // flattened index j -> row (last r with pre[r] <= j) -> sorted position
+    auto position = [&](int32_t j) {
+        int lo = 0, hi = kWave;   // pre[lo] <= j < pre[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (pre[mid] <= j) lo = mid;
+            else hi = mid;
+        }
+        return row0[lo] + (j - pre[lo]);
+    };
+    const int64_t period = a.mlp_period, phase = ((a.step % period) + period) % period;
     double err = 0.0, ref = 0.0, ns = 0.0, nfall = 0.0;
-    if (brick < a.n_bricks && a.n > 0) {   // uniform over the wave
-        const int bx = (geo.nb[0] + kBrick - 1) / kBrick, by = (geo.nb[1] + kBrick - 1) / kBrick;
-        const int ox = (int)(brick % bx) * kBrick, oy = (int)((brick / bx) % by) * kBrick,
-                  oz = (int)(brick / ((int64_t)bx * by)) * kBrick;
-        const int wx = (ox + kBrick < geo.nb[0]) ? kBrick : geo.nb[0] - ox;
-        // lane r owns row (dz, dy) = (r / 8, r % 8): its particles are the
-        // contiguous sorted range of cells ox .. ox + wx - 1 of that row
-        const int dz = lane / kBrick, dy = lane % kBrick;
-        int64_t s0 = 0, s1 = 0;
-        if (oz + dz < geo.nb[2] && oy + dy < geo.nb[1]) {
-            const int64_t c0 = ox + (int64_t)geo.nb[0] * ((oy + dy) + (int64_t)geo.nb[1] * (oz + dz));
-            s0 = seg_clamp(a.start[c0], a.n);
-            s1 = seg_clamp(a.start[c0 + wx], a.n);
-        }
-        int32_t incl = (int32_t)(s1 - s0);   // inclusive prefix over the lanes (rows in order)
+    // kU particles of a thread per round: their ids are loaded together (one
+    // round trip instead of kU), then taken in the thread's order j
+    constexpr int kU = 4;
+    for (int32_t j0 = threadIdx.x; j0 < total; j0 += kU * kBlock) {
+        int64_t s[kU], p[kU];
 #pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int32_t v = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += v;
+        for (int u = 0; u < kU; ++u) {
+            const int32_t j = j0 + u * kBlock;
+            s[u] = position(j < total ? j : j0);
+            p[u] = a.perm[s[u]];
         }
-        pre[wave][lane + 1] = incl;
-        if (lane == 0) pre[wave][0] = 0;
-        row0[wave][lane] = s0;
-        wave_sync();
-        const int32_t total = pre[wave][kWave];
-        // flattened index j -> row (last r with pre[r] <= j) -> sorted position
-        auto position = [&](int32_t j) {
-            int lo = 0, hi = kWave;   // pre[lo] <= j < pre[hi]
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (pre[wave][mid] <= j) lo = mid;
-                else hi = mid;
-            }
-            return row0[wave][lo] + (j - pre[wave][lo]);
-        };
-        const int64_t period = a.mlp_period, phase = ((a.step % period) + period) % period;
-        // kU particles of a lane per round: their ids are loaded together (one
-        // round trip instead of kU), then taken in the lane's order j
-        constexpr int kU = 4;
-        for (int32_t j0 = lane; j0 < total; j0 += kU * kWave) {
-            int64_t s[kU], p[kU];
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int32_t j = j0 + u * kWave;
-                s[u] = position(j < total ? j : j0);
-                p[u] = a.perm[s[u]];
-            }
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                if (j0 + u * kWave >= total) break;
-                int64_t pu = p[u];
-                if (pu < 0 || pu >= a.n) pu = 0;
-                if (pu % period != phase) continue;
-                float ux, uy, uz;
-                fine_velocity(a.sp[s[u]], a, ux, uy, uz);
-                const float4 m = a.uf4[pu];
-                const double ex = (double)m.x - ux, ey = (double)m.y - uy, ez = (double)m.z - uz;
-                err += ex * ex + ey * ey + ez * ez;
-                ref += (double)ux * ux + (double)uy * uy + (double)uz * uz;
-                ns += 1.0;
-            }
-        }
-        const double terr = wave_sum(err), tref = wave_sum(ref), tns = wave_sum(ns);
-        const double tol = (double)a.mlp_tol;
-        if (tns > 0.0 && terr > tol * tol * tref) {
-            for (int32_t j = lane; j < total; j += kWave) {
-                const int64_t s = position(j);
-                int64_t p = a.perm[s];
-                if (p < 0 || p >= a.n) p = 0;
-                float4 m = a.uf4[p];
-                fine_velocity(a.sp[s], a, m.x, m.y, m.z);
-                a.uf4[p] = m;
-                nfall += 1.0;
-            }
+        for (int u = 0; u < kU; ++u) {
+            if (j0 + u * kBlock >= total) break;
+            int64_t pu = p[u];
+            if (pu < 0 || pu >= a.n) pu = 0;
+            if (pu % period != phase) continue;
+            float ux, uy, uz;
+            fine_velocity(a.sp[s[u]], a, ux, uy, uz);
+            const float4 m = a.uf4[pu];
+            const double ex = (double)m.x - ux, ey = (double)m.y - uy, ez = (double)m.z - uz;
+            err += ex * ex + ey * ey + ez * ez;
+            ref += (double)ux * ux + (double)uy * uy + (double)uz * uz;
+            ns += 1.0;
         }
     }
-    const double vals[4] = {nfall, err, ref, ns};
-    const int slots[4] = {SL_NFALL, SL_MLPERR, SL_MLPREF, SL_MLPSAMP};
-    for (int k = 0; k < 4; ++k) {
-        const double t = block_sum(vals[k], red);
-        if (threadIdx.x == 0) a.part[slots[k] * a.part_stride + blockIdx.x] = t;
+    const double terr = block_sum(err, red), tref = block_sum(ref, red), tns = block_sum(ns, red);
+    const double tol = (double)a.mlp_tol;
+    if (tns > 0.0 && terr > tol * tol * tref) {   // uniform over the workgroup
+        for (int32_t j = threadIdx.x; j < total; j += kBlock) {
+            const int64_t s = position(j);
+            int64_t p = a.perm[s];
+            if (p < 0 || p >= a.n) p = 0;
+            float4 m = a.uf4[p];
+            fine_velocity(a.sp[s], a, m.x, m.y, m.z);
+            a.uf4[p] = m;
+            nfall += 1.0;
+        }
+    }
+    const double tfall = block_sum(nfall, red);
+    if (threadIdx.x == 0) {
+        const double vals[4] = {tfall, terr, tref, tns};
+        const int slots[4] = {SL_NFALL, SL_MLPERR, SL_MLPREF, SL_MLPSAMP};
+        for (int k = 0; k < 4; ++k) a.part[slots[k] * a.part_stride + blockIdx.x] = vals[k];
     }
 }
 
@@ -1338,7 +1317,7 @@ int64_t bricks_of(const int nb[3]) {
     for (int a = 0; a < 3; ++a) b *= (nb[a] + mlp::kBrick - 1) / mlp::kBrick;
     return b;
 }
-int64_t mlp_check_blocks(int64_t n_bricks) { return (n_bricks + kWavesPerBlock - 1) / kWavesPerBlock; }
+int64_t mlp_check_blocks(int64_t n_bricks) { return n_bricks; }
 
 // Workgroups of a persistent kernel: one per compute unit, or fewer.
 static unsigned persistent_grid(int64_t items) {

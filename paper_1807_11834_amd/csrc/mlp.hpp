@@ -8,9 +8,10 @@
 //   wn[l]  W_l   as [KP_l][CP_l]  (fan-out padded to a 32-wide contraction),
 //          layers 2-4 only (the backward product needs no input gradient of layer 1).
 //   wtp[l], wnp[l]  the same as wt[l], wn[l] for layers 2-4 with each row in the
-//          permuted slot order of the training pass (column 32q + 16s + 4g + j
+//          permuted slot order of the chained products (column 32q + 16s + 4g + j
 //          stored at 32q + 8g + 4s + j), so that a product fragment is one
-//          16-byte load.
+//          16-byte load; wtp[0] is wt[0] in the slot order of the in-step
+//          inference (slot_of_feature).
 // Padding entries are zero.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -39,6 +40,10 @@ static_assert(kNParam == 58243, "parameter count");
 __host__ __device__ constexpr int perm_col(int c) {
     return (c & ~31) | (((c >> 2) & 3) << 3) | (((c >> 4) & 1) << 2) | (c & 3);
 }
+// Slot of a raw feature in the layer-1 rows of the in-step inference: stencil
+// cell u's seven values in slots 8u .. 8u + 6, the offsets and the diameter in
+// 216 .. 219.
+__host__ __device__ constexpr int slot_of_feature(int k) { return k < 189 ? 8 * (k / 7) + k % 7 : 216 + (k - 189); }
 constexpr int kK1 = 224;     // padded layer-1 fan-in (and the length of mean/1/std)
 
 // Training buffers, sized for max_batch rows.
@@ -69,7 +74,7 @@ inline int64_t n_train_groups(int64_t B) { return (B + kTrainGroupRows - 1) / kT
 struct NetBufs {
     float *params = nullptr, *m = nullptr, *v = nullptr;   // FP32 master and Adam moments [kNParam]
     uint16_t *wt[4] = {}, *wn[4] = {};
-    uint16_t *wtp[4] = {}, *wnp[4] = {};                    // permuted copies, layers 2-4
+    uint16_t *wtp[4] = {}, *wnp[4] = {};                    // permuted copies (wtp of every layer, wnp of 2-4)
     float *mean_inv = nullptr;                              // [2][224]
 };
 
