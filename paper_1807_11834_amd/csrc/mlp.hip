@@ -775,85 +775,118 @@ struct GradParts {
     const double *b[4];
 };
 
-// Flat gradient vector from the partials.  Weight entries follow the
-// partials' layout (per layer the padded [m][k] slots, k fastest), so that the
-// loads of a wave are contiguous; each is summed by kRedGroups threads over
-// interleaved chunks (c mod kRedGroups, two partial sums each) whose results
-// are combined in a fixed order.  The bias entries are summed over the
-// nchunk_b workgroup partials of the training pass (below).
+// Flat gradient vector and loss from the partials, in one launch: a workgroup for
+// the loss, kRedBBlocks for the bias entries (the longest chains first) and
+// kRedWBlocks for the weight entries (three launches of which two do not fill the
+// chip took 24 us of a 65,536-row step).
+//
+// Weight entries follow the partials' layout (per layer the padded [m][k] slots,
+// k fastest), so that the loads of a wave are contiguous; each is summed by
+// kRedGroups threads over interleaved chunks (c mod kRedGroups, two partial sums
+// each) whose results are combined in a fixed order.
+constexpr int kRedThreads = 1024;
 constexpr int kRedGroups = 8;
-constexpr int kRedEntries = kBlock / kRedGroups;   // entries per workgroup
+constexpr int kRedEntries = kRedThreads / kRedGroups;   // weight entries per workgroup
 constexpr int64_t kRedW1 = (int64_t)mpad(0) * kpad(0), kRedW2 = kRedW1 + (int64_t)mpad(1) * kpad(1),
                   kRedW3 = kRedW2 + (int64_t)mpad(2) * kpad(2), kRedTotal = kRedW3 + (int64_t)mpad(3) * kpad(3);
+// Bias entries are summed over the workgroup partials of the training pass:
+// kRedBEntries consecutive entries per workgroup, kRedBLanes threads per entry
+// over interleaved partials (c mod kRedBLanes; a wave reads 8 partials of 8
+// consecutive entries), then one thread per entry adds the lanes' sums in order.
 constexpr int kRedBias = 3 * kHid + kOut;          // bias entries (real ones)
+constexpr int kRedBEntries = 8, kRedBLanes = kRedThreads / kRedBEntries;
+constexpr int kRedWBlocks = (int)((kRedTotal + kRedEntries - 1) / kRedEntries);
+constexpr int kRedBBlocks = (kRedBias + kRedBEntries - 1) / kRedBEntries;
 
-__global__ __launch_bounds__(kBlock) void k_reduce_w(GradParts parts, int64_t nchunk, float *__restrict__ grads) {
+// Sum of p[c stride] over c = first, first + step, ... < count in two alternating
+// partial sums (even and odd terms), eight loads at a time.
+template <typename P>
+__device__ __forceinline__ double strided_sum(const P *__restrict__ p, int64_t stride, int64_t first, int64_t step,
+                                              int64_t count) {
+    constexpr int kU = 8;
+    double s[2] = {0.0, 0.0};
+    int64_t c = first;
+    for (; c + (kU - 1) * step < count; c += kU * step) {
+        P v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) v[u] = p[(c + u * step) * stride];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) s[u & 1] += (double)v[u];
+    }
+    for (int u = 0; c < count; c += step, u ^= 1) s[u] += (double)p[c * stride];
+    return s[0] + s[1];
+}
+
+__device__ __forceinline__ void reduce_weights(const GradParts &parts, int64_t nchunk, int block, double *red,
+                                               float *__restrict__ grads) {
     constexpr int64_t kOffW[4] = {off_w(0), off_w(1), off_w(2), off_w(3)};
-    __shared__ double red[kRedGroups][kRedEntries];
     const int le = threadIdx.x % kRedEntries, grp = threadIdx.x / kRedEntries;
-    const int64_t e = (int64_t)blockIdx.x * kRedEntries + le;
+    const int64_t e = (int64_t)block * kRedEntries + le;
     const int l = e < kRedW1 ? 0 : (e < kRedW2 ? 1 : (e < kRedW3 ? 2 : 3));
     const int64_t r = e - (l == 0 ? 0 : (l == 1 ? kRedW1 : (l == 2 ? kRedW2 : kRedW3)));
     const int MP = l == 3 ? mpad(3) : kHid, KP = l == 0 ? kpad(0) : kHid;
     const int m = (int)(r / KP), k = (int)(r % KP);
-    double s0 = 0.0, s1 = 0.0;
-    if (e < kRedTotal) {
-        const float *w = parts.w[l] + r;
-        const int64_t stride = (int64_t)MP * KP;
-        int64_t c = grp;
-        for (; c + kRedGroups < nchunk; c += 2 * kRedGroups) {
-            s0 += (double)w[c * stride];
-            s1 += (double)w[(c + kRedGroups) * stride];
-        }
-        if (c < nchunk) s0 += (double)w[c * stride];
-    }
-    red[grp][le] = s0 + s1;
+    red[grp * kRedEntries + le] =
+        e < kRedTotal ? strided_sum(parts.w[l] + r, (int64_t)MP * KP, grp, kRedGroups, nchunk) : 0.0;
     __syncthreads();
     if (grp == 0 && e < kRedTotal) {
         double t = 0.0;
 #pragma unroll
-        for (int q = 0; q < kRedGroups; ++q) t += red[q][le];
+        for (int q = 0; q < kRedGroups; ++q) t += red[q * kRedEntries + le];
         const int fi = l == 0 ? kFeat : kHid, fo = l == 3 ? kOut : kHid;
         if (k < fi && m < fo) grads[kOffW[l] + (int64_t)k * fo + m] = (float)t;
     }
 }
 
-// kRedBEntries consecutive bias entries per workgroup, kRedBLanes threads per
-// entry over interleaved partials (c mod kRedBLanes; a wave reads 8 partials
-// of 8 consecutive entries), then one thread per entry adds the lanes' sums
-// in lane order.
-constexpr int kRedBEntries = 8, kRedBLanes = 128, kRedBThreads = kRedBEntries * kRedBLanes;
-__global__ __launch_bounds__(kRedBThreads) void k_reduce_b(GradParts parts, int64_t nchunk_b, float *__restrict__ grads) {
+__device__ __forceinline__ void reduce_biases(const GradParts &parts, int64_t nchunk_b, int block, double *red,
+                                              float *__restrict__ grads) {
     constexpr int64_t kOffB[4] = {off_b(0), off_b(1), off_b(2), off_b(3)};
-    __shared__ double red[kRedBLanes][kRedBEntries];
     const int le = threadIdx.x % kRedBEntries, cl = threadIdx.x / kRedBEntries;
-    const int e = (int)blockIdx.x * kRedBEntries + le;
+    const int e = block * kRedBEntries + le;
     const int l = e < 3 * kHid ? e / kHid : 3, m = e - l * kHid, MP = mpad(l);
-    double s0 = 0.0, s1 = 0.0;
-    if (e < kRedBias) {
-        const double *p = parts.b[l] + m;
-        int64_t c = cl;
-        for (; c + kRedBLanes < nchunk_b; c += 2 * kRedBLanes) {
-            s0 += p[c * MP];
-            s1 += p[(c + kRedBLanes) * MP];
-        }
-        if (c < nchunk_b) s0 += p[c * MP];
-    }
-    red[cl][le] = s0 + s1;
+    red[cl * kRedBEntries + le] = e < kRedBias ? strided_sum(parts.b[l] + m, MP, cl, kRedBLanes, nchunk_b) : 0.0;
     __syncthreads();
     if (cl == 0 && e < kRedBias) {
         double t = 0.0;
-        for (int q = 0; q < kRedBLanes; ++q) t += red[q][le];
+        for (int q = 0; q < kRedBLanes; ++q) t += red[q * kRedBEntries + le];
         grads[kOffB[l] + m] = (float)t;
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_sum_loss(const double *__restrict__ part, int64_t n, float *__restrict__ out) {
-    __shared__ double red[kWavesPerBlock];
+__device__ __forceinline__ void reduce_loss(const double *__restrict__ part, int64_t n, double *red,
+                                            float *__restrict__ out) {
     double v = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += kBlock) v += part[i];
-    v = block_sum(v, red);
-    if (threadIdx.x == 0) out[0] = (float)v;
+    if (threadIdx.x < kBlock) {   // whole waves
+        constexpr int kU = 16;   // loads at a time
+        int64_t i = threadIdx.x;
+        for (; i + (kU - 1) * kBlock < n; i += kU * kBlock) {
+            double p[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) p[u] = part[i + u * kBlock];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) v += p[u];
+        }
+        for (; i < n; i += kBlock) v += part[i];
+        v = wave_sum(v);
+        if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int q = 0; q < kWavesPerBlock; ++q) t += red[q];
+        out[0] = (float)t;
+    }
+}
+
+__global__ __launch_bounds__(kRedThreads) void k_reduce(GradParts parts, int64_t nchunk, int64_t nchunk_b,
+                                                        float *__restrict__ grads,
+                                                        const double *__restrict__ loss_part, int64_t nloss,
+                                                        float *__restrict__ loss) {
+    __shared__ double red[kRedThreads];
+    const int b = blockIdx.x - (loss ? 1 : 0);
+    if (b < 0) reduce_loss(loss_part, nloss, red, loss);
+    else if (b < kRedBBlocks) reduce_biases(parts, nchunk_b, b, red, grads);
+    else reduce_weights(parts, nchunk, b - kRedBBlocks, red, grads);
 }
 
 // Column statistics: pass 0 sums x, pass 1 sums (x - mean)^2, per chunk of rows.
@@ -1383,7 +1416,6 @@ hipError_t launch_forward(const NetBufs &net, const float *feat, int64_t B, floa
 hipError_t launch_gradients(const NetBufs &net, const TrainBufs &tb, const float *feat, const float *resid,
                             const int32_t *idx, int64_t nrows, int64_t B, const float inv_scale[3], float *grads,
                             float *loss, hipStream_t st) {
-    const dim3 bl(kBlock);
     TrainArgs a;
     a.feat = feat;
     a.resid = resid;
@@ -1415,11 +1447,8 @@ hipError_t launch_gradients(const NetBufs &net, const TrainBufs &tb, const float
         parts.w[l] = tb.part_w[l];
         parts.b[l] = tb.part_b[l];
     }
-    hipLaunchKernelGGL(k_reduce_w, dim3((unsigned)((kRedTotal + kRedEntries - 1) / kRedEntries)), bl, 0, st, parts,
-                       (int64_t)nc, grads);
-    hipLaunchKernelGGL(k_reduce_b, dim3((unsigned)((kRedBias + kRedBEntries - 1) / kRedBEntries)), dim3(kRedBThreads), 0,
-                       st, parts, (int64_t)nt, grads);
-    if (loss) hipLaunchKernelGGL(k_sum_loss, dim3(1), bl, 0, st, tb.loss_part, B / 16, loss);
+    hipLaunchKernelGGL(k_reduce, dim3(kRedWBlocks + kRedBBlocks + (loss ? 1 : 0)), dim3(kRedThreads), 0, st, parts,
+                       (int64_t)nc, (int64_t)nt, grads, tb.loss_part, B / 16, loss);
     return hipGetLastError();
 }
 
