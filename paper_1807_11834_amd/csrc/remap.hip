@@ -7,8 +7,8 @@
 // weights w_a[off_a[i] + k] = overlap length / receiver cell length.  Built on
 // the host in FP64 once per grid pair.  Applied on the device by one of three
 // kernels: for a receiver finer than the sender in y and z, tiles of receiver
-// rows over an LDS-staged sender slab (k_remap_tile); otherwise receiver rows
-// per workgroup (k_remap_rows: the y, z part of the sum over whole sender rows
+// rows over an LDS-staged sender slab (k_remap_tile); otherwise receiver rows, one
+// per wave (k_remap_rows: the y, z part of the sum over whole sender rows
 // with coalesced loads, then the x part from LDS); for sender rows too long for
 // LDS, one thread per receiver cell (k_remap: raster order z, y, x).
 // In the compensated FP32 mode the tile and per-cell kernels sum in FP64
@@ -77,66 +77,128 @@ __global__ __launch_bounds__(kBlock) void k_remap(RemapArgs<T> r, const T *__res
     dst[(int64_t)blockIdx.y * r.ndst + c] = acc.value();
 }
 
-// Receiver rows (y, z) of one field per workgroup, grid-strided over the rows.
-// A row's y and z factors are the same for the whole workgroup: the (z, y)
-// sender rows it overlaps and their weights wz * wy are tabulated in LDS (up to
-// kMaxQ at a time), then every sender x of the slab is summed over those rows
-// -- each thread issues its kMaxQ loads together -- giving r(x_s) in LDS; then
-// each receiver x sums its overlapping r values with the x weights.  Sum
-// order: (z, y) in raster order, then x.
+// Receiver rows (y, z) of one field, a wave each, grid-strided over the rows.  A
+// row's y and z factors are the same for the whole wave: the offsets of the (z,
+// y) sender rows it overlaps and their weights wz * wy are formed by one lane
+// each (up to kMaxQ at a time) and read as wave-uniform values; then every
+// sender x is summed over those rows -- a lane takes V neighbouring x, 16 bytes,
+// and issues its kMaxQ loads together -- giving r(x_s) in LDS; then each receiver
+// x sums its overlapping r values with the x weights, which the workgroup keeps
+// in LDS where they fit.  Sum order: (z, y) in raster order, then x.
+//
+// Bound by the sender reads.  A row per workgroup, with three barriers per row
+// and one x per thread, kept too few loads in flight: four 256 x 256 x 512 fields
+// to 96 x 96 x 192 took 189 us (3.0 TB/s of algorithmic bytes).
 constexpr int kMaxQ = 16;
 
-template <typename T, int SM>
+template <typename T, int V> using VecX = T __attribute__((ext_vector_type(V)));
+
+// Wave-uniform value of lane l.
+__device__ __forceinline__ int64_t lane_value(int64_t v, int l) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, l), hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ float lane_value(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_value(double v, int l) {
+    return __longlong_as_double(lane_value((int64_t)__double_as_longlong(v), l));
+}
+
+// x factors of the receiver columns, in LDS or in memory.
+template <typename T> struct XFactors {
+    const int32_t *first, *cnt, *off;
+    const T *w;
+};
+
+template <typename T, int SM, int V>
 __global__ __launch_bounds__(kBlock) void k_remap_rows(RemapArgs<T> r, const T *__restrict__ src,
-                                                       T *__restrict__ dst) {
+                                                       T *__restrict__ dst, int nnz_x /* 0: factors in memory */) {
     // both compensated modes run Kahan in T here: FP64 sums of the sixteen
     // rows in flight per thread ran three times slower
     constexpr int SMR = SM == kSumWide ? (int)kSumKahan : SM;
+    using W = SumT<T, SMR>;
+    using Vec = VecX<T, V>;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    T *row = reinterpret_cast<T *>(lds_raw);
-    __shared__ int64_t qoff[kMaxQ];
-    __shared__ T qw[kMaxQ];
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);   // in a scalar register
+    const int nwave = blockDim.x / kWave;
+    const int nsx = r.ns[0], ndx = r.nd[0];
+    const int pitch = (nsx + 3) & ~3;   // rows stay 16-byte aligned
+    T *row = reinterpret_cast<T *>(lds_raw) + (size_t)wave * pitch;
+    XFactors<T> xf{r.first[0], r.cnt[0], r.off[0], r.w[0]};
+    if (nnz_x > 0) {
+        T *sw = reinterpret_cast<T *>(lds_raw) + (size_t)nwave * pitch;
+        int32_t *si = reinterpret_cast<int32_t *>(sw + nnz_x);
+        for (int i = threadIdx.x; i < nnz_x; i += blockDim.x) sw[i] = r.w[0][i];
+        for (int i = threadIdx.x; i < ndx; i += blockDim.x) {
+            si[i] = r.first[0][i];
+            si[ndx + i] = r.cnt[0][i];
+            si[2 * ndx + i] = r.off[0][i];
+        }
+        xf = XFactors<T>{si, si + ndx, si + 2 * ndx, sw};
+    }
+    __syncthreads();
     const int64_t nrow = (int64_t)r.nd[1] * r.nd[2];
     const T *__restrict__ s = src + (int64_t)blockIdx.y * r.nsrc;
-    const int nsx = r.ns[0];
     const int64_t sxy = (int64_t)r.ns[0] * r.ns[1];
-    const int64_t first_row = xcd_tile(blockIdx.x, gridDim.x);
-    for (int64_t rr = first_row; rr < nrow; rr += gridDim.x) {    // uniform over the workgroup
+    // each XCD takes neighbouring rows of the window the grid covers at a time:
+    // they share sender rows in its L2
+    const int64_t chunk = gridDim.x / 8 > kXcdChunk ? gridDim.x / 8 : kXcdChunk;
+    const int64_t tile = xcd_tile(blockIdx.x, gridDim.x, chunk);
+    // Sender row q0 + lane of receiver row rr: its offset and weight, and the
+    // number of sender rows.  Lanes past the last one hold it again, so that the
+    // loads of the rows are not conditional (a conditional load waits for those
+    // before it).
+    auto terms = [&](int64_t rr, int q0, int64_t &qo, T &qw) {
         const int j = (int)(rr % r.nd[1]), k = (int)(rr / r.nd[1]);
         const int fy = r.first[1][j], ny = r.cnt[1][j], oy = r.off[1][j];
         const int fz = r.first[2][k], nz = r.cnt[2][k], oz = r.off[2][k];
-        const int nq = ny * nz;
+        const int nq = ny * nz, q = q0 + lane < nq ? q0 + lane : nq - 1, kz = q / ny, ky = q % ny;
+        qo = (int64_t)(fz + kz) * sxy + (int64_t)(fy + ky) * nsx;
+        qw = r.w[2][oz + kz] * r.w[1][oy + ky];
+        return nq;
+    };
+    const int64_t step = (int64_t)gridDim.x * nwave;
+    int64_t rr = tile * nwave + wave, qo = 0;   // rr: uniform over the wave
+    T qw = T(0);
+    int nq = rr < nrow ? terms(rr, 0, qo, qw) : 0;
+    for (; rr < nrow; rr += step) {
         for (int q0 = 0; q0 < nq; q0 += kMaxQ) {
             const int mq = nq - q0 < kMaxQ ? nq - q0 : kMaxQ;
-            if (threadIdx.x < mq) {
-                const int q = q0 + threadIdx.x, kz = q / ny, ky = q % ny;
-                qoff[threadIdx.x] = (int64_t)(fz + kz) * sxy + (int64_t)(fy + ky) * nsx;
-                qw[threadIdx.x] = r.w[2][oz + kz] * r.w[1][oy + ky];
-            }
-            __syncthreads();
-            for (int xs = threadIdx.x; xs < nsx; xs += kBlock) {
-                T v[kMaxQ];
+            if (q0 > 0) terms(rr, q0, qo, qw);
+            for (int x0 = 0; x0 < nsx; x0 += kWave * V) {   // V divides nsx
+                const int x = x0 + lane * V;
+                const bool on = x < nsx;
+                const int xl = on ? x : 0;
+                Vec v[kMaxQ];
 #pragma unroll
-                for (int q = 0; q < kMaxQ; ++q) v[q] = q < mq ? s[qoff[q] + xs] : T(0);
-                using W = SumT<T, SMR>;
-                FmaSum<T, SMR> acc;
-                if (q0 > 0) acc.s = W(row[xs]);   // continue the partial sum of earlier rows
+                for (int q = 0; q < kMaxQ; ++q) v[q] = *reinterpret_cast<const Vec *>(s + lane_value(qo, q) + xl);
+                FmaSum<T, SMR> acc[V];
+                if (q0 > 0 && on)   // continue the partial sum of earlier rows
+#pragma unroll
+                    for (int c = 0; c < V; ++c) acc[c].s = W(row[x + c]);
 #pragma unroll
                 for (int q = 0; q < kMaxQ; ++q)
-                    if (q < mq) acc.add(W(qw[q]), W(v[q]));
-                row[xs] = acc.value();
+                    if (q < mq) {
+                        const W w = W(lane_value(qw, q));
+#pragma unroll
+                        for (int c = 0; c < V; ++c) acc[c].add(w, W(v[q][c]));
+                    }
+                if (on)
+#pragma unroll
+                    for (int c = 0; c < V; ++c) row[x + c] = acc[c].value();
             }
-            __syncthreads();
         }
-        T *__restrict__ out = dst + (int64_t)blockIdx.y * r.ndst + rr * r.nd[0];
-        for (int xd = threadIdx.x; xd < r.nd[0]; xd += kBlock) {
-            const int fx = r.first[0][xd], nx = r.cnt[0][xd], ox = r.off[0][xd];
-            using W = SumT<T, SMR>;
+        wave_sync();
+        if (rr + step < nrow) nq = terms(rr + step, 0, qo, qw);   // while the x part runs
+        T *__restrict__ out = dst + (int64_t)blockIdx.y * r.ndst + rr * ndx;
+        for (int xd = lane; xd < ndx; xd += kWave) {
+            const int fx = xf.first[xd], nx = xf.cnt[xd], ox = xf.off[xd];
             FmaSum<T, SMR> acc;
-            for (int kx = 0; kx < nx; ++kx) acc.add(W(r.w[0][ox + kx]), W(row[fx + kx]));
+            for (int kx = 0; kx < nx; ++kx) acc.add(W(xf.w[ox + kx]), W(row[fx + kx]));
             out[xd] = acc.value();
         }
-        __syncthreads();   // the row buffer is reused by the next row
+        wave_sync();   // the row buffer is reused by the next row
     }
 }
 
@@ -300,9 +362,14 @@ __global__ __launch_bounds__(kBlock) void k_remap_tile(RemapArgs<T> r, const T *
 // LDS use k_remap_tile when the receiver is finer than the sender in y and z.
 constexpr size_t kTileLdsBytes = 96 * 1024;
 
-// Sender rows up to this many bytes are staged whole in LDS by k_remap_rows;
-// longer rows take k_remap.
+// Sender rows up to this many bytes are staged whole in LDS by k_remap_rows, four
+// (of four waves) or one to a workgroup; longer rows take k_remap.
 constexpr size_t kRowLdsBytes = 60 * 1024;
+// The x factors go to LDS with them up to this many bytes.
+constexpr size_t kFactorLdsBytes = 24 * 1024;
+// Workgroups of the row kernel over all fields: sixteen waves per compute unit,
+// four rounds, so that the last round is a small part.
+constexpr int64_t kRowBlocks = 4096;
 
 }  // namespace
 
@@ -492,12 +559,22 @@ static hipError_t launch_remap(const couple_remap *r, const void *src, void *dst
         hipLaunchKernelGGL((k_remap_tile<T, SM>), dim3((unsigned)ntile, (unsigned)nfields), dim3(kBlock), tile_lds,
                            st, a, static_cast<const T *>(src), static_cast<T *>(dst), vec4);
     } else if (lds <= kRowLdsBytes) {
-        // enough workgroups to fill the chip several times over, each looping
-        // over rows (a row is a small amount of work when the receiver is finer)
-        const int64_t nrow = (int64_t)r->nd[1] * r->nd[2];
-        const int64_t per_field = std::max<int64_t>(1, std::min<int64_t>(nrow, 8192 / nfields + 1));
-        hipLaunchKernelGGL((k_remap_rows<T, SM>), dim3((unsigned)per_field, (unsigned)nfields), dim3(kBlock), lds,
-                           st, a, static_cast<const T *>(src), static_cast<T *>(dst));
+        const int waves = 4 * lds <= kRowLdsBytes ? 4 : 1;
+        size_t fac = sizeof(T) * (size_t)r->ax[0].nnz + 3 * sizeof(int32_t) * (size_t)r->nd[0];
+        if (fac > kFactorLdsBytes || fac + waves * lds + 64 > kRowLdsBytes) fac = 0;
+        const int nnz_x = fac ? (int)r->ax[0].nnz : 0;
+        const size_t bytes = (size_t)waves * sizeof(T) * (((size_t)r->ns[0] + 3) & ~(size_t)3) + fac;
+        const int64_t nblk = ((int64_t)r->nd[1] * r->nd[2] + waves - 1) / waves;
+        const int64_t per_field = std::max<int64_t>(1, std::min<int64_t>(nblk, kRowBlocks * (4 / waves) / nfields + 1));
+        constexpr int VW = 16 / sizeof(T);
+        const bool vec = r->ns[0] % VW == 0 && reinterpret_cast<uintptr_t>(src) % 16 == 0;
+        auto rows = [&](auto vc) {
+            hipLaunchKernelGGL((k_remap_rows<T, SM, decltype(vc)::value>), dim3((unsigned)per_field, (unsigned)nfields),
+                               dim3((unsigned)(waves * kWave)), bytes, st, a, static_cast<const T *>(src),
+                               static_cast<T *>(dst), nnz_x);
+        };
+        if (vec) rows(std::integral_constant<int, VW>{});
+        else rows(std::integral_constant<int, 1>{});
     } else {
         const int64_t nblk = (a.ndst + kBlock - 1) / kBlock;
         hipLaunchKernelGGL((k_remap<T, SM>), dim3((unsigned)nblk, (unsigned)nfields), dim3(kBlock), 0, st, a,
