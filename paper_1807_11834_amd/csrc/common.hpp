@@ -125,8 +125,7 @@ template <typename T> struct Axis {
     int lo, hi;   // clamped node indices (equal when folded at a wall)
     T t;          // weight of `hi`; `lo` has 1 - t
 };
-template <typename T> __device__ __forceinline__ Axis<T> cic_axis(T x, T s, int n) {
-    T g = x * s - T(0.5);
+template <typename T> __device__ __forceinline__ Axis<T> cic_axis_at(T g, int n) {   // g: position in node units
     T jf = dfloor(g);
     int j = (int)jf;
     Axis<T> a;
@@ -134,6 +133,15 @@ template <typename T> __device__ __forceinline__ Axis<T> cic_axis(T x, T s, int 
     a.lo = clampi(j, n);
     a.hi = clampi(j + 1, n);
     return a;
+}
+template <typename T> __device__ __forceinline__ Axis<T> cic_axis(T x, T s, int n) {
+    return cic_axis_at(dfma(x, s, T(-0.5)), n);
+}
+// x * s - 1/2 with the product rounded (not one FMA).
+template <typename T> __device__ __forceinline__ T node_units_rounded(T x, T s) {
+#pragma clang fp contract(off)
+    const T p = x * s;
+    return p - T(0.5);
 }
 // Weight of axis stencil `a` on node `c` (folded corners add up).
 template <typename T> __device__ __forceinline__ T axis_weight(const Axis<T> &a, int c) {
@@ -173,10 +181,13 @@ __device__ __forceinline__ void gradient_at(int64_t c, int cx, int cy, int cz, c
 // [0, n]: a no-op for a consistent `start`, it keeps every load in bounds.
 __device__ __forceinline__ int32_t seg_clamp(int32_t v, int64_t n) { return v < 0 ? 0 : (v > n ? (int32_t)n : v); }
 
+// Cell c -> (cx, cy, cz), in 32 bits (there are fewer than 2^31 cells: a 64-bit
+// division takes some hundred instructions).
 __device__ __forceinline__ void decode_cell(int64_t c, const int nb[3], int &cx, int &cy, int &cz) {
-    cx = (int)(c % nb[0]);
-    cy = (int)((c / nb[0]) % nb[1]);
-    cz = (int)(c / ((int64_t)nb[0] * nb[1]));
+    const uint32_t row = (uint32_t)c / (uint32_t)nb[0], layer = row / (uint32_t)nb[1];
+    cx = (int)((uint32_t)c - row * (uint32_t)nb[0]);
+    cy = (int)(row - layer * (uint32_t)nb[1]);
+    cz = (int)layer;
 }
 
 // LDS written by some lanes of a wave and read by other lanes of the same wave:
@@ -194,12 +205,13 @@ __device__ __forceinline__ void wave_sync() {
 // The final partial round of chunks keeps the identity mapping (a bijection).
 constexpr int64_t kXcdChunk = 16;
 __device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t nblk, int64_t chunk = kXcdChunk) {
-    const int64_t nx = 8, round = nx * chunk;
-    const int64_t full = (nblk / round) * round;
-    if (b >= full) return b;
-    const int64_t x = b % nx, k = b / nx;          // k-th workgroup dealt to XCD x
-    const int64_t q = k / chunk, r = k % chunk;
-    return (q * nx + x) * chunk + r;
+    // 32 bits: there are fewer than 2^31 tiles
+    const uint32_t nx = 8, ch = (uint32_t)chunk, round = nx * ch, t = (uint32_t)b;
+    const uint32_t full = (uint32_t)nblk / round * round;
+    if (t >= full) return b;
+    const uint32_t x = t % nx, k = t / nx;          // k-th workgroup dealt to XCD x
+    const uint32_t q = k / ch, r = k - q * ch;
+    return (q * nx + x) * ch + r;
 }
 
 // ---- wave / block reductions (fixed tree order -> deterministic) -----------

@@ -423,9 +423,9 @@ __global__ __launch_bounds__(kBlock) void k_deposit_rows(const int32_t *__restri
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int64_t gw = tile * kWavesPerBlock + w;        // (source group, segment)
     if (gw >= nwave) return;                             // wave-uniform; no block barriers below
-    const int64_t grp = gw / nseg;
-    const int x0 = (int)(gw % nseg) * kWave;
-    const int gy = (int)(grp % ngy), gz = (int)(grp / ngy);
+    const uint32_t grp = (uint32_t)gw / (uint32_t)nseg;   // fewer than 2^31 waves
+    const int x0 = (int)((uint32_t)gw - grp * (uint32_t)nseg) * kWave;
+    const int gz = (int)(grp / (uint32_t)ngy), gy = (int)(grp - (uint32_t)gz * (uint32_t)ngy);
     const int x = x0 + lane;
     const int y0 = GS * gy, z0 = GS * gz;
     RowSum<T, SM> acc[A][A][NC];   // [target z - (z0 - 1)][target y - (y0 - 1)][component]

@@ -52,18 +52,54 @@ __device__ __forceinline__ T trilin_pairs(const T *__restrict__ f, const Axis<T>
     return sz * e0 + az.t * e1;
 }
 
-// Trilinear interpolation of the fine-grid velocity at the clamped position q.
+// The four (y, z) rows of x-pairs of one component, and their trilinear value.
+// The products and sums are rounded as written (every sum one FMA), so that a
+// particle's velocity does not depend on where the compiler contracts them; Z:
+// which of the two planes' products is rounded first.
+template <typename T> struct PairRows {
+    T lo[4], hi[4];   // rows (z lo, y lo), (z lo, y hi), (z hi, y lo), (z hi, y hi)
+};
+template <typename T>
+__device__ __forceinline__ PairRows<T> load_pair_rows(const T *__restrict__ f, const Axis<T> &ax, const Axis<T> &ay,
+                                                      const Axis<T> &az, int64_t nx, int64_t nxy) {
+    PairRows<T> r;
+    const int64_t z[2] = {az.lo * nxy, az.hi * nxy}, y[2] = {ay.lo * nx, ay.hi * nx};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) load_pair(f + z[k >> 1] + y[k & 1], ax.lo, ax.hi, r.lo[k], r.hi[k]);
+    return r;
+}
+template <bool Z, typename T>
+__device__ __forceinline__ T trilin_rows(const PairRows<T> &r, const Axis<T> &ax, const Axis<T> &ay, const Axis<T> &az) {
+    const T sx = T(1) - ax.t, sy = T(1) - ay.t, sz = T(1) - az.t;
+    const T c00 = dfma(ax.t, r.hi[0], sx * r.lo[0]), c01 = dfma(ax.t, r.hi[1], sx * r.lo[1]),
+            c10 = dfma(ax.t, r.hi[2], sx * r.lo[2]), c11 = dfma(sx, r.lo[3], ax.t * r.hi[3]);
+    const T e0 = dfma(sy, c00, ay.t * c01), e1 = dfma(sy, c10, ay.t * c11);
+    return Z ? dfma(sz, e0, az.t * e1) : dfma(az.t, e1, sz * e0);
+}
+
+// Trilinear interpolation of the fine-grid velocity at the clamped position q:
+// the twelve row loads of the three components are issued before any is used
+// (component by component, each waited for the one before).
 template <typename T>
 __device__ __forceinline__ void fine_velocity(const vec4<T> &q, const StepArgs<T> &a, T &ux, T &uy, T &uz) {
     const Geo<T> &g = a.g;
     const Axis<T> fx = cic_axis(q.x, g.sf[0], g.nf[0]);
     const Axis<T> fy = cic_axis(q.y, g.sf[1], g.nf[1]);
     const Axis<T> fz = cic_axis(q.z, g.sf[2], g.nf[2]);
-    const int nx = g.nf[0];
-    const int64_t nxy = (int64_t)g.nf[0] * g.nf[1];
-    ux = trilin_pairs(a.fine[0], fx, fy, fz, nx, nxy);
-    uy = trilin_pairs(a.fine[1], fx, fy, fz, nx, nxy);
-    uz = trilin_pairs(a.fine[2], fx, fy, fz, nx, nxy);
+    const int64_t nx = g.nf[0], nxy = (int64_t)g.nf[0] * g.nf[1];
+    if (nx == 1) {   // no pair to load: uniform over the launch
+        ux = trilin(a.fine[0], fx, fy, fz, nx, nxy);
+        uy = trilin(a.fine[1], fx, fy, fz, nx, nxy);
+        uz = trilin(a.fine[2], fx, fy, fz, nx, nxy);
+        return;
+    }
+    PairRows<T> r[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r[k] = load_pair_rows(a.fine[k], fx, fy, fz, nx, nxy);
+    __builtin_amdgcn_sched_barrier(0);
+    ux = trilin_rows<false>(r[0], fx, fy, fz);
+    uy = trilin_rows<false>(r[1], fx, fy, fz);
+    uz = trilin_rows<false>(r[2], fx, fy, fz);
 }
 
 // Void fraction at one particle (clamped position q.xyz): eps_p = sum_c w_pc
@@ -135,9 +171,19 @@ __device__ __forceinline__ vec4<T> sample_one(const vec4<T> &q, const StepArgs<T
         const Axis<T> bz = cic_axis(q.z, g.sb[2], g.nb[2]);
         const int nx = g.nb[0];
         const int64_t nxy = (int64_t)g.nb[0] * g.nb[1];
-        s.x = trilin_pairs(a.U, bx, by, bz, nx, nxy);
-        s.y = trilin_pairs(a.U + g.ncell, bx, by, bz, nx, nxy);
-        s.z = trilin_pairs(a.U + 2 * g.ncell, bx, by, bz, nx, nxy);
+        if (nx == 1) {
+            s.x = trilin(a.U, bx, by, bz, nx, nxy);
+            s.y = trilin(a.U + g.ncell, bx, by, bz, nx, nxy);
+            s.z = trilin(a.U + 2 * g.ncell, bx, by, bz, nx, nxy);
+        } else {
+            PairRows<T> r[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) r[k] = load_pair_rows(a.U + k * g.ncell, bx, by, bz, nx, nxy);
+            __builtin_amdgcn_sched_barrier(0);
+            s.x = trilin_rows<false>(r[0], bx, by, bz);
+            s.y = trilin_rows<false>(r[1], bx, by, bz);
+            s.z = trilin_rows<true>(r[2], bx, by, bz);
+        }
     } else {
         s.x = s.y = s.z = T(0);   // the drag kernel takes u_f from uf_given
     }

@@ -370,9 +370,10 @@ template <typename T, int R> struct BrickLds {
 template <typename T> struct BrickGrid {
     int bnx, bny;
     __device__ __forceinline__ void origin(int64_t brick, int &ox, int &oy, int &oz) const {
-        ox = (int)(brick % bnx) * kBrickX;
-        oy = (int)((brick / bnx) % bny) * kBrickY;
-        oz = (int)(brick / ((int64_t)bnx * bny)) * kBrickZ;
+        const uint32_t row = (uint32_t)brick / (uint32_t)bnx, layer = row / (uint32_t)bny;   // fewer than 2^31 bricks
+        ox = (int)((uint32_t)brick - row * (uint32_t)bnx) * kBrickX;
+        oy = (int)(row - layer * (uint32_t)bny) * kBrickY;
+        oz = (int)layer * kBrickZ;
     }
 };
 
@@ -501,15 +502,15 @@ __device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const Bric
             const int xl = ax.lo - fx0, xh = ax.hi - fx0, yl = ay.lo - fy0, yh = ay.hi - fy0, zl = az.lo - fz0,
                       zh = az.hi - fz0;
             if (xl >= 0 && xh < FX && yl >= 0 && yh < FY && zl >= 0 && zh < FZ) {
-                const T sx = T(1) - ax.t, sy = T(1) - ay.t, sz = T(1) - az.t;
+                const T tx = ax.t, ty = ay.t, tz = az.t, sx = T(1) - tx, sy = T(1) - ty, sz = T(1) - tz;
                 T u[3];
 #pragma unroll
                 for (int f = 0; f < 3; ++f) {
-                    const T e0 = sy * (sx * L.sv[f][zl][yl][xl] + ax.t * L.sv[f][zl][yl][xh]) +
-                                 ay.t * (sx * L.sv[f][zl][yh][xl] + ax.t * L.sv[f][zl][yh][xh]);
-                    const T e1 = sy * (sx * L.sv[f][zh][yl][xl] + ax.t * L.sv[f][zh][yl][xh]) +
-                                 ay.t * (sx * L.sv[f][zh][yh][xl] + ax.t * L.sv[f][zh][yh][xh]);
-                    u[f] = sz * e0 + az.t * e1;
+                    // rounded as written (see trilin_rows; the last sum of w in the other order)
+                    auto row = [&](int z, int y) { return dfma(sx, L.sv[f][z][y][xl], tx * L.sv[f][z][y][xh]); };
+                    const T e0 = dfma(sy, row(zl, yl), ty * row(zl, yh));
+                    const T e1 = dfma(sy, row(zh, yl), ty * row(zh, yh));
+                    u[f] = f < 2 ? dfma(sz, e0, tz * e1) : dfma(tz, e1, sz * e0);
                 }
                 s.x = u[0];
                 s.y = u[1];
@@ -520,7 +521,7 @@ __device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const Bric
             // void fraction at the particle from the haloed phi (its stencil is the
             // containing cell and a neighbour, always inside the halo)
             if (a.cic) {
-                const Axis<T> bx = cic_axis(q.x, g.sb[0], g.nb[0]);
+                const Axis<T> bx = cic_axis_at(node_units_rounded(q.x, g.sb[0]), g.nb[0]);
                 const Axis<T> by = cic_axis(q.y, g.sb[1], g.nb[1]);
                 const Axis<T> bz = cic_axis(q.z, g.sb[2], g.nb[2]);
                 const int hxl = bx.lo - ox + 1, hxh = bx.hi - ox + 1, hyl = by.lo - oy + 1, hyh = by.hi - oy + 1,
@@ -795,8 +796,9 @@ __global__ __launch_bounds__(kBlock) void k_prolong(StepArgs<T> a, ProlongSet<T>
     double sum = 0.0;
     for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
         const int64_t item = xcd_tile(it, items, layer < kXcdChunk ? kXcdChunk : layer);
-        const int cx0 = (int)(item % tnx) << xs, cy0 = (int)((item / tnx) % tny) << ys;
-        const int pz = (int)(item / layer) * planes, cz = pz / R, lz0 = pz % R;   // first fine plane
+        const uint32_t trow = (uint32_t)item / (uint32_t)tnx, tlay = trow / (uint32_t)tny;   // fewer than 2^31 items
+        const int cx0 = (int)((uint32_t)item - trow * (uint32_t)tnx) << xs, cy0 = (int)(trow - tlay * (uint32_t)tny) << ys;
+        const int pz = (int)tlay * planes, cz = pz / R, lz0 = pz % R;   // first fine plane
         // staging: the H + 2 rows of the tile in two rounds of H, and the two
         // halo columns, every load issued before the first LDS write
         const int64_t zo[3] = {(cz > 0 ? cz - 1 : 0) * nxy, cz * nxy, (cz + 1 < g.nb[2] ? cz + 1 : cz) * nxy};
