@@ -509,10 +509,9 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
     __shared__ __align__(16) uint16_t stage[kStageRows * kStagePitch];
     __shared__ float norm[2 * kK1];
     __shared__ double bsum[kTrainTiles][kBiasCols];
-    for (int i = threadIdx.x; i < 2 * kK1; i += kTrainThreads) norm[i] = a.mean_inv[i];
-    __syncthreads();
     constexpr int64_t kOffB0 = off_b(0), kOffB1 = off_b(1), kOffB2 = off_b(2), kOffB3 = off_b(3);
-    const int lane = lane_id(), n = lane & 15, g = lane >> 4, w = threadIdx.x >> 6;
+    const int lane = lane_id(), n = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t tile0 = (int64_t)blockIdx.x * kTrainTiles;
     uint16_t *sh = stage + kStageHt * kStagePitch, *sd = stage + kStageDz * kStagePitch;
     f32x4 acc[2][2], gp[3][2][2];
@@ -520,33 +519,75 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
     bf16x8 x[2][4], f[2][4];
     float4 bv[2];
 
-    // the rows of both tiles; this wave's share of the layer-1 input, feature
-    // blocks kb = 2w, 2w + 1 (< 7), standardised and staged; the layer-1
-    // weight fragments of its neuron blocks
+    // The standardisation table, the row numbers of both tiles and the layer-1
+    // weight fragments of this wave's neuron blocks; then, from the row numbers,
+    // the rows' residuals and the wave's share of their features, blocks kb = 2w,
+    // 2w + 1 (< 7): two memory round trips.  No load is conditional: one that is
+    // waits for those before it, and the rows element by element, tile after
+    // tile, made nine round trips of the two (114 us for 65,536 rows).
     float t[2][4];
     {
-        float fv[2][2][8];
+        constexpr int kNormPer = (2 * kK1 + kTrainThreads - 1) / kTrainThreads;
+        float nv[kNormPer];
 #pragma unroll
-        for (int tt = 0; tt < 2; ++tt) {
-            const int64_t b = (tile0 + tt) * 16 + n;
-            int64_t row = a.idx ? (int64_t)a.idx[b] : b;
-            if (row < 0 || row >= a.nrows) row = 0;   // documented: indices must be in range; keeps loads in bounds
-            const float *fr = a.feat + row * kFeat;
+        for (int i = 0; i < kNormPer; ++i) {
+            const int e = threadIdx.x + i * kTrainThreads;
+            nv[i] = a.mean_inv[e < 2 * kK1 ? e : 0];
+        }
+        int64_t row[2];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) t[tt][j] = (g == 0 && j < kOut) ? a.resid[row * 3 + j] * a.is[j] : 0.f;
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int k = 32 * (2 * w + kk) + 8 * g + i;
-                    fv[tt][kk][i] = k < kFeat ? fr[k] : 0.f;
-                }
+        for (int tt = 0; tt < 2; ++tt) row[tt] = (tile0 + tt) * 16 + n;
+        if (a.idx) {   // uniform over the launch
+            const int32_t r0 = a.idx[row[0]], r1 = a.idx[row[1]];
+            row[0] = r0;
+            row[1] = r1;
         }
         bf16x8 f1[2][7];
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int kb = 0; kb < 7; ++kb) f1[b][kb] = load8(a.wt0 + (16 * (2 * w + b) + n) * kK1 + 32 * kb + 8 * g);
+        issue_fence();
+        float fv[2][2][8], rv[2][kOut];
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) {
+            if (row[tt] < 0 || row[tt] >= a.nrows) row[tt] = 0;   // documented: indices must be in range; keeps loads in bounds
+#pragma unroll
+            for (int j = 0; j < kOut; ++j) rv[tt][j] = a.resid[row[tt] * 3 + j];
+        }
+        if (w < 3) {   // uniform over the wave: blocks 2w, 2w + 1 <= 5 are whole
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const float4_u q = *reinterpret_cast<const float4_u *>(a.feat + row[tt] * kFeat +
+                                                                              32 * (2 * w + kk) + 8 * g + 4 * h);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) fv[tt][kk][4 * h + i] = q[i];
+                    }
+        } else {       // block 6: feature 192 alone
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt) {
+                const float q = a.feat[row[tt] * kFeat + kFeat - 1];
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) fv[tt][kk][i] = (kk == 0 && i == 0 && g == 0) ? q : 0.f;
+            }
+        }
+        issue_fence();
+#pragma unroll
+        for (int i = 0; i < kNormPer; ++i) {
+            const int e = threadIdx.x + i * kTrainThreads;
+            if (e < 2 * kK1) norm[e] = nv[i];
+        }
+        __syncthreads();   // the standardisation table
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) t[tt][j] = (g == 0 && j < kOut) ? rv[tt][j < kOut ? j : 0] * a.is[j < kOut ? j : 0] : 0.f;
         issue_fence();
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt)
@@ -604,9 +645,11 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
     for (int b = 0; b < 2; ++b) f4[b] = load8(a.wnp[3] + (16 * (2 * w + b) + n) * 32 + 8 * g);
     load_bias(a.params + kOffB2, w, g, bv);
     float yb[4] = {0.f, 0.f, 0.f, 0.f};   // output bias of the lane's rows m = 4 g + j
-    if (g == 0)
 #pragma unroll
-        for (int j = 0; j < kOut; ++j) yb[j] = a.params[kOffB3 + j];
+    for (int j = 0; j < kOut; ++j) {
+        const float q = a.params[kOffB3 + j];
+        yb[j] = g == 0 ? q : 0.f;
+    }
     issue_fence();
     finish_hidden(acc, bv, w, n, g, sh + 2 * kHid * kStagePitch, gp[2], wv);
     __syncthreads();   // layer 3 staged
