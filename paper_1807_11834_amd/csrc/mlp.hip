@@ -748,68 +748,80 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
 //   part_w[c][m][k] = sum_{b in chunk} dZ[b][m] H[b][k]   (BF16 x BF16, FP32 accumulate)
 // from the training pass's transposed rows (dZ rows dz_row + 16 MT, H rows
 // h_row + 16 KT, blocks of kTrBlock batch rows).  Rows in chunks of kChunk; B
-// is a multiple of 32.  Each of the kWgradWaves waves of a workgroup owns
-// output column blocks kt and keeps all MT row blocks in registers: per 32 rows
-// it loads one H fragment and the MT dZ fragments and issues MT independent
-// products.
-constexpr int kWgradWaves = 8;
-template <int MT, int KT>
-__device__ __forceinline__ void wgrad_chunk(const uint16_t *__restrict__ tr, int dz_row, int h_row, int64_t B,
+// is a multiple of 32.  A wave takes NK output column blocks from kt on and
+// keeps all MT row blocks of each in registers: per 32 rows it loads NK H
+// fragments and the MT dZ fragments and issues NK MT independent products.  The
+// fragment loads bound it (a dZ fragment is read once per wave of its layer):
+// with one column block per wave they were 9 for 8 products (49 us for 65,536
+// rows), with two they are 10 for 16.
+template <int MT, int KT, int NK>
+__device__ __forceinline__ void wgrad_chunk(const uint16_t *__restrict__ tr, int dz_row, int h_row, int64_t B, int kt,
                                             float *__restrict__ part_w) {
     constexpr int MP = 16 * MT, KP = 16 * KT;
     constexpr int64_t kBlk = (int64_t)kTrRows * kTrBlock;   // elements per block of batch rows
     static_assert(kTrBlock == 32, "one block per 32-row product");
-    const int lane = lane_id(), n = lane & 15, g = lane >> 4, wave = threadIdx.x >> 6;
+    const int lane = lane_id(), n = lane & 15, g = lane >> 4;
     const int64_t c = blockIdx.x;
     const int64_t b0 = c * kChunk, b1 = (b0 + kChunk < B) ? b0 + kChunk : B;
-    for (int kt = wave; kt < KT; kt += kWgradWaves) {
-        f32x4 acc[MT];
+    f32x4 acc[NK][MT];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const uint16_t *pb = tr + (int64_t)(h_row + 16 * kt + n) * kTrBlock + 8 * g;
-        const uint16_t *pa = tr + (int64_t)(dz_row + n) * kTrBlock + 8 * g;
-        // kU groups of 32 rows per round, all their loads issued before the
-        // products (the rows are still summed in order)
-        constexpr int kU = MT > 4 ? 4 : 8;
-        for (int64_t bb = b0; bb < b1; bb += 32 * kU) {
-            bf16x8 bv[kU];
-            bf16x8 av[kU][MT];
+    for (int k = 0; k < NK; ++k)
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int64_t r = bb + 32 * u < b1 ? bb + 32 * u : b1 - 32;
-                const int64_t o = (r / kTrBlock) * kBlk;
-                bv[u] = load8(pb + o);
+        for (int mt = 0; mt < MT; ++mt) acc[k][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint16_t *pb = tr + (int64_t)(h_row + 16 * kt + n) * kTrBlock + 8 * g;
+    const uint16_t *pa = tr + (int64_t)(dz_row + n) * kTrBlock + 8 * g;
+    // kU groups of 32 rows per round, all their loads issued before the products
+    // (the rows are still summed in order)
+    constexpr int kU = 4;
+    for (int64_t bb = b0; bb < b1; bb += 32 * kU) {
+        bf16x8 bv[kU][NK];
+        bf16x8 av[kU][MT];
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) av[u][mt] = load8(pa + 16 * mt * kTrBlock + o);
-            }
+        for (int u = 0; u < kU; ++u) {
+            const int64_t r = bb + 32 * u < b1 ? bb + 32 * u : b1 - 32;
+            const int64_t o = (r / kTrBlock) * kBlk;
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                if (bb + 32 * u >= b1) break;
+            for (int k = 0; k < NK; ++k) bv[u][k] = load8(pb + 16 * k * kTrBlock + o);
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[mt] = mma(av[u][mt], bv[u], acc[mt]);
-            }
+            for (int mt = 0; mt < MT; ++mt) av[u][mt] = load8(pa + 16 * mt * kTrBlock + o);
         }
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            float *o = part_w + (c * MP + 16 * mt + 4 * g) * KP + 16 * kt + n;
+        for (int u = 0; u < kU; ++u) {
+            if (bb + 32 * u >= b1) break;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o[(int64_t)j * KP] = acc[mt][j];
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int k = 0; k < NK; ++k) acc[k][mt] = mma(av[u][mt], bv[u][k], acc[k][mt]);
         }
     }
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            float *o = part_w + (c * MP + 16 * mt + 4 * g) * KP + 16 * (kt + k) + n;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[(int64_t)j * KP] = acc[k][mt][j];
+        }
 }
 
-// The four layers' weight gradients in one launch (blockIdx.y = layer), so
-// that the short layers fill the tail of the long one.
+// The four layers' weight gradients in one launch.  Of the eight waves of
+// workgroup (chunk, 0) seven take layer 1's fourteen column blocks and one the
+// eight of layer 4 (one row block each); those of (chunk, 1) take the eight of
+// layer 2 and of layer 3.
+constexpr int kWgradWaves = 8;
 struct WgradParts {
     float *w[4];
 };
 __global__ __launch_bounds__(kWgradWaves * kWave) void k_wgrad(const uint16_t *__restrict__ tr, int64_t B,
                                                                WgradParts parts) {
-    switch (blockIdx.y) {
-    case 0: wgrad_chunk<8, 14>(tr, kTrDz, 0, B, parts.w[0]); break;
-    case 1: wgrad_chunk<8, 8>(tr, kTrDz + kHid, kTrHt, B, parts.w[1]); break;
-    case 2: wgrad_chunk<8, 8>(tr, kTrDz + 2 * kHid, kTrHt + kHid, B, parts.w[2]); break;
-    default: wgrad_chunk<1, 8>(tr, kTrDz + 3 * kHid, kTrHt + 2 * kHid, B, parts.w[3]); break;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (blockIdx.y == 0) {
+        if (w < 7) wgrad_chunk<8, 14, 2>(tr, kTrDz, 0, B, 2 * w, parts.w[0]);
+        else wgrad_chunk<1, 8, 8>(tr, kTrDz + 3 * kHid, kTrHt + 2 * kHid, B, 0, parts.w[3]);
+    } else if (w < 4) {
+        wgrad_chunk<8, 8, 2>(tr, kTrDz + kHid, kTrHt, B, 2 * w, parts.w[1]);
+    } else {
+        wgrad_chunk<8, 8, 2>(tr, kTrDz + 2 * kHid, kTrHt + kHid, B, 2 * (w - 4), parts.w[2]);
     }
 }
 
@@ -1484,7 +1496,7 @@ hipError_t launch_gradients(const NetBufs &net, const TrainBufs &tb, const float
     const dim3 bw(kWgradWaves * kWave);
     WgradParts wp;
     for (int l = 0; l < 4; ++l) wp.w[l] = tb.part_w[l];
-    hipLaunchKernelGGL(k_wgrad, dim3(nc, 4), bw, 0, st, tb.tr, B, wp);
+    hipLaunchKernelGGL(k_wgrad, dim3(nc, 2), bw, 0, st, tb.tr, B, wp);
     GradParts parts;
     for (int l = 0; l < 4; ++l) {
         parts.w[l] = tb.part_w[l];
