@@ -753,7 +753,8 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
 // fragments and the MT dZ fragments and issues NK MT independent products.  The
 // fragment loads bound it (a dZ fragment is read once per wave of its layer):
 // with one column block per wave they were 9 for 8 products (49 us for 65,536
-// rows), with two they are 10 for 16.
+// rows), with two they are 10 for 16 (35.9 us); with the 256 rows of a whole chunk
+// loaded at once instead of 128, 33.5 us.
 template <int MT, int KT, int NK>
 __device__ __forceinline__ void wgrad_chunk(const uint16_t *__restrict__ tr, int dz_row, int h_row, int64_t B, int kt,
                                             float *__restrict__ part_w) {
@@ -772,7 +773,7 @@ __device__ __forceinline__ void wgrad_chunk(const uint16_t *__restrict__ tr, int
     const uint16_t *pa = tr + (int64_t)(dz_row + n) * kTrBlock + 8 * g;
     // kU groups of 32 rows per round, all their loads issued before the products
     // (the rows are still summed in order)
-    constexpr int kU = 4;
+    constexpr int kU = 8;
     for (int64_t bb = b0; bb < b1; bb += 32 * kU) {
         bf16x8 bv[kU][NK];
         bf16x8 av[kU][MT];
