@@ -220,19 +220,37 @@ struct ForwardNet {
     const float *params, *mean_inv;
 };
 
+// One layer's weights (rows of 32 KB BF16, 16 MB rows) into LDS as product
+// fragments [neuron block][contraction block], 16 bytes per lane, by THREADS
+// threads; all its loads are issued together.  (One loop over the fragments of
+// all layers waits for the layer's address and then its weights, a fragment at a
+// time: 26.5 us for the forward pass of 50,001 rows, 23.1 with all together.)
+template <int KB, int MB, int THREADS>
+__device__ __forceinline__ void stage_weights(const uint16_t *__restrict__ W, uint4 (*frag)[kWave]) {
+    constexpr int kItems = MB * KB * kWave, kPer = (kItems + THREADS - 1) / THREADS;
+    uint4 v[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e0 = threadIdx.x + i * THREADS, e = e0 < kItems ? e0 : 0;
+        const int f = e >> 6, r = e & 15, gg = (e >> 4) & 3;
+        v[i] = *reinterpret_cast<const uint4 *>(W + (16 * (f / KB) + r) * (32 * KB) + 32 * (f % KB) + 8 * gg);
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = threadIdx.x + i * THREADS;
+        if (e < kItems) frag[e >> 6][e & 63] = v[i];
+    }
+}
+
 __global__ __launch_bounds__(kFwdWaves * kWave) void k_forward(const float *__restrict__ feat, int64_t B, ForwardNet net,
                                                                float *__restrict__ y) {
     __shared__ ForwardLds L;
     constexpr int NT = kFwdTiles, kThreads = kFwdWaves * kWave;
     const int lane = lane_id(), n = lane & 15, g = lane >> 4, wave = threadIdx.x >> 6;
-    for (int e = threadIdx.x; e < kFwdFrags * kWave; e += kThreads) {
-        const int f = e >> 6, r = e & 15, gg = (e >> 4) & 3;
-        const int l = f < kFwdFrag1 ? 0 : (f < kFwdFrag1 + kFwdFragH ? 1 : (f < kFwdFrag1 + 2 * kFwdFragH ? 2 : 3));
-        const int ff = f - (l == 0 ? 0 : kFwdFrag1 + (l - 1) * kFwdFragH), kbs = l == 0 ? 7 : 4;
-        const int mb = ff / kbs, kb = ff % kbs;
-        L.frag[f][e & 63] =
-            *reinterpret_cast<const uint4 *>(net.wt[l] + (16 * mb + r) * (32 * kbs) + 32 * kb + 8 * gg);
-    }
+    stage_weights<7, 8, kThreads>(net.wt[0], L.frag);
+    stage_weights<4, 8, kThreads>(net.wt[1], L.frag + kFwdFrag1);
+    stage_weights<4, 8, kThreads>(net.wt[2], L.frag + kFwdFrag1 + kFwdFragH);
+    stage_weights<4, 1, kThreads>(net.wt[3], L.frag + kFwdFrag1 + 2 * kFwdFragH);
     for (int e = threadIdx.x; e < 3 * kHid + 16; e += kThreads) {
         const int l = e / kHid, m = e % kHid;
         constexpr int64_t kB0 = off_b(0), kB1 = off_b(1), kB2 = off_b(2), kB3 = off_b(3);
@@ -1051,7 +1069,7 @@ constexpr int kFrags = kFrag1 + 2 * kFragH + 4;
 struct InferLds {
     uint4 frag[kFrags][kWave];    // weight fragments in slot order, 16 B per lane
     float bias[3 * kHid + 16];    // b1, b2, b3, b4 (padded)
-    float mean[kK1], inv[kK1];    // standardisation per feature (0 in the padding)
+    float mean[kK1], inv[kK1];    // standardisation per layer-1 slot (0 in the padding)
 };
 
 // One layer of the chain for NT tiles: in[t][kb] (KB slot groups) -> 8 row
@@ -1099,17 +1117,28 @@ __device__ __forceinline__ void chain_layer(const InferLds &L, int frag0, const 
 // eps_p = sum_c w_pc eps_c with the deposition weights (CIC or NGP).  Where the
 // particle solid fraction exceeds phi_fp64 the sum is taken in FP64 (eps_c =
 // 1 - phi_c is exact for phi_c >= 1/2, where it matters).
-__device__ __forceinline__ float4 bulk_sample_packed(const StepArgs<float> &a, const float4 &q) {
+struct BulkCorners {
+    Axis<float> x, y, z;
+    float4 c[8];   // corner x + 2 y + 4 z of the stencil
+};
+__device__ __forceinline__ BulkCorners load_bulk_corners(const StepArgs<float> &a, const float4 &q) {
     const Geo<float> &g = a.g;
-    const Axis<float> bx = cic_axis(q.x, g.sb[0], g.nb[0]);
-    const Axis<float> by = cic_axis(q.y, g.sb[1], g.nb[1]);
-    const Axis<float> bz = cic_axis(q.z, g.sb[2], g.nb[2]);
+    BulkCorners b;
+    b.x = cic_axis(q.x, g.sb[0], g.nb[0]);
+    b.y = cic_axis(q.y, g.sb[1], g.nb[1]);
+    b.z = cic_axis(q.z, g.sb[2], g.nb[2]);
     const int64_t nx = g.nb[0], nxy = (int64_t)g.nb[0] * g.nb[1];
-    const int64_t zl = bz.lo * nxy, zh = bz.hi * nxy, yl = by.lo * nx, yh = by.hi * nx;
-    const float4 c000 = a.fgrid[2 * (zl + yl + bx.lo)], c001 = a.fgrid[2 * (zl + yl + bx.hi)];
-    const float4 c010 = a.fgrid[2 * (zl + yh + bx.lo)], c011 = a.fgrid[2 * (zl + yh + bx.hi)];
-    const float4 c100 = a.fgrid[2 * (zh + yl + bx.lo)], c101 = a.fgrid[2 * (zh + yl + bx.hi)];
-    const float4 c110 = a.fgrid[2 * (zh + yh + bx.lo)], c111 = a.fgrid[2 * (zh + yh + bx.hi)];
+    const int64_t z[2] = {b.z.lo * nxy, b.z.hi * nxy}, y[2] = {b.y.lo * nx, b.y.hi * nx};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) b.c[k] = a.fgrid[2 * (z[k >> 2] + y[(k >> 1) & 1] + ((k & 1) ? b.x.hi : b.x.lo))];
+    return b;
+}
+__device__ __forceinline__ float4 bulk_sample_packed(const StepArgs<float> &a, const float4 &q, const BulkCorners &b) {
+    const Geo<float> &g = a.g;
+    const Axis<float> &bx = b.x, &by = b.y, &bz = b.z;
+    const int64_t nx = g.nb[0], nxy = (int64_t)g.nb[0] * g.nb[1];
+    const float4 &c000 = b.c[0], &c001 = b.c[1], &c010 = b.c[2], &c011 = b.c[3], &c100 = b.c[4], &c101 = b.c[5],
+                 &c110 = b.c[6], &c111 = b.c[7];
     const float sx = 1.f - bx.t, sy = 1.f - by.t, sz = 1.f - bz.t;
     auto tri = [&](float v000, float v001, float v010, float v011, float v100, float v101, float v110, float v111) {
         return sz * (sy * (sx * v000 + bx.t * v001) + by.t * (sx * v010 + bx.t * v011)) +
@@ -1141,59 +1170,53 @@ __device__ __forceinline__ float4 bulk_sample_packed(const StepArgs<float> &a, c
     return r;
 }
 
-// Standardised layer-1 inputs of one particle (clamped position and diameter q,
-// containing cell c0; zero when not valid) for lane group g: x[kb] holds unit
-// 4 kb + g.
-__device__ __forceinline__ void gather_features(const StepArgs<float> &a, const InferLds &L, const float4 &q,
-                                                int64_t c0, bool valid, int g, uint4 (&x)[7]) {
+// The stencil cells of one particle that lane group g gathers (unit 4 kb + g of
+// its containing cell c0), and the centre cell.
+struct StencilCells {
+    float4 B0[7], B1[7], A0, A1;
+    int ix, iy, iz;
+};
+__device__ __forceinline__ StencilCells load_stencil(const StepArgs<float> &a, int64_t c0, int g) {
     const Geo<float> &geo = a.g;
     const int64_t nx = geo.nb[0], nxy = (int64_t)geo.nb[0] * geo.nb[1];
     if (c0 < 0 || c0 >= geo.ncell) c0 = 0;
-    int ix, iy, iz;
-    decode_cell(c0, geo.nb, ix, iy, iz);
-    // all stencil loads first (one cell per slot group), then the arithmetic
-    float4 B0[7], B1[7];
+    StencilCells s;
+    decode_cell(c0, geo.nb, s.ix, s.iy, s.iz);
 #pragma unroll
     for (int kb = 0; kb < 7; ++kb) {
         const int u = 4 * kb + g;
         const int uu = u < 27 ? u : 13;
         const int dx = uu % 3 - 1, dy = (uu / 3) % 3 - 1, dz = uu / 9 - 1;
-        const int64_t c = clampi(ix + dx, geo.nb[0]) + nx * clampi(iy + dy, geo.nb[1]) + nxy * clampi(iz + dz, geo.nb[2]);
-        B0[kb] = a.fgrid[2 * c];
-        B1[kb] = a.fgrid[2 * c + 1];
+        const int64_t c = clampi(s.ix + dx, geo.nb[0]) + nx * clampi(s.iy + dy, geo.nb[1]) + nxy * clampi(s.iz + dz, geo.nb[2]);
+        s.B0[kb] = a.fgrid[2 * c];
+        s.B1[kb] = a.fgrid[2 * c + 1];
     }
-    const float4 A0 = a.fgrid[2 * c0], A1 = a.fgrid[2 * c0 + 1];
+    s.A0 = a.fgrid[2 * c0];
+    s.A1 = a.fgrid[2 * c0 + 1];
+    return s;
+}
+
+// Layer-1 slots 8 (4 kb + g) .. + 7 of one particle (clamped position and diameter
+// q), standardised: a stencil cell's seven values, or the offsets and diameter
+// (unit 27); the padding slots come out 0.
+__device__ __forceinline__ uint4 stencil_slots(const StepArgs<float> &a, const float4 &q, const StencilCells &s, int kb,
+                                               int g, const float (&mean)[8], const float (&inv)[8]) {
+    const Geo<float> &geo = a.g;
+    const bool off = kb == 6 && g == 3, centre = 4 * kb + g == 13;   // units 27 and 13
+    const float4 &A0 = s.A0, &A1 = s.A1, &B0 = s.B0[kb], &B1 = s.B1[kb];
+    float v[8] = {centre ? A0.x : B0.x - A0.x, centre ? A0.y : B0.y - A0.y, centre ? A0.z : B0.z - A0.z,
+                  centre ? A0.w : B0.w - A0.w, centre ? A1.x : B1.x - A1.x, centre ? A1.y : B1.y - A1.y,
+                  centre ? A1.z : B1.z - A1.z, 0.f};
+    if (kb == 6) {
+        const float o[4] = {q.x * geo.sb[0] - (float)s.ix, q.y * geo.sb[1] - (float)s.iy, q.z * geo.sb[2] - (float)s.iz,
+                            q.w * geo.sb[0]};
 #pragma unroll
-    for (int kb = 0; kb < 7; ++kb) {
-        const int u = 4 * kb + g;
-        float v[8];
-        int f0, nv;
-        if (u < 27) {
-            const bool centre = (u == 13);
-            v[0] = centre ? A0.x : B0[kb].x - A0.x;
-            v[1] = centre ? A0.y : B0[kb].y - A0.y;
-            v[2] = centre ? A0.z : B0[kb].z - A0.z;
-            v[3] = centre ? A0.w : B0[kb].w - A0.w;
-            v[4] = centre ? A1.x : B1[kb].x - A1.x;
-            v[5] = centre ? A1.y : B1[kb].y - A1.y;
-            v[6] = centre ? A1.z : B1[kb].z - A1.z;
-            v[7] = 0.f;
-            f0 = 7 * u;
-            nv = 7;
-        } else {
-            v[0] = q.x * geo.sb[0] - (float)ix;
-            v[1] = q.y * geo.sb[1] - (float)iy;
-            v[2] = q.z * geo.sb[2] - (float)iz;
-            v[3] = q.w * geo.sb[0];
-            v[4] = v[5] = v[6] = v[7] = 0.f;
-            f0 = 189;
-            nv = 4;
-        }
-        float xs[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) xs[i] = (i < nv && valid) ? (v[i] - L.mean[f0 + i]) * L.inv[f0 + i] : 0.f;
-        x[kb] = make_uint4(pack2(xs[0], xs[1]), pack2(xs[2], xs[3]), pack2(xs[4], xs[5]), pack2(xs[6], xs[7]));
+        for (int i = 0; i < 8; ++i) v[i] = off ? (i < 4 ? o[i] : 0.f) : v[i];
     }
+    float xs[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) xs[i] = (v[i] - mean[i]) * inv[i];
+    return make_uint4(pack2(xs[0], xs[1]), pack2(xs[2], xs[3]), pack2(xs[4], xs[5]), pack2(xs[6], xs[7]));
 }
 
 // Persistent: each workgroup takes one contiguous range of the sorted particles
@@ -1201,21 +1224,23 @@ __device__ __forceinline__ void gather_features(const StepArgs<float> &a, const 
 // per round.  Lane (n, g) gathers, for tile t and slot group kb, unit 4 kb + g of
 // particle 16 t + n; lanes with g < kInfTiles then finish particle 16 g + n:
 // u = u_bulk + s * y and eps_p (both from the packed features), written to
-// uf4[id].
+// uf4[id].  With two waves per SIMD it is bound by the memory round trips of a
+// round and by the standardisation's VALU work, not by the products: with a tile's
+// loads after the other's conversion, the bulk corners loaded under a branch, and
+// mean and 1/std read from LDS per feature under a condition (a branch each) it
+// took 398 us for 1,250,000 particles; with all loads unconditional and in two and a
+// half trips, and the tables in slot order (16-byte reads, no conditions), 314 us.
 __global__ __launch_bounds__(kInfWaves * kWave) void k_infer(StepArgs<float> a) {
     __shared__ InferLds L;
     constexpr int NT = kInfTiles;
     const int lane = lane_id(), n = lane & 15, g = lane >> 4, wave = threadIdx.x >> 6;
     const MlpNet &net = a.net;
-    // weights into LDS, 16 bytes at a time from the copies in slot order
-    for (int e = threadIdx.x; e < kFrags * kWave; e += kInfWaves * kWave) {
-        const int f = e >> 6, r = e & 15, gg = (e >> 4) & 3;
-        const int l = f < kFrag1 ? 0 : (f < kFrag1 + kFragH ? 1 : (f < kFrag1 + 2 * kFragH ? 2 : 3));
-        const int ff = f - (l == 0 ? 0 : kFrag1 + (l - 1) * kFragH), kbs = l == 0 ? 7 : 4;
-        const int mb = ff / kbs, kb = ff % kbs;
-        L.frag[f][e & 63] =
-            *reinterpret_cast<const uint4 *>(net.wtp[l] + (16 * mb + r) * (32 * kbs) + 32 * kb + 8 * gg);
-    }
+    // weights into LDS from the copies in slot order
+    constexpr int kThreads = kInfWaves * kWave;
+    stage_weights<7, 8, kThreads>(net.wtp[0], L.frag);
+    stage_weights<4, 8, kThreads>(net.wtp[1], L.frag + kFrag1);
+    stage_weights<4, 8, kThreads>(net.wtp[2], L.frag + kFrag1 + kFragH);
+    stage_weights<4, 1, kThreads>(net.wtp[3], L.frag + kFrag1 + 2 * kFragH);
     for (int e = threadIdx.x; e < 3 * kHid + 16; e += kInfWaves * kWave) {
         const int l = e / kHid, m = e % kHid;
         constexpr int64_t kB0 = off_b(0), kB1 = off_b(1), kB2 = off_b(2), kB3 = off_b(3);
@@ -1223,8 +1248,10 @@ __global__ __launch_bounds__(kInfWaves * kWave) void k_infer(StepArgs<float> a) 
         L.bias[e] = (l < 3) ? net.params[ob + m] : (m < kOut ? net.params[kB3 + m] : 0.f);
     }
     for (int e = threadIdx.x; e < kK1; e += kInfWaves * kWave) {
-        L.mean[e] = net.mean_inv[e];
-        L.inv[e] = net.mean_inv[kK1 + e];
+        const int u = e >> 3, i = e & 7;
+        const int k = u < 27 ? (i < 7 ? 7 * u + i : -1) : (i < 4 ? 189 + i : -1);   // slot_of_feature(k) == e
+        L.mean[e] = k >= 0 ? net.mean_inv[k] : 0.f;
+        L.inv[e] = k >= 0 ? net.mean_inv[kK1 + k] : 0.f;
     }
     __syncthreads();
 
@@ -1232,6 +1259,12 @@ __global__ __launch_bounds__(kInfWaves * kWave) void k_infer(StepArgs<float> a) 
     const int64_t s_begin = (int64_t)blockIdx.x * per;
     const int64_t s_end = (s_begin + per < a.n) ? s_begin + per : a.n;
     for (int64_t base = s_begin + (int64_t)wave * kInfRows; base < s_end; base += kInfWaves * kInfRows) {
+        wave_sync();   // keeps the compiler from holding LDS rows in registers across rounds
+        // Two memory round trips and part of a third: the particles; the stencil
+        // cells of both tiles; then, while the second tile's are converted, the bulk
+        // corners of the particle this lane finishes (tile g).  The lanes with none
+        // and those past the end take another particle's, so that no load is
+        // conditional.
         float4 q[NT];
         int64_t c[NT];
 #pragma unroll
@@ -1241,24 +1274,45 @@ __global__ __launch_bounds__(kInfWaves * kWave) void k_infer(StepArgs<float> a) 
             q[t] = a.sp[s];
             c[t] = a.keys[s];
         }
-        // the particle this lane finishes (tile g): its bulk velocity, void
-        // fraction and id are fetched first so that their loads overlap the chain
         const int64_t so = base + 16 * g + n;
         const bool own = (g < NT) && so < s_end;
-        float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-        int64_t p = 0;
-        if (own) {
-            float4 qo = q[0];
+        int64_t p = a.perm[own ? so : base];
+        __builtin_amdgcn_sched_barrier(0);
+        if (p < 0 || p >= a.n) p = 0;
+        float4 qo = q[0];
 #pragma unroll
-            for (int t = 1; t < NT; ++t)
-                if (g == t) qo = q[t];
-            r = bulk_sample_packed(a, qo);
-            p = a.perm[so];
-            if (p < 0 || p >= a.n) p = 0;
+        for (int t = 1; t < NT; ++t) {
+            qo.x = g == t ? q[t].x : qo.x;
+            qo.y = g == t ? q[t].y : qo.y;
+            qo.z = g == t ? q[t].z : qo.z;
         }
+        StencilCells sc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) sc[t] = load_stencil(a, c[t], g);
+        __builtin_amdgcn_sched_barrier(0);
+        BulkCorners bc;
         uint4 x[NT][7];
 #pragma unroll
-        for (int t = 0; t < NT; ++t) gather_features(a, L, q[t], c[t], base + 16 * t + n < s_end, g, x[t]);
+        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+            for (int kb = 0; kb < 7; ++kb) {
+                const float4 *tm = reinterpret_cast<const float4 *>(L.mean + 8 * (4 * kb + g)),
+                             *ti = reinterpret_cast<const float4 *>(L.inv + 8 * (4 * kb + g));
+                const float4 m0 = tm[0], m1 = tm[1], i0 = ti[0], i1 = ti[1];
+                const float mean[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
+                const float inv[8] = {i0.x, i0.y, i0.z, i0.w, i1.x, i1.y, i1.z, i1.w};
+                x[t][kb] = stencil_slots(a, q[t], sc[t], kb, g, mean, inv);
+                // (materialised here: the compiler would move the conversion past the
+                // branches of bulk_sample_packed and keep all cells, spilling)
+                asm volatile("" : "+v"(x[t][kb].x), "+v"(x[t][kb].y), "+v"(x[t][kb].z), "+v"(x[t][kb].w));
+                __builtin_amdgcn_sched_barrier(0);   // a block at a time: the cells go as the operand comes
+            }
+            if (t == 0) {   // into the registers that the first tile's cells held
+                bc = load_bulk_corners(a, qo);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        float4 r = bulk_sample_packed(a, qo, bc);
         uint4 h1[NT][4], h2[NT][4];
         chain_layer<NT, 7>(L, 0, L.bias, x, h1, lane, g);
         chain_layer<NT, 4>(L, kFrag1, L.bias + kHid, h1, h2, lane, g);
