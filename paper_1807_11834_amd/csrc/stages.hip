@@ -344,19 +344,28 @@ __device__ __forceinline__ T trilin_alpha8(const T *__restrict__ alpha8, const A
 }
 
 // Restriction of the velocity with the fine-grid lookup, tiled in bricks of
-// 8 x 4 x 2 bulk cells.  Filling a brick: 256 threads, four per cell (one per
-// fine child plane z), each loads its plane's r x r rows of u, v, w, stores them
-// in LDS and sums its plane (compensated); the four plane sums are combined in
-// order through cross-lane reads (the pressure is restricted by k_restrict
-// before this kernel).  The brick's particles (8 rows of up to 8 cells,
-// contiguous in the sorted order, flattened over the threads) then take their
-// trilinear fine velocity from LDS when all eight fine nodes lie in the brick
-// (from global memory when the stencil crosses a brick face) and their void
-// fraction from a haloed copy of phi in LDS.  The brick is 8r fine cells wide
+// 8 x 4 x 2 bulk cells.  Filling a brick: four threads per cell (one per fine
+// child plane z) for u and v and four for w, each loads its plane's r x r rows of
+// a component, stores them in LDS and sums its plane (compensated); the four
+// plane sums are combined in order through cross-lane reads (the pressure is
+// restricted by k_restrict before this kernel).  The brick's particles (8 rows of
+// up to 8 cells, contiguous in the sorted order, flattened over the threads) then
+// take their trilinear fine velocity from LDS when all eight fine nodes lie in
+// the brick (from global memory when the stencil crosses a brick face) and their
+// void fraction from a haloed copy of phi in LDS.  The brick is 8r fine cells wide
 // along x (one 128-byte line per row for r = 4 in FP32).
-// One workgroup per brick: fill, then the particles.
+// One workgroup per brick: fill, then the particles.  In a packed bed of 512 x 512
+// x 1024 fine cells and 10 million particles the fill alone takes 620 of the 1000
+// us (3.2 GB), the scattered stores of the results 200 and the particles at brick
+// faces 90.  Lanes along x in the fill (rather than four planes of a cell next to
+// each other, whose LDS stores conflict): 1042 -> 1016; 512 threads instead of
+// 256, so that a brick's particles (a few hundred) are one batch of one particle
+// per thread: -> 1001, and 95 -> 90 for 256^3 cells with 2 million.  (Loading the
+// first particles before the barrier: 1039; bricks ordered in columns of two to
+// eight along z, or dealt to the XCDs in rows or layers: no faster.)
 constexpr int kBrickX = 8, kBrickY = 4, kBrickZ = 2;
-constexpr int kBrickThreads = 4 * kBrickX * kBrickY * kBrickZ;
+constexpr int kBrickFill = 4 * kBrickX * kBrickY * kBrickZ;   // threads that fill one component
+constexpr int kBrickThreads = 2 * kBrickFill;
 constexpr int kBrickRows = kBrickY * kBrickZ;                                     // particle rows of a brick
 constexpr int kBrickHalo = (kBrickX + 2) * (kBrickY + 2) * (kBrickZ + 2);         // phi with a one-cell halo
 
@@ -377,16 +386,19 @@ template <typename T> struct BrickGrid {
     }
 };
 
-// Fill the brick at (ox, oy, oz) into L and (if write_u) write its U; thread t in
-// [0, 256).
+// Fill the brick at (ox, oy, oz) into L and (if write_u) write its U; thread t of
+// kBrickThreads: the first half u and v, the other w, phi and the particle rows.
 template <typename T, int R, int SM>
 __device__ __forceinline__ void brick_fill(const StepArgs<T> &a, BrickLds<T, R> &L, int t, int ox, int oy, int oz,
                                            bool write_u) {
     constexpr int HX = kBrickX + 2, HY = kBrickY + 2;
     const Geo<T> &g = a.g;
     const int lane = t % kWave;
-    const int cl = t >> 2, rz = t & 3;   // cell of the brick, fine child plane
-    const int lx = cl % kBrickX, ly = (cl / kBrickX) % kBrickY, lz = cl / (kBrickX * kBrickY);
+    const bool upper = t >= kBrickFill;   // a wave is in one half
+    t %= kBrickFill;
+    // cell of the brick and fine child plane: the eight lanes along x read and
+    // write a contiguous row
+    const int lx = t % kBrickX, rz = (t / kBrickX) % 4, ly = (t / (4 * kBrickX)) % kBrickY, lz = t / (4 * kBrickX * kBrickY);
     const int cx = ox + lx, cy = oy + ly, cz = oz + lz;
     const bool inside = cx < g.nb[0] && cy < g.nb[1] && cz < g.nb[2];
     const int64_t nx = g.nb[0], nxy = (int64_t)g.nb[0] * g.nb[1];
@@ -395,9 +407,9 @@ __device__ __forceinline__ void brick_fill(const StepArgs<T> &a, BrickLds<T, R> 
     // particle rows (their first sorted position and count), phi with its halo
     // (indices clamped at the walls) and the fine rows, so that a workgroup
     // waits for one memory round trip instead of three.
-    static_assert(kBrickHalo <= kBrickThreads, "one halo value per thread");
+    static_assert(kBrickHalo <= kBrickFill, "one halo value per thread");
     int32_t seg0 = 0, seg1 = 0;
-    if (t < kBrickRows) {
+    if (upper && t < kBrickRows) {
         const int wx = (ox + kBrickX < g.nb[0]) ? kBrickX : g.nb[0] - ox;
         const int ry = oy + t % kBrickY, rzz = oz + t / kBrickY;
         if (ry < g.nb[1] && rzz < g.nb[2]) {
@@ -408,48 +420,53 @@ __device__ __forceinline__ void brick_fill(const StepArgs<T> &a, BrickLds<T, R> 
     }
     const int hx = t % HX, hy = (t / HX) % HY, hz = t / (HX * HY);
     T ph = T(0);
-    if (t < kBrickHalo) {
+    if (upper && t < kBrickHalo) {
         const int gx = clampi(ox - 1 + hx, g.nb[0]), gy = clampi(oy - 1 + hy, g.nb[1]), gz = clampi(oz - 1 + hz, g.nb[2]);
         ph = a.phi[gx + nx * gy + nxy * gz];
     }
     const bool work = inside && rz < R;
     const int64_t base = ((int64_t)R * cz + rz) * nfxy + (int64_t)R * cy * nfx + (int64_t)R * cx;
     const T inv = T(1) / T(R * R * R);
-    Row<T, R> rows[3][R];
-    if (work) {
+    Row<T, R> rows[2][R];
 #pragma unroll
-        for (int f = 0; f < 3; ++f)
+    for (int i = 0; i < 2; ++i) {
+        if (upper && i == 1) break;
+        const T *__restrict__ q = (upper ? a.fine[2] : a.fine[i]) + base;
+        if (work) {
 #pragma unroll
-            for (int ry = 0; ry < R; ++ry) rows[f][ry] = load_row<T, R>(a.fine[f] + base + ry * nfx);
+            for (int ry = 0; ry < R; ++ry) rows[i][ry] = load_row<T, R>(q + ry * nfx);
+        }
     }
-    if (t < kBrickRows) {
+    if (upper && t < kBrickRows) {
         const int32_t b0 = seg_clamp(seg0, a.n);
         L.beg[t] = b0;
         L.cnt[t] = seg_clamp(seg1, a.n) - b0;
     }
-    if (t < kBrickHalo) L.sphi[hz][hy][hx] = ph;
+    if (upper && t < kBrickHalo) L.sphi[hz][hy][hx] = ph;
 #pragma unroll
-    for (int f = 0; f < 3; ++f) {
+    for (int i = 0; i < 2; ++i) {
+        if (upper && i == 1) break;
+        const int f = upper ? 2 : i;
         ChildSum<T, SM> plane;
         if (work) {
 #pragma unroll
             for (int ry = 0; ry < R; ++ry)
 #pragma unroll
-                for (int rx = 0; rx < R; ++rx) plane.add(rows[f][ry].v[rx]);
+                for (int rx = 0; rx < R; ++rx) plane.add(rows[i][ry].v[rx]);
 #pragma unroll
             for (int ry = 0; ry < R; ++ry)
 #pragma unroll
-                for (int rx = 0; rx < R; ++rx) L.sv[f][lz * R + rz][ly * R + ry][lx * R + rx] = rows[f][ry].v[rx];
+                for (int rx = 0; rx < R; ++rx) L.sv[f][lz * R + rz][ly * R + ry][lx * R + rx] = rows[i][ry].v[rx];
         }
         // the planes of this cell in order (with a Kahan sum, s_0, -c_0, s_1,
         // ...), read from the cell's four lanes; the plane-0 lane writes the
         // average
         ChildSum<T, SM> acc;
-        const int l0 = lane & ~3;
+        const int l0 = lane - kBrickX * rz;
 #pragma unroll
         for (int k = 0; k < R; ++k) {
-            const auto sk = __shfl(plane.acc.s, l0 + k, kWave);
-            const auto ck = ChildSum<T, SM>::kComp ? __shfl(plane.acc.c, l0 + k, kWave) : plane.acc.c;
+            const auto sk = __shfl(plane.acc.s, l0 + kBrickX * k, kWave);
+            const auto ck = ChildSum<T, SM>::kComp ? __shfl(plane.acc.c, l0 + kBrickX * k, kWave) : plane.acc.c;
             acc.add_plane(sk, ck);
         }
         if (write_u && inside && rz == 0) a.U[f * g.ncell + (cx + nx * cy + nxy * cz)] = acc.hi(inv);
@@ -457,8 +474,7 @@ __device__ __forceinline__ void brick_fill(const StepArgs<T> &a, BrickLds<T, R> 
 }
 
 // The particles of the filled brick at (ox, oy, oz): thread t of nt, batches
-// first, first + step, ... of kBrickBatch particles per thread.
-constexpr int kBrickBatch = 2;
+// first, first + step, ... of one particle per thread.
 template <typename T, int R>
 __device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const BrickLds<T, R> &L, int t, int nt, int first,
                                                 int step, int ox, int oy, int oz) {
@@ -470,88 +486,71 @@ __device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const Bric
     for (int r = 0; r < kBrickRows; ++r) pre[r + 1] = pre[r] + L.cnt[r];
     const int total = pre[kBrickRows];
     const int fx0 = ox * R, fy0 = oy * R, fz0 = oz * R;
-    // up to kPB particles per thread at a time: their loads are issued together
-    constexpr int kPB = kBrickBatch;
-    for (int j0 = t + first * kPB * nt; j0 < total; j0 += step * kPB * nt) {
-        vec4<T> qs[kPB];
-        int64_t ps[kPB];
+    for (int j = t + first * nt; j < total; j += step * nt) {
+        int r = 0;
 #pragma unroll
-        for (int k = 0; k < kPB; ++k) {
-            const int j = j0 + k * nt;
-            int64_t i = L.beg[0];
-            if (j < total) {
-                int r = 0;
+        for (int q = 1; q < kBrickRows; ++q) r += (pre[q] <= j) ? 1 : 0;
+        const int64_t i = L.beg[r] + (j - pre[r]);
+        const vec4<T> q = a.sp[i];
+        int64_t p = a.perm[i];
+        if (p < 0 || p >= a.n) p = 0;   // perm is a permutation of [0, n)
+        vec4<T> s;
+        // fine trilinear velocity: from LDS when the eight nodes lie in the brick
+        const Axis<T> ax = cic_axis(q.x, g.sf[0], g.nf[0]);
+        const Axis<T> ay = cic_axis(q.y, g.sf[1], g.nf[1]);
+        const Axis<T> az = cic_axis(q.z, g.sf[2], g.nf[2]);
+        const int xl = ax.lo - fx0, xh = ax.hi - fx0, yl = ay.lo - fy0, yh = ay.hi - fy0, zl = az.lo - fz0,
+                  zh = az.hi - fz0;
+        if (xl >= 0 && xh < FX && yl >= 0 && yh < FY && zl >= 0 && zh < FZ) {
+            const T tx = ax.t, ty = ay.t, tz = az.t, sx = T(1) - tx, sy = T(1) - ty, sz = T(1) - tz;
+            T u[3];
 #pragma unroll
-                for (int q = 1; q < kBrickRows; ++q) r += (pre[q] <= j) ? 1 : 0;
-                i = L.beg[r] + (j - pre[r]);
+            for (int f = 0; f < 3; ++f) {
+                // rounded as written (see trilin_rows; the last sum of w in the other order)
+                auto row = [&](int z, int y) { return dfma(sx, L.sv[f][z][y][xl], tx * L.sv[f][z][y][xh]); };
+                const T e0 = dfma(sy, row(zl, yl), ty * row(zl, yh));
+                const T e1 = dfma(sy, row(zh, yl), ty * row(zh, yh));
+                u[f] = f < 2 ? dfma(sz, e0, tz * e1) : dfma(tz, e1, sz * e0);
             }
-            qs[k] = a.sp[i];
-            ps[k] = a.perm[i];
+            s.x = u[0];
+            s.y = u[1];
+            s.z = u[2];
+        } else {
+            fine_velocity(q, a, s.x, s.y, s.z);
         }
-#pragma unroll
-        for (int k = 0; k < kPB; ++k) {
-            if (j0 + k * nt >= total) break;
-            const vec4<T> q = qs[k];
-            int64_t p = ps[k];
-            if (p < 0 || p >= a.n) p = 0;   // perm is a permutation of [0, n)
-            vec4<T> s;
-            // fine trilinear velocity: from LDS when the eight nodes lie in the brick
-            const Axis<T> ax = cic_axis(q.x, g.sf[0], g.nf[0]);
-            const Axis<T> ay = cic_axis(q.y, g.sf[1], g.nf[1]);
-            const Axis<T> az = cic_axis(q.z, g.sf[2], g.nf[2]);
-            const int xl = ax.lo - fx0, xh = ax.hi - fx0, yl = ay.lo - fy0, yh = ay.hi - fy0, zl = az.lo - fz0,
-                      zh = az.hi - fz0;
-            if (xl >= 0 && xh < FX && yl >= 0 && yh < FY && zl >= 0 && zh < FZ) {
-                const T tx = ax.t, ty = ay.t, tz = az.t, sx = T(1) - tx, sy = T(1) - ty, sz = T(1) - tz;
-                T u[3];
-#pragma unroll
-                for (int f = 0; f < 3; ++f) {
-                    // rounded as written (see trilin_rows; the last sum of w in the other order)
-                    auto row = [&](int z, int y) { return dfma(sx, L.sv[f][z][y][xl], tx * L.sv[f][z][y][xh]); };
-                    const T e0 = dfma(sy, row(zl, yl), ty * row(zl, yh));
-                    const T e1 = dfma(sy, row(zh, yl), ty * row(zh, yh));
-                    u[f] = f < 2 ? dfma(sz, e0, tz * e1) : dfma(tz, e1, sz * e0);
-                }
-                s.x = u[0];
-                s.y = u[1];
-                s.z = u[2];
+        // void fraction at the particle from the haloed phi (its stencil is the
+        // containing cell and a neighbour, always inside the halo)
+        if (a.cic) {
+            const Axis<T> bx = cic_axis_at(node_units_rounded(q.x, g.sb[0]), g.nb[0]);
+            const Axis<T> by = cic_axis(q.y, g.sb[1], g.nb[1]);
+            const Axis<T> bz = cic_axis(q.z, g.sb[2], g.nb[2]);
+            const int hxl = bx.lo - ox + 1, hxh = bx.hi - ox + 1, hyl = by.lo - oy + 1, hyh = by.hi - oy + 1,
+                      hzl = bz.lo - oz + 1, hzh = bz.hi - oz + 1;
+            const T f000 = L.sphi[hzl][hyl][hxl], f001 = L.sphi[hzl][hyl][hxh], f010 = L.sphi[hzl][hyh][hxl],
+                    f011 = L.sphi[hzl][hyh][hxh], f100 = L.sphi[hzh][hyl][hxl], f101 = L.sphi[hzh][hyl][hxh],
+                    f110 = L.sphi[hzh][hyh][hxl], f111 = L.sphi[hzh][hyh][hxh];
+            const T sx = T(1) - bx.t, sy = T(1) - by.t, sz = T(1) - bz.t;
+            const T phi_p = sz * (sy * (sx * f000 + bx.t * f001) + by.t * (sx * f010 + bx.t * f011)) +
+                            bz.t * (sy * (sx * f100 + bx.t * f101) + by.t * (sx * f110 + bx.t * f111));
+            if (std::is_same<T, float>::value && phi_p > (T)a.phi_fp64) {
+                // FP64 weights from the same positions; the cancellation in 1 - phi is exact
+                const double gx = (double)q.x * (double)g.sb[0] - 0.5, gy = (double)q.y * (double)g.sb[1] - 0.5,
+                             gz = (double)q.z * (double)g.sb[2] - 0.5;
+                const double tx = gx - floor(gx), ty = gy - floor(gy), tz = gz - floor(gz);
+                const double ux = 1.0 - tx, uy = 1.0 - ty, uz = 1.0 - tz;
+                const double ph =
+                    uz * (uy * (ux * (double)f000 + tx * (double)f001) + ty * (ux * (double)f010 + tx * (double)f011)) +
+                    tz * (uy * (ux * (double)f100 + tx * (double)f101) + ty * (ux * (double)f110 + tx * (double)f111));
+                s.w = (T)(1.0 - ph);
             } else {
-                fine_velocity(q, a, s.x, s.y, s.z);
+                s.w = T(1) - phi_p;
             }
-            // void fraction at the particle from the haloed phi (its stencil is the
-            // containing cell and a neighbour, always inside the halo)
-            if (a.cic) {
-                const Axis<T> bx = cic_axis_at(node_units_rounded(q.x, g.sb[0]), g.nb[0]);
-                const Axis<T> by = cic_axis(q.y, g.sb[1], g.nb[1]);
-                const Axis<T> bz = cic_axis(q.z, g.sb[2], g.nb[2]);
-                const int hxl = bx.lo - ox + 1, hxh = bx.hi - ox + 1, hyl = by.lo - oy + 1, hyh = by.hi - oy + 1,
-                          hzl = bz.lo - oz + 1, hzh = bz.hi - oz + 1;
-                const T f000 = L.sphi[hzl][hyl][hxl], f001 = L.sphi[hzl][hyl][hxh], f010 = L.sphi[hzl][hyh][hxl],
-                        f011 = L.sphi[hzl][hyh][hxh], f100 = L.sphi[hzh][hyl][hxl], f101 = L.sphi[hzh][hyl][hxh],
-                        f110 = L.sphi[hzh][hyh][hxl], f111 = L.sphi[hzh][hyh][hxh];
-                const T sx = T(1) - bx.t, sy = T(1) - by.t, sz = T(1) - bz.t;
-                const T phi_p = sz * (sy * (sx * f000 + bx.t * f001) + by.t * (sx * f010 + bx.t * f011)) +
-                                bz.t * (sy * (sx * f100 + bx.t * f101) + by.t * (sx * f110 + bx.t * f111));
-                if (std::is_same<T, float>::value && phi_p > (T)a.phi_fp64) {
-                    // FP64 weights from the same positions; the cancellation in 1 - phi is exact
-                    const double gx = (double)q.x * (double)g.sb[0] - 0.5, gy = (double)q.y * (double)g.sb[1] - 0.5,
-                                 gz = (double)q.z * (double)g.sb[2] - 0.5;
-                    const double tx = gx - floor(gx), ty = gy - floor(gy), tz = gz - floor(gz);
-                    const double ux = 1.0 - tx, uy = 1.0 - ty, uz = 1.0 - tz;
-                    const double ph =
-                        uz * (uy * (ux * (double)f000 + tx * (double)f001) + ty * (ux * (double)f010 + tx * (double)f011)) +
-                        tz * (uy * (ux * (double)f100 + tx * (double)f101) + ty * (ux * (double)f110 + tx * (double)f111));
-                    s.w = (T)(1.0 - ph);
-                } else {
-                    s.w = T(1) - phi_p;
-                }
-            } else {
-                const int ix = cell_axis(q.x, g.sb[0], g.nb[0]), iy = cell_axis(q.y, g.sb[1], g.nb[1]),
-                          iz = cell_axis(q.z, g.sb[2], g.nb[2]);
-                s.w = T(1) - L.sphi[iz - oz + 1][iy - oy + 1][ix - ox + 1];
-            }
-            a.uf4[p] = s;
+        } else {
+            const int ix = cell_axis(q.x, g.sb[0], g.nb[0]), iy = cell_axis(q.y, g.sb[1], g.nb[1]),
+                      iz = cell_axis(q.z, g.sb[2], g.nb[2]);
+            s.w = T(1) - L.sphi[iz - oz + 1][iy - oy + 1][ix - ox + 1];
         }
+        a.uf4[p] = s;
     }
 }
 
@@ -957,7 +956,7 @@ static void launch_grid_stages(const StepArgs<T> &a, hipStream_t st, int phases)
         const BrickGrid<T> bg{(a.g.nb[0] + kBrickX - 1) / kBrickX, (a.g.nb[1] + kBrickY - 1) / kBrickY};
         // bricks alone that fill the chip (two per compute unit) take one workgroup each; fewer share the
         // mean number of particles in batches
-        const int64_t batch = nbk * kBrickBatch * kBrickThreads;
+        const int64_t batch = nbk * kBrickThreads;
         const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(512 / nbk, (a.n + batch - 1) / batch));
         hipLaunchKernelGGL((k_restrict_brick<T, R, SM>), dim3((unsigned)nbk, (unsigned)parts), dim3(kBrickThreads), 0,
                            st, a, bg);
