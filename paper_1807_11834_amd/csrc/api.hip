@@ -129,7 +129,7 @@ static ScratchPlan scratch_plan(const couple_config &c, int64_t nmax, bool tight
     p.bytes[B_PLO] = fsz * ncell;
     const int dep_slots = deposit_group(c.nb) == 1 ? 9 : 4;   // CIC partial slots per cell and component
     p.bytes[B_DEP] = (c.deposit == COUPLE_CIC ? dep_slots * (c.semi_implicit ? 4 : 3) : 1) * fsz * ncell;
-    p.bytes[B_PART] = sizeof(double) * (SL_COUNT * p.part_stride + SL_COUNT * 64);
+    p.bytes[B_PART] = sizeof(double) * SL_COUNT * p.part_stride;
     p.bytes[B_FGRID] = c.vel_source == COUPLE_VEL_MLP ? sizeof(float4) * 2 * ncell : 0;
     p.bytes[B_ALPHA8] = c.vof ? 8 * fsz * ncell : 0;
     return p;

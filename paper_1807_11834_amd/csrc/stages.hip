@@ -896,35 +896,43 @@ struct DiagSpec {
     double scale[SL_COUNT];
 };
 
-// Stage 1: workgroup (slot, chunk) sums a contiguous chunk of the slot's
-// partials (thread t: elements t, t + kBlock, ... of the chunk, in order), then a
-// fixed tree; stage 2: one workgroup per slot combines the kDiagChunks values in
-// order.  Deterministic.
-constexpr int kDiagChunks = 32;
+// One workgroup per slot: thread t takes the partials t, t + kDiagThreads, ... in
+// order, kDiagBatch loads in flight, then a fixed tree.  Deterministic.  Bound by
+// the launch and by one or (39,000 partials of 10 million particles) five memory
+// round trips; a stage of many chunks and one that combines them were two
+// launches (2.8 + 2.5 us of a small step, 4.9 + 4.7 of one of 2 million particles;
+// in one 2.9 and 4.7, and 10.7 for 10 million instead of 9.7 and the gap).
+constexpr int kDiagThreads = 1024, kDiagBatch = 8;
 
-__global__ __launch_bounds__(kBlock) void k_diag1(const double *__restrict__ part, int64_t ps, DiagSpec spec,
-                                                  double *__restrict__ part2) {
-    __shared__ double red[kWavesPerBlock];
-    const int s = blockIdx.x / kDiagChunks, ch = blockIdx.x % kDiagChunks;
-    const bool is_max = (s == SL_MAXPHI);
-    const int nb = spec.nblk[s];
-    const int per = (nb + kDiagChunks - 1) / kDiagChunks;
-    const int j0 = ch * per, j1 = (j0 + per < nb) ? j0 + per : nb;
-    const double *src = part + s * ps;
-    double v = 0.0;
-    for (int j = j0 + threadIdx.x; j < j1; j += kBlock) v = is_max ? fmax(v, src[j]) : v + src[j];
-    const double t = is_max ? block_max(v, red) : block_sum(v, red);
-    if (threadIdx.x == 0) part2[blockIdx.x] = t;
-}
-
-__global__ __launch_bounds__(kWave) void k_diag2(const double *__restrict__ part2, DiagSpec spec,
-                                                 double *__restrict__ diag) {
+__global__ __launch_bounds__(kDiagThreads) void k_diag(const double *__restrict__ part, int64_t ps, DiagSpec spec,
+                                                       double *__restrict__ diag) {
+    __shared__ double red[kDiagThreads / kWave];
     const int s = blockIdx.x;
     const bool is_max = (s == SL_MAXPHI);
+    const int nb = spec.nblk[s];
+    const double *src = part + s * ps;
     double v = 0.0;
-    if (threadIdx.x < kDiagChunks) v = part2[s * kDiagChunks + threadIdx.x];
+    for (int j0 = threadIdx.x; j0 < nb; j0 += kDiagBatch * kDiagThreads) {
+        double x[kDiagBatch];
+#pragma unroll
+        for (int u = 0; u < kDiagBatch; ++u) {
+            const int j = j0 + u * kDiagThreads;
+            x[u] = src[j < nb ? j : nb - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kDiagBatch; ++u) {
+            const double y = j0 + u * kDiagThreads < nb ? x[u] : 0.0;
+            v = is_max ? fmax(v, y) : v + y;
+        }
+    }
     v = is_max ? wave_max(v) : wave_sum(v);
-    if (threadIdx.x == 0) diag[s] = v * spec.scale[s];
+    if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < kDiagThreads / kWave; ++w) t = is_max ? fmax(t, red[w]) : t + red[w];
+        diag[s] = t * spec.scale[s];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1095,10 +1103,7 @@ template <typename T> hipError_t launch_stages(const StepArgs<T> &a, hipStream_t
     }
     if (phases & kPhaseDiag) {
         a.mk->mark("diag", st);
-        double *part2 = a.part + (int64_t)SL_COUNT * a.part_stride;
-        hipLaunchKernelGGL(k_diag1, dim3(SL_COUNT * kDiagChunks), dim3(kBlock), 0, st, a.part, a.part_stride, spec,
-                           part2);
-        hipLaunchKernelGGL(k_diag2, dim3(SL_COUNT), dim3(kWave), 0, st, part2, spec, a.diag);
+        hipLaunchKernelGGL(k_diag, dim3(SL_COUNT), dim3(kDiagThreads), 0, st, a.part, a.part_stride, spec, a.diag);
         a.mk->mark(nullptr, st);
     }
     return hipGetLastError();
