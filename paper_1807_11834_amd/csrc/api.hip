@@ -123,7 +123,7 @@ static ScratchPlan scratch_plan(const couple_config &c, int64_t nmax, bool tight
     for (int64_t b : {pblk, cblk, ntile, mblk, prblk})
         if (b > p.part_stride) p.part_stride = b;
     p.bytes[B_KEYS_A] = p.bytes[B_KEYS_B] = p.bytes[B_VALS_A] = p.bytes[B_VALS_B] = sizeof(uint32_t) * nmax;
-    p.bytes[B_HIST] = sizeof(uint32_t) * 256 * ntile;
+    p.bytes[B_HIST] = std::max(sizeof(uint32_t) * 256 * ntile, tight ? 0 : count_sort_bytes(nmax, ncell));
     p.bytes[B_TOTALS] = sizeof(uint32_t) * 256;
     p.bytes[B_SP] = p.bytes[B_UF4] = 4 * fsz * nmax;
     p.bytes[B_PLO] = fsz * ncell;
@@ -181,6 +181,7 @@ extern "C" int couple_init(const couple_config *cfg, couple_handle **out) {
     const ScratchPlan plan = scratch_plan(*cfg, cfg->max_particles);
     h->part_stride = plan.part_stride;
     h->sort.max_tiles = plan.max_tiles;
+    h->sort.hist_bytes = plan.bytes[B_HIST];
     bool ok = true;
     for (int b = 0; b < B_COUNT && ok; ++b)
         if (plan.bytes[b] > 0 || b < B_FGRID) ok = dev_alloc(buf_slot(h, b), plan.bytes[b]);
@@ -422,6 +423,7 @@ extern "C" int couple_step_noalloc(const couple_config *cfg, const couple_inputs
     h.nfine = h.ncell * cfg->ratio * cfg->ratio * cfg->ratio;
     h.part_stride = plan.part_stride;
     h.sort.max_tiles = plan.max_tiles;
+    h.sort.hist_bytes = plan.bytes[B_HIST];
     size_t off = 0;
     for (int b = 0; b < B_COUNT; ++b) {
         *buf_slot(&h, b) = plan.bytes[b] ? base + off : nullptr;

@@ -33,7 +33,12 @@ struct SortScratch {
     uint32_t *hist;              // [256 * max_tiles]
     uint32_t *totals;            // [256]
     int64_t max_tiles;           // tiles the histograms hold
+    size_t hist_bytes = 0;       // bytes of `hist` that a counting sort may use (0: none)
 };
+
+// Bytes of histograms for which a step of up to nmax particles over ncell cells
+// sorts by counting cells (0: it never does).
+size_t count_sort_bytes(int64_t nmax, int64_t ncell);
 
 // Tiles of a sort of n keys whose histograms hold max_tiles tiles; the fewest
 // and the most that any sort of up to n keys takes (the histograms hold at least
