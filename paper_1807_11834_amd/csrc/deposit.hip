@@ -101,13 +101,16 @@ __device__ __forceinline__ void load_values(int64_t id, const vec4<T> &q, const 
 // ---------------------------------------------------------------------------
 // NGP (containing cell)
 // ---------------------------------------------------------------------------
-// A workgroup takes 64 consecutive cells at a time, whose particles are one run
-// of the sorted order.  The run passes through LDS in chunks, every load of a
+// A workgroup takes up to 64 consecutive cells at a time, whose particles are one
+// run of the sorted order.  The run passes through LDS in chunks, every load of a
 // chunk in flight together; lane (cell) of wave (component) then sums its
 // cell's part of the chunk in canonical order.  One thread per cell that loads
 // and adds particle by particle waits for two dependent loads per particle: 512
 // cells of 20 particles in FP64 took 3 + 12 us (sorted copy, solid fraction)
-// and 19 us (source), on two compute units.
+// and 19 us (source), on two compute units.  In groups of 64 cells they were two
+// chunks of 8 workgroups (10.4 and 10.2 us); in groups of 16, with four of a
+// cell's values read from LDS at a time, 6.6 and 6.1 (a whole step with 127 per
+// cell: 190 -> 84 us).
 // A cell's sum of v, or for the solid fraction of v / V_b: the product rounded
 // before it is widened, otherwise one FMA with the running sum.
 template <typename T, int SM, int MODE> struct NgpSum {
@@ -119,7 +122,10 @@ template <typename T, int SM, int MODE> struct NgpSum {
     }
     __device__ __forceinline__ T value() const { return acc.value(); }
 };
-constexpr int kNgpCells = kWave, kNgpItems = 4, kNgpChunk = kBlock * kNgpItems;
+constexpr int kNgpItems = 4, kNgpChunk = kBlock * kNgpItems, kNgpRead = 4;
+// Cells of a group: one per lane, or sixteen where that leaves less than a
+// workgroup per compute unit (a group's particles then rarely exceed a chunk).
+static int ngp_cells(int64_t ncell) { return ncell < (int64_t)kWave * 256 ? 16 : kWave; }
 
 template <typename T, int SM, int MODE>
 __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restrict__ start,
@@ -128,16 +134,16 @@ __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restric
                                                         const T *__restrict__ drag, int64_t n, Geo<T> g,
                                                         const T *__restrict__ P, const T *__restrict__ Plo,
                                                         T *__restrict__ out, T *__restrict__ out2, T *__restrict__ G,
-                                                        double *__restrict__ part, int64_t ps) {
+                                                        double *__restrict__ part, int64_t ps, int cells) {
     constexpr int NC = DepNc<MODE>::value;
     static_assert(NC <= kWavesPerBlock, "a wave per component");
     __shared__ T val[NC][kNgpChunk];
     const int lane = threadIdx.x % kWave, comp = threadIdx.x / kWave;
     double vsum = 0.0, vmax = 0.0;
-    for (int64_t c0 = (int64_t)blockIdx.x * kNgpCells; c0 < g.ncell; c0 += (int64_t)gridDim.x * kNgpCells) {
+    for (int64_t c0 = (int64_t)blockIdx.x * cells; c0 < g.ncell; c0 += (int64_t)gridDim.x * cells) {
         const int64_t c = c0 + lane;
-        const int64_t c1 = c0 + kNgpCells < g.ncell ? c0 + kNgpCells : g.ncell;
-        const bool mine = c < g.ncell && comp < NC;
+        const int64_t c1 = c0 + cells < g.ncell ? c0 + cells : g.ncell;
+        const bool mine = c < c1 && comp < NC;
         const int32_t rs = seg_clamp(start[c0], n), re = seg_clamp(start[c1], n);
         int32_t s = 0, e = 0;
         if (mine) {
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restric
         }
         GradLoads<T> gl;
         int cx = 0, cy = 0, cz = 0;
-        const bool grad = MODE == kForce && comp == kWavesPerBlock - 1 && c < g.ncell;   // the wave with no component
+        const bool grad = MODE == kForce && comp == kWavesPerBlock - 1 && c < c1;   // the wave with no component
         if (grad) {
             decode_cell(c, g.nb, cx, cy, cz);
             gl = load_gradient(c, cx, cy, cz, g, P, Plo);
@@ -182,7 +188,14 @@ __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restric
             __syncthreads();
             if (mine) {
                 const int32_t b0 = (int32_t)((s > cs ? s : cs) - cs), b1 = (int32_t)((e < cs + m ? e : cs + m) - cs);
-                for (int32_t k = b0; k < b1; ++k) acc.add(val[comp][k], g.inv_vb);
+                for (int32_t k = b0; k < b1; k += kNgpRead) {
+                    T x[kNgpRead];
+#pragma unroll
+                    for (int u = 0; u < kNgpRead; ++u) x[u] = val[comp][k + u < b1 ? k + u : k];
+#pragma unroll
+                    for (int u = 0; u < kNgpRead; ++u)
+                        if (k + u < b1) acc.add(x[u], g.inv_vb);
+                }
             }
             __syncthreads();
         }
@@ -536,7 +549,8 @@ __global__ __launch_bounds__(kBlock) void k_deposit_sum(const T *__restrict__ pa
 int deposit_blocks(int64_t ncell, int cic, int64_t part_stride) {
     if (cic) return (int)((ncell + kBlock - 1) / kBlock);   // pass 2
     // as many workgroups as there are partials for, each looping over its groups of cells
-    return (int)std::min((ncell + kNgpCells - 1) / kNgpCells, part_stride);
+    const int cells = ngp_cells(ncell);
+    return (int)std::min((ncell + cells - 1) / cells, part_stride);
 }
 
 static int64_t row_waves(const int nb[3], int G) {
@@ -571,7 +585,8 @@ static int launch_deposit(const StepArgs<T> &a, T *out, T *out2, hipStream_t st,
         else rows_and_sums(std::integral_constant<int, 2>{});
     } else {
         hipLaunchKernelGGL((k_deposit_ngp<T, SM, MODE>), dim3(nblk), dim3(kBlock), 0, st, a.start, pk,
-                           a.sp, a.perm, a.drag, a.n, a.g, a.P, a.Plo, out, out2, a.G, a.part, a.part_stride);
+                           a.sp, a.perm, a.drag, a.n, a.g, a.P, a.Plo, out, out2, a.G, a.part, a.part_stride,
+                           ngp_cells(a.g.ncell));
     }
     return nblk;
 }
