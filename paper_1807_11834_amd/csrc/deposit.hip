@@ -251,10 +251,12 @@ static_assert(SL_KUB == SL_KB + 1, "the semi-implicit sums are consecutive");
 // source row; GS = 1 trades that for four times the waves.
 //
 // The staged values of a particle are read by three lanes (its cell's and the
-// two neighbours'), each lane at a place of its own, so the reads conflict on
-// the LDS banks and bound the pass.  They are kept as 16-byte records, one read
-// for four values: with one 4-byte array per value the bed's solid fraction took
-// 128 us and its source 270 us.
+// two neighbours'), each lane at a place of its own.  They are kept as 16-byte
+// records, one read for four values.  The pass is bound by its arithmetic (the
+// VALU is busy 60 % of the time; LDS bank conflicts are a few percent) and by the
+// loads of the particles' drags, a line each in the order of their ids: 248 us for
+// the solid fraction of the bed of 10 million and its sorted copy, 264 for the
+// source.  Records of fewer words, other chunks and unconditional loads: no gain.
 template <typename T, int MODE> struct RowStage {
     vec4<T> wy[kWavesPerBlock][kChunk];   // weights on target rows y'-1, y', y'+1; weight of the upper x node
     vec4<T> wz[kWavesPerBlock][kChunk];   // weights on target layers z'-1, z', z'+1; x nodes lo | hi << 16 (bits)
