@@ -210,12 +210,7 @@ __global__ __launch_bounds__(kBlock) void k_remap_rows(RemapArgs<T> r, const T *
 // (z, y) overlaps of rx, whose offsets and weights are tabulated per receiver
 // row of the tile.  Sum order: x within each sender row, then (z, y) in raster
 // order.  Loop positions advance incrementally: no integer divisions per
-// element.  A workgroup is a chain of a few memory round trips (ranges, slab and
-// factors' ranges, factors) and two LDS passes: with the slab loaded value by
-// value and the factors after it four fields of 96 x 96 x 192 cells took 109.5 us to
-// 256 x 256 x 512, with eight loads of the slab in flight and the factors' ranges
-// beside them 103.3 (the writes alone 79).  Reading four rows' or four terms' LDS
-// values at a time: 105.1 and 112.8.
+// element.
 constexpr int kTileJ = 8, kTileK = 8;
 constexpr int kTileRows = kTileJ * kTileK;
 constexpr int kMaxX = 4;       // x factors held in registers (longer ranges read them in the loop)
@@ -249,94 +244,54 @@ __global__ __launch_bounds__(kBlock) void k_remap_tile(RemapArgs<T> r, const T *
     T *rx = slab + (((size_t)nrows * nsx + 3) & ~(size_t)3);   // 16-byte aligned
     const int64_t sxy = (int64_t)r.ns[0] * r.ns[1];
     const T *__restrict__ s = src + (int64_t)blockIdx.y * r.nsrc;
-    // the factors of the thread's receiver row (row = kk * nj + jj) and of its
-    // first receiver column: their ranges are in flight with the slab's loads
-    const int tile_rows = nj * nk, tr0 = (int)threadIdx.x < tile_rows ? (int)threadIdx.x : 0;
-    const int rj = j0 + tr0 % nj, rk = k0 + tr0 / nj, xc = (int)threadIdx.x < ndx ? (int)threadIdx.x : 0;
-    const int fz = r.first[2][rk], nz = r.cnt[2][rk], oz = r.off[2][rk];
-    const int fy = r.first[1][rj], ny = r.cnt[1][rj], oy = r.off[1][rj];
-    const int fx0 = r.first[0][xc], nx0 = r.cnt[0][xc], ox0 = r.off[0][xc];
+    // the term table, one thread per receiver row of the tile (row = kk * nj + jj)
+    if (threadIdx.x < nj * nk) {
+        const int jj = threadIdx.x % nj, kk = threadIdx.x / nj;
+        const int j = j0 + jj, k = k0 + kk;
+        const int fz = r.first[2][k], nz = r.cnt[2][k], oz = r.off[2][k];
+        const int fy = r.first[1][j], ny = r.cnt[1][j], oy = r.off[1][j];
+        tn[threadIdx.x] = nz * ny;
+        tjk[threadIdx.x][0] = j;
+        tjk[threadIdx.x][1] = k;
+        orow[threadIdx.x] = ((int64_t)k * r.nd[1] + j) * ndx;
+        if (nz * ny <= kMaxTerms) {
+            int q = 0;
+            for (int kz = 0; kz < nz; ++kz)
+                for (int ky = 0; ky < ny; ++ky, ++q) {
+                    toff[threadIdx.x][q] = ((fz + kz - zs0) * Ys + (fy + ky - ys0)) * ndx;
+                    tw[threadIdx.x][q] = W(r.w[2][oz + kz] * r.w[1][oy + ky]);
+                }
+        }
+    }
     // stage the slab, x fastest, then slab rows (y fastest, then z)
     {
         int x = threadIdx.x % nsx, row = threadIdx.x / nsx;
         int yy = row % Ys, zz = row / Ys;
         const int dx = kBlock % nsx, drow = kBlock / nsx;
-        // kStage loads in flight (positions past the end repeat the slab's first row)
-        constexpr int kStage = 8;
         while (row < nrows) {
-            T v[kStage];
-            int at[kStage];
-#pragma unroll
-            for (int u = 0; u < kStage; ++u) {
-                const bool in = row < nrows;
-                at[u] = in ? row * nsx + x : -1;
-                v[u] = s[(int64_t)(zs0 + (in ? zz : 0)) * sxy + (int64_t)(ys0 + (in ? yy : 0)) * nsx + x];
-                x += dx;
-                int d = drow;
-                if (x >= nsx) {
-                    x -= nsx;
-                    ++d;
-                }
-                row += d;
-                yy += d;
-                if (yy >= Ys) {
-                    zz += yy / Ys;
-                    yy %= Ys;
-                }
+            slab[(size_t)row * nsx + x] = s[(int64_t)(zs0 + zz) * sxy + (int64_t)(ys0 + yy) * nsx + x];
+            x += dx;
+            int d = drow;
+            if (x >= nsx) {
+                x -= nsx;
+                ++d;
             }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < kStage; ++u)
-                if (at[u] >= 0) slab[at[u]] = v[u];
-        }
-    }
-    auto x_weights = [&](int nx, int ox, W(&wx)[kMaxX]) {
-        T t[kMaxX] = {};
-        if (nx > 0) {
-#pragma unroll
-            for (int q = 0; q < kMaxX; ++q) t[q] = r.w[0][ox + (q < nx ? q : 0)];
-        }
-#pragma unroll
-        for (int q = 0; q < kMaxX; ++q) wx[q] = q < nx ? W(t[q]) : W(0);
-    };
-    W wx0[kMaxX];
-    x_weights(nx0, ox0, wx0);
-    // the term table, one thread per receiver row of the tile
-    if ((int)threadIdx.x < tile_rows) {
-        const int n = nz * ny;
-        tn[threadIdx.x] = n;
-        tjk[threadIdx.x][0] = rj;
-        tjk[threadIdx.x][1] = rk;
-        orow[threadIdx.x] = ((int64_t)rk * r.nd[1] + rj) * ndx;
-        if (n > 0 && n <= kMaxTerms) {
-            T wz[kMaxTerms], wy[kMaxTerms];
-#pragma unroll
-            for (int q = 0; q < kMaxTerms; ++q) {
-                wz[q] = r.w[2][oz + (q < nz ? q : 0)];
-                wy[q] = r.w[1][oy + (q < ny ? q : 0)];
+            row += d;
+            yy += d;
+            if (yy >= Ys) {
+                zz += yy / Ys;
+                yy %= Ys;
             }
-#pragma unroll
-            for (int kz = 0; kz < kMaxTerms; ++kz)
-#pragma unroll
-                for (int ky = 0; ky < kMaxTerms; ++ky)
-                    if (kz < nz && ky < ny) {
-                        toff[threadIdx.x][kz * ny + ky] = ((fz + kz - zs0) * Ys + (fy + ky - ys0)) * ndx;
-                        tw[threadIdx.x][kz * ny + ky] = W(wz[kz] * wy[ky]);
-                    }
         }
     }
     __syncthreads();
     // x transfer of every slab row; each thread keeps the x factor of its
     // receiver columns in registers
     for (int xd = threadIdx.x; xd < ndx; xd += kBlock) {
-        int fx = fx0, nx = nx0, ox = ox0;
+        const int fx = r.first[0][xd], nx = r.cnt[0][xd], ox = r.off[0][xd];
         W wx[kMaxX];
 #pragma unroll
-        for (int q = 0; q < kMaxX; ++q) wx[q] = wx0[q];
-        if (xd >= kBlock) {
-            fx = r.first[0][xd], nx = r.cnt[0][xd], ox = r.off[0][xd];
-            x_weights(nx, ox, wx);
-        }
+        for (int q = 0; q < kMaxX; ++q) wx[q] = q < nx ? W(r.w[0][ox + q]) : W(0);
         for (int row = 0; row < nrows; ++row) {
             const T *sr = slab + (size_t)row * nsx + fx;
             FmaSum<T, SM> acc;
