@@ -27,7 +27,8 @@
  * x_a[n[a]] (finite); `nodes` holds the three axes' node coordinates one after
  * the other (n[0] + 1 + n[1] + 1 + n[2] + 1 doubles, host memory).  Both grids
  * must span the same interval on every axis (end nodes equal to within 1e-12
- * relative).  Fields are [nz][ny][nx], x fastest; `nfields` fields are stored
+ * relative; a receiver cell inside that margin that overlaps no sender cell
+ * receives 0).  Fields are [nz][ny][nx], x fastest; `nfields` fields are stored
  * back to back (a vector field is nfields = 3).
  *
  * Memory and errors follow couple.h: device pointers owned by the caller,

@@ -148,12 +148,15 @@ __global__ __launch_bounds__(kBlock) void k_remap_rows(RemapArgs<T> r, const T *
     // Sender row q0 + lane of receiver row rr: its offset and weight, and the
     // number of sender rows.  Lanes past the last one hold it again, so that the
     // loads of the rows are not conditional (a conditional load waits for those
-    // before it).
+    // before it).  A row that overlaps no sender row (the grids' ends may differ
+    // by rounding) has no factors to read.
     auto terms = [&](int64_t rr, int q0, int64_t &qo, T &qw) {
         const int j = (int)(rr % r.nd[1]), k = (int)(rr / r.nd[1]);
         const int fy = r.first[1][j], ny = r.cnt[1][j], oy = r.off[1][j];
         const int fz = r.first[2][k], nz = r.cnt[2][k], oz = r.off[2][k];
-        const int nq = ny * nz, q = q0 + lane < nq ? q0 + lane : nq - 1, kz = q / ny, ky = q % ny;
+        const int nq = ny * nz;
+        if (nq == 0) return 0;   // uniform over the wave
+        const int q = q0 + lane < nq ? q0 + lane : nq - 1, kz = q / ny, ky = q % ny;
         qo = (int64_t)(fz + kz) * sxy + (int64_t)(fy + ky) * nsx;
         qw = r.w[2][oz + kz] * r.w[1][oy + ky];
         return nq;
@@ -189,6 +192,8 @@ __global__ __launch_bounds__(kBlock) void k_remap_rows(RemapArgs<T> r, const T *
                     for (int c = 0; c < V; ++c) row[x + c] = acc[c].value();
             }
         }
+        if (nq == 0)   // receives 0
+            for (int x = lane; x < nsx; x += kWave) row[x] = T(0);
         wave_sync();
         if (rr + step < nrow) nq = terms(rr + step, 0, qo, qw);   // while the x part runs
         T *__restrict__ out = dst + (int64_t)blockIdx.y * r.ndst + rr * ndx;
@@ -263,8 +268,9 @@ __global__ __launch_bounds__(kBlock) void k_remap_tile(RemapArgs<T> r, const T *
                 }
         }
     }
-    // stage the slab, x fastest, then slab rows (y fastest, then z)
-    {
+    // stage the slab, x fastest, then slab rows (y fastest, then z); none where
+    // the tile overlaps no sender row
+    if (nrows > 0) {
         int x = threadIdx.x % nsx, row = threadIdx.x / nsx;
         int yy = row % Ys, zz = row / Ys;
         const int dx = kBlock % nsx, drow = kBlock / nsx;
