@@ -107,21 +107,16 @@ struct ScratchPlan {
 };
 
 // `tight`: the least scratch a step runs in (histograms for the fewest tiles a
-// sort can take, diagnostic partials for fewer workgroups of the prolongation).
+// sort can take).
 static ScratchPlan scratch_plan(const couple_config &c, int64_t nmax, bool tight = false) {
     ScratchPlan p{};
     const int64_t ncell = (int64_t)c.nb[0] * c.nb[1] * c.nb[2];
     const size_t fsz = (c.precision == COUPLE_FP64) ? sizeof(double) : sizeof(float);
     const int64_t ntile = p.max_tiles = tight ? sort_tiles_min(nmax) : sort_tiles_max(nmax);
-    const int64_t pblk = (nmax + kBlock - 1) / kBlock, cblk = (ncell + kBlock - 1) / kBlock;
     // one FP64 partial per workgroup and slot: the stride covers the largest
-    // grid of any kernel that writes partials (the prolongation and the NGP
-    // deposition take no more workgroups than that)
+    // grid of any kernel that writes partials
     const int64_t mblk = c.vel_source == COUPLE_VEL_MLP ? mlp_check_blocks(bricks_of(c.nb)) : 1;
-    const int64_t prblk = tight ? 1 : std::min<int64_t>(prolong_items(c.nb, c.ratio), 1024);
-    p.part_stride = 1;
-    for (int64_t b : {pblk, cblk, ntile, mblk, prblk})
-        if (b > p.part_stride) p.part_stride = b;
+    p.part_stride = std::max({most_partials(nmax, ncell), ntile, mblk});
     p.bytes[B_KEYS_A] = p.bytes[B_KEYS_B] = p.bytes[B_VALS_A] = p.bytes[B_VALS_B] = sizeof(uint32_t) * nmax;
     p.bytes[B_HIST] = std::max(sizeof(uint32_t) * 256 * ntile, tight ? 0 : count_sort_bytes(nmax, ncell));
     p.bytes[B_TOTALS] = sizeof(uint32_t) * 256;

@@ -548,11 +548,10 @@ __global__ __launch_bounds__(kBlock) void k_deposit_sum(const T *__restrict__ pa
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-int deposit_blocks(int64_t ncell, int cic, int64_t part_stride) {
+int deposit_blocks(int64_t n, int64_t ncell, int cic) {
     if (cic) return (int)((ncell + kBlock - 1) / kBlock);   // pass 2
-    // as many workgroups as there are partials for, each looping over its groups of cells
-    const int cells = ngp_cells(ncell);
-    return (int)std::min((ncell + cells - 1) / cells, part_stride);
+    const int cells = ngp_cells(ncell);   // NGP: each loops over its groups of cells
+    return (int)std::min((ncell + cells - 1) / cells, most_partials(n, ncell));
 }
 
 static int64_t row_waves(const int nb[3], int G) {
@@ -571,7 +570,7 @@ static int row_blocks(const int nb[3], int G) {
 
 template <typename T, int SM, int MODE>
 static int launch_deposit(const StepArgs<T> &a, T *out, T *out2, hipStream_t st, const char *sum_mark) {
-    const int nblk = deposit_blocks(a.g.ncell, a.cic, a.part_stride);
+    const int nblk = deposit_blocks(a.n, a.g.ncell, a.cic);
     // the packed particles until the velocity is sampled; (beta, beta u_p) once the drag has run
     const vec4<T> *pk = a.uf4;
     if (a.cic) {

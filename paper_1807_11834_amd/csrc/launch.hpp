@@ -144,13 +144,22 @@ int64_t bricks_of(const int nb[3]);
 template <typename T, int SM> int launch_deposit_phi(const StepArgs<T> &a, hipStream_t st);
 template <typename T, int SM> int launch_deposit_force(const StepArgs<T> &a, hipStream_t st);
 template <typename T, int SM> int launch_deposit_semi(const StepArgs<T> &a, hipStream_t st);
-int deposit_blocks(int64_t ncell, int cic, int64_t part_stride);
+int deposit_blocks(int64_t n, int64_t ncell, int cic);
 // Source rows per group of the CIC row pass (1 or 2 in y and z): the partial
 // buffer holds (G == 1 ? 9 : 4) slots per cell and component.
 int deposit_group(const int nb[3]);
 
-// Work items per field of a prolongation (stages.hip), which takes as many
-// workgroups per field, one FP64 partial each, or as many as the partials allow.
-int64_t prolong_items(const int nb[3], int ratio);
+// Workgroups per field of a prolongation (stages.hip), one FP64 partial each.
+int64_t prolong_blocks(int64_t n, const int nb[3], int ratio);
+
+// Most workgroups (one FP64 partial each) of a kernel that can loop over its work:
+// as many as the step's other kernels have, or two per compute unit.  It depends on
+// the step's sizes alone, not on the scratch at hand, so that the diagnostics are
+// the same bits whatever max_particles a handle has, and in static scratch.
+inline int64_t most_partials(int64_t n, int64_t ncell) {
+    const int64_t pblk = (n + kBlock - 1) / kBlock, cblk = (ncell + kBlock - 1) / kBlock;
+    const int64_t m = pblk > cblk ? pblk : cblk;
+    return m > 512 ? m : 512;
+}
 
 }  // namespace cpl

@@ -742,8 +742,7 @@ template <typename T> struct ProlongSet {
 // every field (blockIdx.y).  The tile's 3 x 3 x 3 neighbourhoods (the tile with a
 // one-cell halo, indices clamped at the walls) are staged in LDS in one memory
 // round trip, and each thread writes its cell's children plane by plane.
-// Workgroups loop over the items, as many workgroups as there are diagnostic
-// partials for.
+// Workgroups loop over the items (prolong_blocks).
 constexpr int kPMaxX = 7, kPMinX = 4;   // tiles of 128 x 2 ... 16 x 16 cells
 constexpr int kPStage = ((1 << kPMaxX) + 2) * ((kBlock >> kPMaxX) + 2);   // staged values of the widest tile
 static_assert(((1 << kPMinX) + 2) * ((kBlock >> kPMinX) + 2) <= kPStage, "the widest tile has the most halo");
@@ -765,17 +764,16 @@ static int64_t prolong_layer(const int nb[3]) {   // tiles of a layer
 // Fine planes per item: all r of them (x and y interpolated once), or one where
 // whole tiles would leave the four or more fields fewer than 1024 workgroups.
 static int prolong_planes(const int nb[3], int ratio) { return prolong_layer(nb) * nb[2] * 4 < 1024 ? 1 : ratio; }
-int64_t prolong_items(const int nb[3], int ratio) {
+static int64_t prolong_items(const int nb[3], int ratio) {
     return prolong_layer(nb) * nb[2] * (ratio / prolong_planes(nb, ratio));
 }
 static_assert(kBlock == 256, "a tile has 2^8 cells");
 
-// Workgroups per field: one per item, or as many as there are partials (a
-// multiple of the XCDs, so that each keeps its share of the items).
-static int64_t prolong_blocks(const int nb[3], int ratio, int64_t part_stride) {
-    const int64_t items = prolong_items(nb, ratio);
-    if (items <= part_stride) return items;
-    return part_stride >= 8 ? part_stride / 8 * 8 : part_stride;
+// Workgroups per field: one per item, or the most there may be (a multiple of the
+// XCDs, so that each keeps its share of the items).
+int64_t prolong_blocks(int64_t n, const int nb[3], int ratio) {
+    const int64_t items = prolong_items(nb, ratio), most = most_partials(n, (int64_t)nb[0] * nb[1] * nb[2]);
+    return items <= most ? items : most / 8 * 8;
 }
 
 template <typename T, int R>
@@ -1023,7 +1021,7 @@ static void launch_grid_stages(const StepArgs<T> &a, hipStream_t st, int phases)
         for (int k = 0; k < 3; ++k) add(a.KU + k * nc, a.fine_KU + k * nf, SL_KUF + k);
     }
     a.mk->mark("prolong", st);
-    hipLaunchKernelGGL((k_prolong<T, R>), dim3((unsigned)prolong_blocks(a.g.nb, R, a.part_stride), (unsigned)m),
+    hipLaunchKernelGGL((k_prolong<T, R>), dim3((unsigned)prolong_blocks(a.n, a.g.nb, R), (unsigned)m),
                        dim3(kBlock), 0, st, a, fs, prolong_shift(a.g.nb[0]), prolong_planes(a.g.nb, R),
                        prolong_items(a.g.nb, R));
     }
@@ -1049,7 +1047,7 @@ template <typename T> hipError_t launch_stages(const StepArgs<T> &a, hipStream_t
         spec.nblk[s] = (int)cb;
         spec.scale[s] = 1.0;
     }
-    const int db = deposit_blocks(a.g.ncell, a.cic, a.part_stride);
+    const int db = deposit_blocks(a.n, a.g.ncell, a.cic);
     spec.nblk[SL_PHISUM] = db;
     spec.nblk[SL_MAXPHI] = db;
     for (int k = 0; k < 3; ++k) spec.nblk[SL_FB + k] = db;
@@ -1063,7 +1061,7 @@ template <typename T> hipError_t launch_stages(const StepArgs<T> &a, hipStream_t
     spec.nblk[SL_MLPERR] = nmlp;
     spec.nblk[SL_MLPREF] = nmlp;
     spec.nblk[SL_MLPSAMP] = nmlp;
-    const int ptiles = (int)prolong_blocks(a.g.nb, a.ratio, a.part_stride);   // k_prolong
+    const int ptiles = (int)prolong_blocks(a.n, a.g.nb, a.ratio);   // k_prolong
     spec.nblk[SL_EPSF] = ptiles;
     for (int k = 0; k < 3; ++k) spec.nblk[SL_FF + k] = ptiles;
     for (int k = 0; k < 4; ++k) {
