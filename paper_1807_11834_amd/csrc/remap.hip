@@ -77,18 +77,21 @@ __global__ __launch_bounds__(kBlock) void k_remap(RemapArgs<T> r, const T *__res
     dst[(int64_t)blockIdx.y * r.ndst + c] = acc.value();
 }
 
-// Receiver rows (y, z) of one field, a wave each, grid-strided over the rows.  A
-// row's y and z factors are the same for the whole wave: the offsets of the (z,
-// y) sender rows it overlaps and their weights wz * wy are formed by one lane
-// each (up to kMaxQ at a time) and read as wave-uniform values; then every
-// sender x is summed over those rows -- a lane takes V neighbouring x, 16 bytes,
-// and issues its kMaxQ loads together -- giving r(x_s) in LDS; then each receiver
-// x sums its overlapping r values with the x weights, which the workgroup keeps
-// in LDS where they fit.  Sum order: (z, y) in raster order, then x.
+// Receiver rows (y, z) of one field, TEAM waves each (1 or the workgroup's 4),
+// grid-strided over the rows.  A row's y and z factors are the same for the whole
+// wave: the offsets of the (z, y) sender rows it overlaps and their weights wz * wy
+// are formed by one lane each (up to kMaxQ at a time) and read as wave-uniform
+// values; then every sender x is summed over those rows -- a lane takes V
+// neighbouring x, 16 bytes, and issues its kMaxQ loads together -- giving r(x_s) in
+// LDS; then each receiver x sums its overlapping r values with the x weights, which
+// the workgroup keeps in LDS where they fit.  Sum order: (z, y) in raster order,
+// then x.
 //
 // Bound by the sender reads.  A row per workgroup, with three barriers per row
 // and one x per thread, kept too few loads in flight: four 256 x 256 x 512 fields
-// to 96 x 96 x 192 took 189 us (3.0 TB/s of algorithmic bytes).
+// to 96 x 96 x 192 took 189 us (3.0 TB/s of algorithmic bytes), with a wave per row
+// 130.  The four waves share a row where four rows do not fit in LDS (a workgroup
+// of one wave then leaves a compute unit two to ten waves) or there are too few rows.
 constexpr int kMaxQ = 16;
 
 template <typename T, int V> using VecX = T __attribute__((ext_vector_type(V)));
@@ -111,7 +114,7 @@ template <typename T> struct XFactors {
     const T *w;
 };
 
-template <typename T, int SM, int V>
+template <typename T, int SM, int V, int TEAM>
 __global__ __launch_bounds__(kBlock) void k_remap_rows(RemapArgs<T> r, const T *__restrict__ src,
                                                        T *__restrict__ dst, int nnz_x /* 0: factors in memory */) {
     // both compensated modes run Kahan in T here: FP64 sums of the sixteen
@@ -121,10 +124,16 @@ __global__ __launch_bounds__(kBlock) void k_remap_rows(RemapArgs<T> r, const T *
     using Vec = VecX<T, V>;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);   // in a scalar register
-    const int nwave = blockDim.x / kWave;
+    constexpr int nwave = kWavesPerBlock / TEAM;                        // rows of a workgroup at a time
+    const int wrow = TEAM == 1 ? wave : 0;                              // this wave's
+    const int tlane = TEAM == 1 ? lane : (int)threadIdx.x;              // lane of the row's team
+    auto team_sync = [] {
+        if constexpr (TEAM == 1) wave_sync();
+        else __syncthreads();
+    };
     const int nsx = r.ns[0], ndx = r.nd[0];
     const int pitch = (nsx + 3) & ~3;   // rows stay 16-byte aligned
-    T *row = reinterpret_cast<T *>(lds_raw) + (size_t)wave * pitch;
+    T *row = reinterpret_cast<T *>(lds_raw) + (size_t)wrow * pitch;
     XFactors<T> xf{r.first[0], r.cnt[0], r.off[0], r.w[0]};
     if (nnz_x > 0) {
         T *sw = reinterpret_cast<T *>(lds_raw) + (size_t)nwave * pitch;
@@ -162,15 +171,15 @@ __global__ __launch_bounds__(kBlock) void k_remap_rows(RemapArgs<T> r, const T *
         return nq;
     };
     const int64_t step = (int64_t)gridDim.x * nwave;
-    int64_t rr = tile * nwave + wave, qo = 0;   // rr: uniform over the wave
+    int64_t rr = tile * nwave + wrow, qo = 0;   // rr: uniform over the team
     T qw = T(0);
     int nq = rr < nrow ? terms(rr, 0, qo, qw) : 0;
     for (; rr < nrow; rr += step) {
         for (int q0 = 0; q0 < nq; q0 += kMaxQ) {
             const int mq = nq - q0 < kMaxQ ? nq - q0 : kMaxQ;
             if (q0 > 0) terms(rr, q0, qo, qw);
-            for (int x0 = 0; x0 < nsx; x0 += kWave * V) {   // V divides nsx
-                const int x = x0 + lane * V;
+            for (int x0 = 0; x0 < nsx; x0 += TEAM * kWave * V) {   // V divides nsx
+                const int x = x0 + tlane * V;
                 const bool on = x < nsx;
                 const int xl = on ? x : 0;
                 Vec v[kMaxQ];
@@ -193,17 +202,17 @@ __global__ __launch_bounds__(kBlock) void k_remap_rows(RemapArgs<T> r, const T *
             }
         }
         if (nq == 0)   // receives 0
-            for (int x = lane; x < nsx; x += kWave) row[x] = T(0);
-        wave_sync();
+            for (int x = tlane; x < nsx; x += TEAM * kWave) row[x] = T(0);
+        team_sync();
         if (rr + step < nrow) nq = terms(rr + step, 0, qo, qw);   // while the x part runs
         T *__restrict__ out = dst + (int64_t)blockIdx.y * r.ndst + rr * ndx;
-        for (int xd = lane; xd < ndx; xd += kWave) {
+        for (int xd = tlane; xd < ndx; xd += TEAM * kWave) {
             const int fx = xf.first[xd], nx = xf.cnt[xd], ox = xf.off[xd];
             FmaSum<T, SMR> acc;
             for (int kx = 0; kx < nx; ++kx) acc.add(W(xf.w[ox + kx]), W(row[fx + kx]));
             out[xd] = acc.value();
         }
-        wave_sync();   // the row buffer is reused by the next row
+        team_sync();   // the row buffer is reused by the next row
     }
 }
 
@@ -369,13 +378,23 @@ __global__ __launch_bounds__(kBlock) void k_remap_tile(RemapArgs<T> r, const T *
 constexpr size_t kTileLdsBytes = 96 * 1024;
 
 // Sender rows up to this many bytes are staged whole in LDS by k_remap_rows, four
-// (of four waves) or one to a workgroup; longer rows take k_remap.
+// to a workgroup or one; longer rows take k_remap.
 constexpr size_t kRowLdsBytes = 60 * 1024;
 // The x factors go to LDS with them up to this many bytes.
 constexpr size_t kFactorLdsBytes = 24 * 1024;
 // Workgroups of the row kernel over all fields: sixteen waves per compute unit,
 // four rounds, so that the last round is a small part.
 constexpr int64_t kRowBlocks = 4096;
+// A workgroup's four waves share one row instead of taking one each
+//   - where there are fewer receiver rows over all fields than one per SIMD: 256 x
+//     256 x 512 FP32 cells to 8 x 8 x 16, 88 us (a wave per row: 121; to 16 x 16 x 32,
+//     512 rows, 30 and 36; to 32 x 32 x 64, 2048 rows, 33 and 25);
+//   - where a sender row is longer than this: four of them in LDS leave a compute
+//     unit too few waves.  4 fields of 3000 x 32 x 32 (12 KB) to 3000 x 30 x 30, 44 us
+//     (95); 2000 x 50 x 50 (8 KB) to 800 x 24 x 24, 28 (31).  With 6.4 KB a wave per
+//     row is the faster: 800 x 90 x 90 in FP64 to 790 x 80 x 80, 48 against 56.
+constexpr int64_t kTeamRows = 1024;
+constexpr size_t kTeamRowBytes = 7 * 1024;
 
 }  // namespace
 
@@ -565,22 +584,28 @@ static hipError_t launch_remap(const couple_remap *r, const void *src, void *dst
         hipLaunchKernelGGL((k_remap_tile<T, SM>), dim3((unsigned)ntile, (unsigned)nfields), dim3(kBlock), tile_lds,
                            st, a, static_cast<const T *>(src), static_cast<T *>(dst), vec4);
     } else if (lds <= kRowLdsBytes) {
-        const int waves = 4 * lds <= kRowLdsBytes ? 4 : 1;
+        const int64_t nrow = (int64_t)r->nd[1] * r->nd[2];
+        const int rows = lds > kTeamRowBytes || nrow * nfields < kTeamRows ? 1 : kWavesPerBlock;   // per workgroup
         size_t fac = sizeof(T) * (size_t)r->ax[0].nnz + 3 * sizeof(int32_t) * (size_t)r->nd[0];
-        if (fac > kFactorLdsBytes || fac + waves * lds + 64 > kRowLdsBytes) fac = 0;
+        if (fac > kFactorLdsBytes || fac + rows * lds + 64 > kRowLdsBytes) fac = 0;
         const int nnz_x = fac ? (int)r->ax[0].nnz : 0;
-        const size_t bytes = (size_t)waves * sizeof(T) * (((size_t)r->ns[0] + 3) & ~(size_t)3) + fac;
-        const int64_t nblk = ((int64_t)r->nd[1] * r->nd[2] + waves - 1) / waves;
-        const int64_t per_field = std::max<int64_t>(1, std::min<int64_t>(nblk, kRowBlocks * (4 / waves) / nfields + 1));
+        const size_t bytes = (size_t)rows * sizeof(T) * (((size_t)r->ns[0] + 3) & ~(size_t)3) + fac;
+        const int64_t nblk = (nrow + rows - 1) / rows;
+        const int64_t per_field = std::max<int64_t>(1, std::min<int64_t>(nblk, kRowBlocks / nfields + 1));
         constexpr int VW = 16 / sizeof(T);
-        const bool vec = r->ns[0] % VW == 0 && reinterpret_cast<uintptr_t>(src) % 16 == 0;
-        auto rows = [&](auto vc) {
-            hipLaunchKernelGGL((k_remap_rows<T, SM, decltype(vc)::value>), dim3((unsigned)per_field, (unsigned)nfields),
-                               dim3((unsigned)(waves * kWave)), bytes, st, a, static_cast<const T *>(src),
-                               static_cast<T *>(dst), nnz_x);
+        const bool vec = r->ns[0] % VW == 0 && reinterpret_cast<uintptr_t>(src) % 16 == 0 &&
+                         (rows > 1 || 2 * r->ns[0] >= kBlock * VW);   // at least half of a team's lanes load
+        auto launch = [&](auto vc, auto tc) {
+            hipLaunchKernelGGL((k_remap_rows<T, SM, decltype(vc)::value, decltype(tc)::value>),
+                               dim3((unsigned)per_field, (unsigned)nfields), dim3(kBlock), bytes, st, a,
+                               static_cast<const T *>(src), static_cast<T *>(dst), nnz_x);
         };
-        if (vec) rows(std::integral_constant<int, VW>{});
-        else rows(std::integral_constant<int, 1>{});
+        auto launch_team = [&](auto vc) {
+            if (rows == 1) launch(vc, std::integral_constant<int, kWavesPerBlock>{});
+            else launch(vc, std::integral_constant<int, 1>{});
+        };
+        if (vec) launch_team(std::integral_constant<int, VW>{});
+        else launch_team(std::integral_constant<int, 1>{});
     } else {
         const int64_t nblk = (a.ndst + kBlock - 1) / kBlock;
         hipLaunchKernelGGL((k_remap<T, SM>), dim3((unsigned)nblk, (unsigned)nfields), dim3(kBlock), 0, st, a,
