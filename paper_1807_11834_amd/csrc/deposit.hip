@@ -301,6 +301,14 @@ template <int G> struct GroupSlots { static constexpr int value = G == 1 ? 3 : 2
 // One source row (ys, zs) of the wave's group: row JY, layer KZ of the group.
 // Its contributions go to the accumulators [KZ + 0..2][JY + 0..2] (A = G + 2
 // target rows per axis).
+// Waves per SIMD asked of the compiler.  The Kahan source (2 x 2 groups) would take
+// 170 registers per lane, two waves; in 168, three waves, with two words kept in
+// memory from the prologue to the final stores: 400 -> 318 us for the bed of 10
+// million, 88 -> 67 for 100,000 particles in 4.2 million cells.
+template <typename T, int SM, int MODE> struct RowWaves {
+    static constexpr int value = std::is_same<T, float>::value && SM == kSumKahan && MODE == kForce ? 3 : 1;
+};
+
 template <typename T, int SM, int MODE, int JY, int KZ, int A>
 __device__ __forceinline__ void deposit_source_row(RowSum<T, SM> (&acc)[A][A][DepNc<MODE>::value],
                                                    RowStage<T, MODE> &st, int w, int lane, int x0, int ys, int zs,
@@ -423,11 +431,9 @@ __device__ __forceinline__ void deposit_source_row(RowSum<T, SM> (&acc)[A][A][De
 }
 
 template <typename T, int SM, int MODE, int GS>
-__global__ __launch_bounds__(kBlock) void k_deposit_rows(const int32_t *__restrict__ start,
-                                                         const vec4<T> *__restrict__ pk, vec4<T> *__restrict__ sp,
-                                                         const int32_t *__restrict__ perm,
-                                                         const T *__restrict__ drag, int64_t n, Geo<T> g,
-                                                         T *__restrict__ partial) {
+__global__ __launch_bounds__(kBlock, (RowWaves<T, SM, MODE>::value)) void k_deposit_rows(
+    const int32_t *__restrict__ start, const vec4<T> *__restrict__ pk, vec4<T> *__restrict__ sp,
+    const int32_t *__restrict__ perm, const T *__restrict__ drag, int64_t n, Geo<T> g, T *__restrict__ partial) {
     constexpr int NC = DepNc<MODE>::value, A = GS + 2, S = GroupSlots<GS>::value;
     __shared__ RowStage<T, MODE> st;
     const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
