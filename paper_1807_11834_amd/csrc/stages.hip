@@ -365,7 +365,21 @@ __device__ __forceinline__ T trilin_alpha8(const T *__restrict__ alpha8, const A
 // eight along z, or dealt to the XCDs in rows or layers: no faster.)
 constexpr int kBrickX = 8, kBrickY = 4, kBrickZ = 2;
 constexpr int kBrickFill = 4 * kBrickX * kBrickY * kBrickZ;   // threads that fill one component
-constexpr int kBrickThreads = 2 * kBrickFill;
+// HALVES = 2: the first half of 512 threads fills u and v, the other w, phi and the
+// particle rows; 1: each of 256 fills all three.  Ratio 4 takes 512, and so do fewer
+// bricks than fill the chip (two per compute unit), whose particles are then one
+// batch (17 x 13 x 19 cells of ratio 2 with 20,000 particles, 7.6 us; with 256
+// threads 9.0).  More bricks of a smaller ratio have little to fill, half of the
+// threads or more idle meanwhile: 128 x 128 x 256 cells of ratio 1 with 100,000
+// particles, 115 us with 256 threads and 200 with 512, in FP64 163 and 367; 100^3 of
+// ratio 2 with 50,000, 36 and 57.
+template <int HALVES> constexpr int kBrickThreads = HALVES * kBrickFill;
+constexpr int64_t kBrickFew = 512;
+// Waves per SIMD asked of the compiler: FP64 would take 98 registers, four waves; in
+// 96, five (the FP64 figure above: 189 -> 163 us; six spill, 174).
+template <typename T, int HALVES> struct BrickWaves {
+    static constexpr int value = HALVES == 1 && sizeof(T) == 8 ? 5 : 1;
+};
 constexpr int kBrickRows = kBrickY * kBrickZ;                                     // particle rows of a brick
 constexpr int kBrickHalo = (kBrickX + 2) * (kBrickY + 2) * (kBrickZ + 2);         // phi with a one-cell halo
 
@@ -387,15 +401,20 @@ template <typename T> struct BrickGrid {
 };
 
 // Fill the brick at (ox, oy, oz) into L and (if write_u) write its U; thread t of
-// kBrickThreads: the first half u and v, the other w, phi and the particle rows.
-template <typename T, int R, int SM>
+// kBrickThreads<HALVES>.
+template <typename T, int R, int SM, int HALVES>
 __device__ __forceinline__ void brick_fill(const StepArgs<T> &a, BrickLds<T, R> &L, int t, int ox, int oy, int oz,
                                            bool write_u) {
     constexpr int HX = kBrickX + 2, HY = kBrickY + 2;
     const Geo<T> &g = a.g;
     const int lane = t % kWave;
-    const bool upper = t >= kBrickFill;   // a wave is in one half
+    constexpr bool kSplit = HALVES == 2;
+    const bool upper = kSplit && t >= kBrickFill;   // a wave is in one half
+    const bool rest = upper || !kSplit;             // phi and the particle rows
     t %= kBrickFill;
+    // components of this thread: f0, f0 + 1, ... (nf of them)
+    constexpr int NF = kSplit ? 2 : 3;
+    const int f0 = upper ? 2 : 0, nf = upper ? 1 : NF;
     // cell of the brick and fine child plane: the eight lanes along x read and
     // write a contiguous row
     const int lx = t % kBrickX, rz = (t / kBrickX) % 4, ly = (t / (4 * kBrickX)) % kBrickY, lz = t / (4 * kBrickX * kBrickY);
@@ -409,7 +428,7 @@ __device__ __forceinline__ void brick_fill(const StepArgs<T> &a, BrickLds<T, R> 
     // waits for one memory round trip instead of three.
     static_assert(kBrickHalo <= kBrickFill, "one halo value per thread");
     int32_t seg0 = 0, seg1 = 0;
-    if (upper && t < kBrickRows) {
+    if (rest && t < kBrickRows) {
         const int wx = (ox + kBrickX < g.nb[0]) ? kBrickX : g.nb[0] - ox;
         const int ry = oy + t % kBrickY, rzz = oz + t / kBrickY;
         if (ry < g.nb[1] && rzz < g.nb[2]) {
@@ -420,33 +439,33 @@ __device__ __forceinline__ void brick_fill(const StepArgs<T> &a, BrickLds<T, R> 
     }
     const int hx = t % HX, hy = (t / HX) % HY, hz = t / (HX * HY);
     T ph = T(0);
-    if (upper && t < kBrickHalo) {
+    if (rest && t < kBrickHalo) {
         const int gx = clampi(ox - 1 + hx, g.nb[0]), gy = clampi(oy - 1 + hy, g.nb[1]), gz = clampi(oz - 1 + hz, g.nb[2]);
         ph = a.phi[gx + nx * gy + nxy * gz];
     }
     const bool work = inside && rz < R;
     const int64_t base = ((int64_t)R * cz + rz) * nfxy + (int64_t)R * cy * nfx + (int64_t)R * cx;
     const T inv = T(1) / T(R * R * R);
-    Row<T, R> rows[2][R];
+    Row<T, R> rows[NF][R];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        if (upper && i == 1) break;
+    for (int i = 0; i < NF; ++i) {
+        if (i >= nf) break;
         const T *__restrict__ q = (upper ? a.fine[2] : a.fine[i]) + base;
         if (work) {
 #pragma unroll
             for (int ry = 0; ry < R; ++ry) rows[i][ry] = load_row<T, R>(q + ry * nfx);
         }
     }
-    if (upper && t < kBrickRows) {
+    if (rest && t < kBrickRows) {
         const int32_t b0 = seg_clamp(seg0, a.n);
         L.beg[t] = b0;
         L.cnt[t] = seg_clamp(seg1, a.n) - b0;
     }
-    if (upper && t < kBrickHalo) L.sphi[hz][hy][hx] = ph;
+    if (rest && t < kBrickHalo) L.sphi[hz][hy][hx] = ph;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        if (upper && i == 1) break;
-        const int f = upper ? 2 : i;
+    for (int i = 0; i < NF; ++i) {
+        if (i >= nf) break;
+        const int f = f0 + i;
         ChildSum<T, SM> plane;
         if (work) {
 #pragma unroll
@@ -558,16 +577,16 @@ __device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const Bric
 // (gridDim.y = 1 otherwise) several that fill the same brick and share its
 // particles: a batch of 512 is a chain of dependent loads (10,000 particles in 8
 // bricks, FP64: 19 us for three batches by one workgroup each).
-template <typename T, int R, int SM>
-__global__ __launch_bounds__(kBrickThreads) void k_restrict_brick(StepArgs<T> a, BrickGrid<T> bg) {
+template <typename T, int R, int SM, int HALVES>
+__global__ __launch_bounds__(kBrickThreads<HALVES>, (BrickWaves<T, HALVES>::value)) void k_restrict_brick(StepArgs<T> a, BrickGrid<T> bg) {
     static_assert(R <= 4, "one thread per fine child plane");
-    static_assert(kBrickRows <= kBrickThreads, "one particle row per thread");
+    static_assert(kBrickRows <= kBrickFill, "one particle row per thread");
     __shared__ BrickLds<T, R> L;
     int ox, oy, oz;
     bg.origin(xcd_tile(blockIdx.x, gridDim.x), ox, oy, oz);
-    brick_fill<T, R, SM>(a, L, threadIdx.x, ox, oy, oz, blockIdx.y == 0);
+    brick_fill<T, R, SM, HALVES>(a, L, threadIdx.x, ox, oy, oz, blockIdx.y == 0);
     __syncthreads();
-    brick_particles<T, R>(a, L, threadIdx.x, kBrickThreads, blockIdx.y, gridDim.y, ox, oy, oz);
+    brick_particles<T, R>(a, L, threadIdx.x, kBrickThreads<HALVES>, blockIdx.y, gridDim.y, ox, oy, oz);
 }
 
 template <typename T, int R> int64_t brick_blocks(const Geo<T> &g) {
@@ -960,12 +979,17 @@ static void launch_grid_stages(const StepArgs<T> &a, hipStream_t st, int phases)
         a.mk->mark("restrict_lookup", st);
         const int64_t nbk = brick_blocks<T, R>(a.g);
         const BrickGrid<T> bg{(a.g.nb[0] + kBrickX - 1) / kBrickX, (a.g.nb[1] + kBrickY - 1) / kBrickY};
-        // bricks alone that fill the chip (two per compute unit) take one workgroup each; fewer share the
-        // mean number of particles in batches
-        const int64_t batch = nbk * kBrickThreads;
-        const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(512 / nbk, (a.n + batch - 1) / batch));
-        hipLaunchKernelGGL((k_restrict_brick<T, R, SM>), dim3((unsigned)nbk, (unsigned)parts), dim3(kBrickThreads), 0,
-                           st, a, bg);
+        auto bricks = [&](auto hc) {
+            constexpr int H = decltype(hc)::value;
+            // bricks alone that fill the chip take one workgroup each; fewer share the
+            // mean number of particles in batches
+            const int64_t batch = nbk * kBrickThreads<H>;
+            const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(kBrickFew / nbk, (a.n + batch - 1) / batch));
+            hipLaunchKernelGGL((k_restrict_brick<T, R, SM, H>), dim3((unsigned)nbk, (unsigned)parts),
+                               dim3(kBrickThreads<H>), 0, st, a, bg);
+        };
+        if (R == 4 || nbk <= kBrickFew) bricks(std::integral_constant<int, 2>{});
+        else bricks(std::integral_constant<int, R == 4 ? 2 : 1>{});
     } else if (a.vel_source == 3) {
         if constexpr (std::is_same<T, float>::value) {
             a.mk->mark("restrict", st);
