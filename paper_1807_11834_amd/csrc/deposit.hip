@@ -8,8 +8,8 @@
 //
 // The particles are in the canonical (cell, id) order with CSR offsets `start`.
 // CIC: two passes through partial sums per group of source rows (see below);
-// every particle is staged once per pass.  NGP: one thread per cell sums its
-// own segment.
+// every particle is staged once per pass.  NGP: a workgroup sums the segments of a
+// group of cells, staged together.
 #include <algorithm>
 #include <type_traits>
 
@@ -101,16 +101,16 @@ __device__ __forceinline__ void load_values(int64_t id, const vec4<T> &q, const 
 // ---------------------------------------------------------------------------
 // NGP (containing cell)
 // ---------------------------------------------------------------------------
-// A workgroup takes up to 64 consecutive cells at a time, whose particles are one
+// A workgroup takes a group of consecutive cells at a time, whose particles are one
 // run of the sorted order.  The run passes through LDS in chunks, every load of a
-// chunk in flight together; lane (cell) of wave (component) then sums its
-// cell's part of the chunk in canonical order.  One thread per cell that loads
-// and adds particle by particle waits for two dependent loads per particle: 512
-// cells of 20 particles in FP64 took 3 + 12 us (sorted copy, solid fraction)
-// and 19 us (source), on two compute units.  In groups of 64 cells they were two
-// chunks of 8 workgroups (10.4 and 10.2 us); in groups of 16, with four of a
-// cell's values read from LDS at a time, 6.6 and 6.1 (a whole step with 127 per
-// cell: 190 -> 84 us).
+// chunk in flight together; a cell's part of the chunk is then summed in canonical
+// order, by lane (cell) of wave (component) or, in a WIDE group of 256 cells, by
+// thread (cell) for all components.  One thread per cell that loads and adds
+// particle by particle waits for two dependent loads per particle: 512 cells of 20
+// particles in FP64 took 3 + 12 us (sorted copy, solid fraction) and 19 us (source),
+// on two compute units.  In groups of 64 cells they were two chunks of 8 workgroups
+// (10.4 and 10.2 us); in groups of 16, with four of a cell's values read from LDS at
+// a time, 6.6 and 6.1.
 // A cell's sum of v, or for the solid fraction of v / V_b: the product rounded
 // before it is widened, otherwise one FMA with the running sum.
 template <typename T, int SM, int MODE> struct NgpSum {
@@ -123,11 +123,27 @@ template <typename T, int SM, int MODE> struct NgpSum {
     __device__ __forceinline__ T value() const { return acc.value(); }
 };
 constexpr int kNgpItems = 4, kNgpChunk = kBlock * kNgpItems, kNgpRead = 4;
-// Cells of a group: one per lane, or sixteen where that leaves less than a
-// workgroup per compute unit (a group's particles then rarely exceed a chunk).
-static int ngp_cells(int64_t ncell) { return ncell < (int64_t)kWave * 256 ? 16 : kWave; }
+// Cells of a group.  With few particles per cell a wide group: three quarters of the
+// threads of a group of 64 have no cell to sum, and the groups' barriers are most of
+// the time.  Solid fraction and source of 128 x 128 x 256 cells with 0.24 particles
+// each take 37 + 67 us so, 78 + 108 in groups of 64; with 1.2, 119 + 126 and 121 + 139;
+// with 2.4, 330 + 225 and 227 + 228.  Where a wide group has a particle for every
+// second cell or fewer each thread loads its own (20,000 particles in all: 26 + 50
+// us; through LDS 29 + 55).
+//   Otherwise a cell per lane, or sixteen where that leaves less than a workgroup per
+// compute unit, but no more than have a chunk of particles: a group's chunks are
+// summed one after the other (64 cells of 3125 particles: 123 + 190 us; in groups of
+// sixteen 1572 + 2346, with a thread per cell 1027 + 1771).
+constexpr int kNgpSparse = 2;     // particles per cell of the widest groups, at most
+constexpr int kNgpDirect = 128;   // particles of a wide group that are not staged
+static int ngp_cells(int64_t n, int64_t ncell) {
+    if (n <= kNgpSparse * ncell) return kBlock;
+    int cells = ncell < (int64_t)kWave * 256 ? 16 : kWave;
+    while (cells > 1 && cells * n > kNgpChunk * ncell) cells /= 2;
+    return cells;
+}
 
-template <typename T, int SM, int MODE>
+template <typename T, int SM, int MODE, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restrict__ start,
                                                         const vec4<T> *__restrict__ pk, vec4<T> *__restrict__ sp,
                                                         const int32_t *__restrict__ perm,
@@ -137,11 +153,13 @@ __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restric
                                                         double *__restrict__ part, int64_t ps, int cells) {
     constexpr int NC = DepNc<MODE>::value;
     static_assert(NC <= kWavesPerBlock, "a wave per component");
+    constexpr int NA = WIDE ? NC : 1;   // components a thread sums
     __shared__ T val[NC][kNgpChunk];
-    const int lane = threadIdx.x % kWave, comp = threadIdx.x / kWave;
-    double vsum = 0.0, vmax = 0.0;
+    __shared__ double red[kWavesPerBlock];
+    const int lane = threadIdx.x % kWave, comp = WIDE ? 0 : threadIdx.x / kWave;
+    double vsum[NA] = {}, vmax = 0.0;
     for (int64_t c0 = (int64_t)blockIdx.x * cells; c0 < g.ncell; c0 += (int64_t)gridDim.x * cells) {
-        const int64_t c = c0 + lane;
+        const int64_t c = c0 + (WIDE ? (int)threadIdx.x : lane);
         const int64_t c1 = c0 + cells < g.ncell ? c0 + cells : g.ncell;
         const bool mine = c < c1 && comp < NC;
         const int32_t rs = seg_clamp(start[c0], n), re = seg_clamp(start[c1], n);
@@ -150,15 +168,35 @@ __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restric
             s = seg_clamp(start[c], n);
             e = seg_clamp(start[c + 1], n);
         }
+        // the gradient, by the wave with no component or in a wide group by every thread
         GradLoads<T> gl;
         int cx = 0, cy = 0, cz = 0;
-        const bool grad = MODE == kForce && comp == kWavesPerBlock - 1 && c < c1;   // the wave with no component
+        const bool grad = MODE == kForce && (WIDE || comp == kWavesPerBlock - 1) && c < c1;
         if (grad) {
             decode_cell(c, g.nb, cx, cy, cz);
             gl = load_gradient(c, cx, cy, cz, g, P, Plo);
         }
-        NgpSum<T, SM, MODE> acc;
-        for (int64_t cs = rs; cs < re; cs += kNgpChunk) {   // uniform over the workgroup
+        NgpSum<T, SM, MODE> acc[NA];
+        // few particles in a wide group: each thread loads its own
+        const bool direct = WIDE && re - rs <= kNgpDirect;   // uniform over the workgroup
+        if constexpr (WIDE)
+            if (direct && mine)
+                for (int32_t p = s; p < e; ++p) {
+                    int64_t id = perm[p];
+                    if (id < 0 || id >= n) id = 0;
+                    vec4<T> q;
+                    T v[NC];
+                    if constexpr (MODE == kPhi) {
+                        q = pk[id];
+                        sp[p] = q;
+                        v[0] = sphere_volume(q.w);
+                    } else {
+                        load_values<T, MODE>(id, q, drag, pk, g.inv_vb, v);
+                    }
+#pragma unroll
+                    for (int j = 0; j < NA; ++j) acc[j].add(v[j], g.inv_vb);
+                }
+        for (int64_t cs = direct ? re : rs; cs < re; cs += kNgpChunk) {   // uniform over the workgroup
             const int m = (int)(re - cs < kNgpChunk ? re - cs : kNgpChunk);
             int64_t id[kNgpItems];
             vec4<T> q[kNgpItems];
@@ -189,43 +227,44 @@ __global__ __launch_bounds__(kBlock) void k_deposit_ngp(const int32_t *__restric
             if (mine) {
                 const int32_t b0 = (int32_t)((s > cs ? s : cs) - cs), b1 = (int32_t)((e < cs + m ? e : cs + m) - cs);
                 for (int32_t k = b0; k < b1; k += kNgpRead) {
-                    T x[kNgpRead];
-#pragma unroll
-                    for (int u = 0; u < kNgpRead; ++u) x[u] = val[comp][k + u < b1 ? k + u : k];
+                    T x[kNgpRead][NA];
 #pragma unroll
                     for (int u = 0; u < kNgpRead; ++u)
-                        if (k + u < b1) acc.add(x[u], g.inv_vb);
+#pragma unroll
+                        for (int j = 0; j < NA; ++j) x[u][j] = val[comp + j][k + u < b1 ? k + u : k];
+#pragma unroll
+                    for (int u = 0; u < kNgpRead; ++u)
+                        if (k + u < b1)
+#pragma unroll
+                            for (int j = 0; j < NA; ++j) acc[j].add(x[u][j], g.inv_vb);
                 }
             }
             __syncthreads();
         }
         if (mine) {
-            const T t = acc.value();
-            if constexpr (MODE == kPhi) {
-                out[c] = t;
-                vsum += (double)t;
-                vmax = fmax(vmax, (double)t);
-            } else if constexpr (MODE == kForce) {
-                const T f = -t * g.inv_vb;
-                out[comp * g.ncell + c] = f;
-                vsum += (double)f;
-            } else {
-                const T f = t * g.inv_vb;
-                if (comp == 0) out[c] = f;
-                else out2[(comp - 1) * g.ncell + c] = f;
-                vsum += (double)f;
+#pragma unroll
+            for (int j = 0; j < NA; ++j) {
+                const int k = comp + j;
+                const T t = acc[j].value();
+                const T f = MODE == kPhi ? t : (MODE == kForce ? -t * g.inv_vb : t * g.inv_vb);
+                if (MODE != kSemi || k == 0) out[k * g.ncell + c] = f;
+                else out2[(k - 1) * g.ncell + c] = f;
+                vsum[j] += (double)f;
+                if (MODE == kPhi) vmax = fmax(vmax, (double)f);
             }
         }
         if (grad) write_gradient(gl, c, cx, cy, cz, g, G);
     }
-    const double t = wave_sum(vsum);
-    if (lane == 0 && comp < NC) {
-        const int slot = MODE == kPhi ? SL_PHISUM : (MODE == kForce ? SL_FB + comp : SL_KB + comp);
-        part[slot * ps + blockIdx.x] = t;
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+        const int k = comp + j;
+        const double t = WIDE ? block_sum(vsum[j], red) : wave_sum(vsum[j]);
+        const int slot = MODE == kPhi ? SL_PHISUM : (MODE == kForce ? SL_FB + k : SL_KB + k);
+        if ((WIDE ? (int)threadIdx.x : lane) == 0 && k < NC) part[slot * ps + blockIdx.x] = t;
     }
     if constexpr (MODE == kPhi) {
-        const double m = wave_max(vmax);
-        if (lane == 0 && comp == 0) part[SL_MAXPHI * ps + blockIdx.x] = m;
+        const double m = WIDE ? block_max(vmax, red) : wave_max(vmax);
+        if (threadIdx.x == 0) part[SL_MAXPHI * ps + blockIdx.x] = m;
     }
 }
 static_assert(SL_KUB == SL_KB + 1, "the semi-implicit sums are consecutive");
@@ -556,7 +595,7 @@ __global__ __launch_bounds__(kBlock) void k_deposit_sum(const T *__restrict__ pa
 // ---------------------------------------------------------------------------
 int deposit_blocks(int64_t n, int64_t ncell, int cic) {
     if (cic) return (int)((ncell + kBlock - 1) / kBlock);   // pass 2
-    const int cells = ngp_cells(ncell);   // NGP: each loops over its groups of cells
+    const int cells = ngp_cells(n, ncell);   // NGP: each loops over its groups of cells
     return (int)std::min((ncell + cells - 1) / cells, most_partials(n, ncell));
 }
 
@@ -591,9 +630,14 @@ static int launch_deposit(const StepArgs<T> &a, T *out, T *out2, hipStream_t st,
         if (deposit_group(a.g.nb) == 1) rows_and_sums(std::integral_constant<int, 1>{});
         else rows_and_sums(std::integral_constant<int, 2>{});
     } else {
-        hipLaunchKernelGGL((k_deposit_ngp<T, SM, MODE>), dim3(nblk), dim3(kBlock), 0, st, a.start, pk,
-                           a.sp, a.perm, a.drag, a.n, a.g, a.P, a.Plo, out, out2, a.G, a.part, a.part_stride,
-                           ngp_cells(a.g.ncell));
+        const int cells = ngp_cells(a.n, a.g.ncell);
+        auto groups = [&](auto wide) {
+            hipLaunchKernelGGL((k_deposit_ngp<T, SM, MODE, decltype(wide)::value>), dim3(nblk), dim3(kBlock), 0, st,
+                               a.start, pk, a.sp, a.perm, a.drag, a.n, a.g, a.P, a.Plo, out, out2, a.G, a.part,
+                               a.part_stride, cells);
+        };
+        if (cells == kBlock) groups(std::true_type{});
+        else groups(std::false_type{});
     }
     return nblk;
 }
