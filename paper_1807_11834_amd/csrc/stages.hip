@@ -760,7 +760,8 @@ template <typename T> struct ProlongSet {
 // that leaves few workgroups one fine plane of such a tile; one launch takes
 // every field (blockIdx.y).  The tile's 3 x 3 x 3 neighbourhoods (the tile with a
 // one-cell halo, indices clamped at the walls) are staged in LDS in one memory
-// round trip, and each thread writes its cell's children plane by plane.
+// round trip, and each thread writes its cell's children plane by plane (ratio 1, a
+// copy, stages nothing: eight fields of 4.2 million cells 180 -> 136 us).
 // Workgroups loop over the items (prolong_blocks).
 constexpr int kPMaxX = 7, kPMinX = 4;   // tiles of 128 x 2 ... 16 x 16 cells
 constexpr int kPStage = ((1 << kPMaxX) + 2) * ((kBlock >> kPMaxX) + 2);   // staged values of the widest tile
@@ -815,6 +816,16 @@ __global__ __launch_bounds__(kBlock) void k_prolong(StepArgs<T> a, ProlongSet<T>
         const uint32_t trow = (uint32_t)item / (uint32_t)tnx, tlay = trow / (uint32_t)tny;   // fewer than 2^31 items
         const int cx0 = (int)((uint32_t)item - trow * (uint32_t)tnx) << xs, cy0 = (int)(trow - tlay * (uint32_t)tny) << ys;
         const int pz = (int)tlay * planes, cz = pz / R, lz0 = pz % R;   // first fine plane
+        if constexpr (R == 1) {   // the child is the cell (a sum with the defect 0)
+            const int cx = cx0 + i, cy = cy0 + j;
+            if (cx < g.nb[0] && cy < g.nb[1]) {
+                const int64_t c = cz * nxy + cy * nx + cx;
+                const T q = (f == 0 ? T(1) - B[c] : B[c]) + T(0);
+                store_row<T, 1>(out + c, &q);
+                if (c >= a.own_c0 && c < a.own_c1) sum += (double)q;
+            }
+            continue;
+        }
         // staging: the H + 2 rows of the tile in two rounds of H, and the two
         // halo columns, every load issued before the first LDS write
         const int64_t zo[3] = {(cz > 0 ? cz - 1 : 0) * nxy, cz * nxy, (cz + 1 < g.nb[2] ? cz + 1 : cz) * nxy};
