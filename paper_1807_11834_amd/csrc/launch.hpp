@@ -149,9 +149,6 @@ int deposit_blocks(int64_t n, int64_t ncell, int cic);
 // buffer holds (G == 1 ? 9 : 4) slots per cell and component.
 int deposit_group(const int nb[3]);
 
-// Workgroups per field of a prolongation (stages.hip), one FP64 partial each.
-int64_t prolong_blocks(int64_t n, const int nb[3], int ratio);
-
 // Most workgroups (one FP64 partial each) of a kernel that can loop over its work:
 // as many as the step's other kernels have, or two per compute unit.  It depends on
 // the step's sizes alone, not on the scratch at hand, so that the diagnostics are

@@ -767,32 +767,53 @@ constexpr int kPMaxX = 7, kPMinX = 4;   // tiles of 128 x 2 ... 16 x 16 cells
 constexpr int kPStage = ((1 << kPMaxX) + 2) * ((kBlock >> kPMaxX) + 2);   // staged values of the widest tile
 static_assert(((1 << kPMinX) + 2) * ((kBlock >> kPMinX) + 2) <= kPStage, "the widest tile has the most halo");
 
-// Tile width: the widest that pads x by at most a quarter, else the widest of
-// those that pad it least.
-static int prolong_shift(int nx) {
+// Tile width.  In general the widest that pads x by at most a quarter, else the
+// widest of those that pad it least: padding costs idle lanes (3 x 300 x 300 cells of
+// ratio 2 take 36 us in tiles of 16 x 16, 163 in 64 x 4), narrow tiles short rows
+// (100^3 cells of ratio 2 take 45 us in 16 x 16, where a quarter draws the line, and 36
+// in 64 x 4; 72^3 17.6 and 21.2).
+//   The writes of ratio 4 bound it whatever is padded, if there are enough tiles, and
+// are fastest from rows of 64 cells or 128: FP32 150 x 90 x 50 cells take 202 us in 32
+// x 8, 178 in 64 x 4; FP64 72^3 290 in 16 x 16, 208 in 64 x 4, 16 x 64 x 64 62 and 32
+// (128 x 2 where x is not a multiple of it: 72^3 294; where it is, 128 x 64 x 64 456, in
+// 64 x 4 472).  Up to sixteen cells in FP32, eight in FP64, are the faster in 16 x 16 (16
+// x 64 x 64, 17 and 20; 8 x 64 x 64, 28 and 32), and so are few tiles (FP64 32^3: 24 in
+// 32 x 8, 29).
+static int prolong_shift(const int nb[3], int ratio, bool fp64) {
+    const int nx = nb[0];
     auto padded = [&](int xs) { return (((int64_t)nx + (1 << xs) - 1) >> xs) << xs; };
+    if (ratio == 4 && nx > (fp64 ? 8 : 16) && (padded(6) >> 6) * (((int64_t)nb[1] + 3) / 4) * nb[2] >= 512)
+        return (fp64 ? nx % 128 == 0 : 4 * padded(7) <= 5 * (int64_t)nx) ? 7 : 6;
     for (int xs = kPMaxX; xs >= kPMinX; --xs)
         if (4 * padded(xs) <= 5 * (int64_t)nx) return xs;
     for (int xs = kPMaxX; xs > kPMinX; --xs)
         if (padded(xs) == padded(kPMinX)) return xs;
     return kPMinX;
 }
-static int64_t prolong_layer(const int nb[3]) {   // tiles of a layer
-    const int xs = prolong_shift(nb[0]), ys = 8 - xs;
-    return (((int64_t)nb[0] + (1 << xs) - 1) >> xs) * (((int64_t)nb[1] + (1 << ys) - 1) >> ys);
-}
-// Fine planes per item: all r of them (x and y interpolated once), or one where
-// whole tiles would leave the four or more fields fewer than 1024 workgroups.
-static int prolong_planes(const int nb[3], int ratio) { return prolong_layer(nb) * nb[2] * 4 < 1024 ? 1 : ratio; }
-static int64_t prolong_items(const int nb[3], int ratio) {
-    return prolong_layer(nb) * nb[2] * (ratio / prolong_planes(nb, ratio));
+// How a prolongation is split: tile width 2^xs, fine planes per item (all r of them,
+// x and y interpolated once, or one where whole tiles would leave the four or more
+// fields fewer than 1024 workgroups: FP64 8^3 cells of ratio 4 take 6.9 us a plane at a
+// time, 7.4 otherwise, 16^3 8.3 and 9.0; FP32 differs by less, 24^3 10.0 and 8.8),
+// items.
+struct ProlongSplit {
+    int xs, planes;
+    int64_t items;
+};
+static ProlongSplit prolong_split(const int nb[3], int ratio, bool fp64) {
+    ProlongSplit p;
+    p.xs = prolong_shift(nb, ratio, fp64);
+    const int ys = 8 - p.xs;
+    const int64_t tiles = (((int64_t)nb[0] + (1 << p.xs) - 1) >> p.xs) * (((int64_t)nb[1] + (1 << ys) - 1) >> ys) * nb[2];
+    p.planes = tiles * 4 < 1024 ? 1 : ratio;
+    p.items = tiles * (ratio / p.planes);
+    return p;
 }
 static_assert(kBlock == 256, "a tile has 2^8 cells");
 
-// Workgroups per field: one per item, or the most there may be (a multiple of the
-// XCDs, so that each keeps its share of the items).
-int64_t prolong_blocks(int64_t n, const int nb[3], int ratio) {
-    const int64_t items = prolong_items(nb, ratio), most = most_partials(n, (int64_t)nb[0] * nb[1] * nb[2]);
+// Workgroups per field, one FP64 partial each: one per item, or the most there may be
+// (a multiple of the XCDs, so that each keeps its share of the items).
+static int64_t prolong_blocks(int64_t n, int64_t ncell, int64_t items) {
+    const int64_t most = most_partials(n, ncell);
     return items <= most ? items : most / 8 * 8;
 }
 
@@ -1056,9 +1077,9 @@ static void launch_grid_stages(const StepArgs<T> &a, hipStream_t st, int phases)
         for (int k = 0; k < 3; ++k) add(a.KU + k * nc, a.fine_KU + k * nf, SL_KUF + k);
     }
     a.mk->mark("prolong", st);
-    hipLaunchKernelGGL((k_prolong<T, R>), dim3((unsigned)prolong_blocks(a.n, a.g.nb, R), (unsigned)m),
-                       dim3(kBlock), 0, st, a, fs, prolong_shift(a.g.nb[0]), prolong_planes(a.g.nb, R),
-                       prolong_items(a.g.nb, R));
+    const ProlongSplit ps = prolong_split(a.g.nb, R, sizeof(T) == 8);
+    hipLaunchKernelGGL((k_prolong<T, R>), dim3((unsigned)prolong_blocks(a.n, nc, ps.items), (unsigned)m), dim3(kBlock), 0,
+                       st, a, fs, ps.xs, ps.planes, ps.items);
     }
 }
 
@@ -1096,7 +1117,8 @@ template <typename T> hipError_t launch_stages(const StepArgs<T> &a, hipStream_t
     spec.nblk[SL_MLPERR] = nmlp;
     spec.nblk[SL_MLPREF] = nmlp;
     spec.nblk[SL_MLPSAMP] = nmlp;
-    const int ptiles = (int)prolong_blocks(a.n, a.g.nb, a.ratio);   // k_prolong
+    const int ptiles =   // k_prolong
+        (int)prolong_blocks(a.n, a.g.ncell, prolong_split(a.g.nb, a.ratio, sizeof(T) == 8).items);
     spec.nblk[SL_EPSF] = ptiles;
     for (int k = 0; k < 3; ++k) spec.nblk[SL_FF + k] = ptiles;
     for (int k = 0; k < 4; ++k) {
