@@ -143,14 +143,6 @@ template <typename T> __device__ __forceinline__ T node_units_rounded(T x, T s) 
     const T p = x * s;
     return p - T(0.5);
 }
-// Weight of axis stencil `a` on node `c` (folded corners add up).
-template <typename T> __device__ __forceinline__ T axis_weight(const Axis<T> &a, int c) {
-    T w = T(0);
-    if (a.lo == c) w += T(1) - a.t;
-    if (a.hi == c) w += a.t;
-    return w;
-}
-
 // Containing-cell index along one axis: floor(x * s), clamped; x = L -> n - 1.
 template <typename T> __device__ __forceinline__ int cell_axis(T x, T s, int n) {
     return clampi((int)dfloor(x * s), n);

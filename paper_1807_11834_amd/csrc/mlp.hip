@@ -49,7 +49,6 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
 __device__ __forceinline__ uint32_t bf16_bits(float x) { return pack2(x, 0.f) & 0xffffu; }
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ __forceinline__ bf16x8 load8(const uint16_t *p) { return as_bf16x8(*reinterpret_cast<const uint4 *>(p)); }
-__device__ __forceinline__ bf16x8 zero8() { return as_bf16x8(make_uint4(0u, 0u, 0u, 0u)); }
 __device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -66,10 +65,6 @@ __device__ __forceinline__ float sig2u(float z) {
     return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(z * t));
 }
 __device__ __forceinline__ float gelu(float z) { return z * sig2u(z); }
-__device__ __forceinline__ float gelu_grad(float z) {
-    const float s = sig2u(z);
-    return s + 2.f * z * s * (1.f - s) * (kGc * fmaf(3.f * kGa, z * z, 1.f));
-}
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
