@@ -6,7 +6,7 @@
 
 namespace cpl {
 
-constexpr int kBlock = 256;          // threads per workgroup for every kernel
+constexpr int kBlock = 256;          // threads per workgroup, unless a kernel says otherwise
 constexpr int kWave = 64;            // CDNA wavefront width
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr double kPi = 3.14159265358979323846;
@@ -96,9 +96,6 @@ struct FmaSum : FmaState<typename std::conditional<SM == kSumWide, double, T>::t
     __device__ __forceinline__ T value() const { return T(this->s); }
 };
 
-template <typename T> __device__ __forceinline__ T tmin(T a, T b) { return a < b ? a : b; }
-template <typename T> __device__ __forceinline__ T tmax(T a, T b) { return a > b ? a : b; }
-
 __device__ __forceinline__ float dfloor(float x) { return floorf(x); }
 __device__ __forceinline__ double dfloor(double x) { return floor(x); }
 __device__ __forceinline__ float dsqrt(float x) { return sqrtf(x); }
@@ -137,7 +134,9 @@ template <typename T> __device__ __forceinline__ Axis<T> cic_axis_at(T g, int n)
 template <typename T> __device__ __forceinline__ Axis<T> cic_axis(T x, T s, int n) {
     return cic_axis_at(dfma(x, s, T(-0.5)), n);
 }
-// x * s - 1/2 with the product rounded (not one FMA).
+// x * s - 1/2 with the product rounded (not one FMA): the x axis of the brick lookup's
+// void fraction alone.  It has no reason but that this lookup's outputs have always
+// been rounded so; its x weights are off the deposition's by an ulp of x * s.
 template <typename T> __device__ __forceinline__ T node_units_rounded(T x, T s) {
 #pragma clang fp contract(off)
     const T p = x * s;

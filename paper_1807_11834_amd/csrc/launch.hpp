@@ -26,11 +26,12 @@ struct Marker {
     }
 };
 
-// Scratch of the radix sort, owned by the handle.
+// Scratch of the sort, owned by the handle.
 struct SortScratch {
     uint32_t *keys_a, *keys_b;   // [max_particles]
     uint32_t *vals_a, *vals_b;   // [max_particles]
-    uint32_t *hist;              // [256 * max_tiles]
+    uint32_t *hist;              // [256 * max_tiles] digit counts of the radix passes, or the counting
+                                 // sort's 16-bit counts per tile and cell (up to hist_bytes)
     uint32_t *totals;            // [256]
     int64_t max_tiles;           // tiles the histograms hold
     size_t hist_bytes = 0;       // bytes of `hist` that a counting sort may use (0: none)

@@ -766,8 +766,9 @@ __global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2
 // fragments and the MT dZ fragments and issues NK MT independent products.  The
 // fragment loads bound it (a dZ fragment is read once per wave of its layer):
 // with one column block per wave they were 9 for 8 products (49 us for 65,536
-// rows), with two they are 10 for 16 (35.9 us); with the 256 rows of a whole chunk
-// loaded at once instead of 128, 33.5 us.
+// rows), with two they are 10 for 16 (35.9 us); unrolled over the 256 rows of a chunk
+// instead of 128, 33.5 us.  The compiler moves the loads down to their products: its 94
+// registers (five waves per SIMD) are the 64 sums and some seven fragments.
 template <int MT, int KT, int NK>
 __device__ __forceinline__ void wgrad_chunk(const uint16_t *__restrict__ tr, int dz_row, int h_row, int64_t B, int kt,
                                             float *__restrict__ part_w) {
@@ -784,8 +785,7 @@ __device__ __forceinline__ void wgrad_chunk(const uint16_t *__restrict__ tr, int
         for (int mt = 0; mt < MT; ++mt) acc[k][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     const uint16_t *pb = tr + (int64_t)(h_row + 16 * kt + n) * kTrBlock + 8 * g;
     const uint16_t *pa = tr + (int64_t)(dz_row + n) * kTrBlock + 8 * g;
-    // kU groups of 32 rows per round, all their loads issued before the products
-    // (the rows are still summed in order)
+    // kU groups of 32 rows per round (the rows are summed in order)
     constexpr int kU = 8;
     for (int64_t bb = b0; bb < b1; bb += 32 * kU) {
         bf16x8 bv[kU][NK];

@@ -54,8 +54,12 @@ __device__ __forceinline__ T trilin_pairs(const T *__restrict__ f, const Axis<T>
 
 // The four (y, z) rows of x-pairs of one component, and their trilinear value.
 // The products and sums are rounded as written (every sum one FMA), so that a
-// particle's velocity does not depend on where the compiler contracts them; Z:
-// which of the two planes' products is rounded first.
+// lookup's result does not depend on where the compiler contracts them.  Which
+// product of each sum is rounded first (c11 the other way round than its
+// neighbours, Z for the last sum of the bulk velocity's w, a third order in the brick
+// kernel's LDS lookup) has no reason but to keep the bits that each lookup's
+// outputs have always had; they agree to the rounding of these sums, so a particle
+// whose stencil crosses a brick face may differ from its neighbours in the last bit.
 template <typename T> struct PairRows {
     T lo[4], hi[4];   // rows (z lo, y lo), (z lo, y hi), (z hi, y lo), (z hi, y hi)
 };

@@ -525,7 +525,7 @@ __device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const Bric
             T u[3];
 #pragma unroll
             for (int f = 0; f < 3; ++f) {
-                // rounded as written (see trilin_rows; the last sum of w in the other order)
+                // rounded as written, in this lookup's own order (see trilin_rows)
                 auto row = [&](int z, int y) { return dfma(sx, L.sv[f][z][y][xl], tx * L.sv[f][z][y][xh]); };
                 const T e0 = dfma(sy, row(zl, yl), ty * row(zl, yh));
                 const T e1 = dfma(sy, row(zh, yl), ty * row(zh, yh));
@@ -540,6 +540,7 @@ __device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const Bric
         // void fraction at the particle from the haloed phi (its stencil is the
         // containing cell and a neighbour, always inside the halo)
         if (a.cic) {
+            // (x rounded as this lookup always has: see node_units_rounded)
             const Axis<T> bx = cic_axis_at(node_units_rounded(q.x, g.sb[0]), g.nb[0]);
             const Axis<T> by = cic_axis(q.y, g.sb[1], g.nb[1]);
             const Axis<T> bz = cic_axis(q.z, g.sb[2], g.nb[2]);
@@ -576,9 +577,13 @@ __device__ __forceinline__ void brick_particles(const StepArgs<T> &a, const Bric
 // One workgroup per brick, or where there are few bricks of many particles
 // (gridDim.y = 1 otherwise) several that fill the same brick and share its
 // particles: a batch of 512 is a chain of dependent loads (10,000 particles in 8
-// bricks, FP64: 19 us for three batches by one workgroup each).
+// bricks, FP64: 14 us with one workgroup each, 10 with three; 65,000 53 and 13).  They
+// share while that gives at most two workgroups per compute unit (400,000 in 32^3 FP64
+// cells, 1024 bricks: 28 us; sharing up to eight per unit 38; 200,000 in 24^3, 216
+// bricks, where two share one: 20, alone 17).
 template <typename T, int R, int SM, int HALVES>
-__global__ __launch_bounds__(kBrickThreads<HALVES>, (BrickWaves<T, HALVES>::value)) void k_restrict_brick(StepArgs<T> a, BrickGrid<T> bg) {
+__global__ __launch_bounds__(kBrickThreads<HALVES>, (BrickWaves<T, HALVES>::value)) void k_restrict_brick(
+    StepArgs<T> a, BrickGrid<T> bg) {
     static_assert(R <= 4, "one thread per fine child plane");
     static_assert(kBrickRows <= kBrickFill, "one particle row per thread");
     __shared__ BrickLds<T, R> L;
