@@ -130,15 +130,17 @@ constexpr int kNgpItems = 4, kNgpChunk = kBlock * kNgpItems, kNgpRead = 4;
 // with 2.4, 330 + 225 and 227 + 228.  Where a wide group has a particle for every
 // second cell or fewer each thread loads its own (20,000 particles in all: 26 + 50
 // us; through LDS 29 + 55).
-//   Otherwise a cell per lane, or sixteen where that leaves less than a workgroup per
-// compute unit, but no more than have a chunk of particles: a group's chunks are
-// summed one after the other (64 cells of 3125 particles: 123 + 190 us; in groups of
-// sixteen 1572 + 2346, with a thread per cell 1027 + 1771).
+//   Otherwise a cell per lane, or sixteen in up to 8192 cells, where that leaves most
+// compute units without a workgroup (4096 cells of 10 particles: 7.5 + 7.4 us, in
+// groups of 64 8.1 + 8.0; 13,824 of 11: 11.0 + 10.7 and 9.2 + 9.5), but no more than
+// have a chunk of particles: a group's chunks are summed one after the other (64 cells
+// of 3125 particles: 123 + 190 us; in groups of sixteen 1572 + 2346, with a thread per
+// cell 1027 + 1771).
 constexpr int kNgpSparse = 2;     // particles per cell of the widest groups, at most
 constexpr int kNgpDirect = 128;   // particles of a wide group that are not staged
 static int ngp_cells(int64_t n, int64_t ncell) {
     if (n <= kNgpSparse * ncell) return kBlock;
-    int cells = ncell < (int64_t)kWave * 256 ? 16 : kWave;
+    int cells = ncell <= 8192 ? 16 : kWave;
     while (cells > 1 && cells * n > kNgpChunk * ncell) cells /= 2;
     return cells;
 }

@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
     ((9, 7, 5), 630, False), ((9, 7, 5), 631, False),            # 315 cells: 256-cell groups, then 16
     ((40, 32, 16), 7, True), ((40, 32, 16), 900, False),         # groups of 128 particles and fewer load directly
     ((40, 32, 16), 2700, False), ((40, 32, 16), 40_000, True),   # and more; a crowded cell over many chunks
+    ((16, 16, 32), 16_500, False), ((16, 16, 33), 17_000, True),   # groups of 16 and of 64
     ((40, 32, 16), 41_000, False), ((2, 3, 1), 3000, False), ((1, 1, 1), 2049, False), ((5, 4, 4), 5200, True)])
 @pytest.mark.parametrize("precision", ["wide", "kahan", "naive", "fp64"])
 def test_groups(nb, n, crowded, precision):
