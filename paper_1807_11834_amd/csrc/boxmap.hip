@@ -22,23 +22,22 @@ namespace cpl {
 // the map's sum mode (SumMode).  A thread takes a batch of its row's entries
 // together: their values of every field are loaded at once and added in order.
 // The entries of a workgroup's rows are one run of the CSR arrays, taken in one of
-// three ways by its length (us for four FP32 fields of a 64 x 64 x 128 grid with a
-// refined quarter, unless stated):
-//   - at most kWindows windows: through LDS, read with 16-byte loads, batches of
-//     kBatch (to 85 x 85 x 171 cells, 46; from memory 62);
-//   - longer: each thread reads its entries from memory, since a window holds few
-//     rows and only their threads would work (to 32 x 32 x 64 cells, 64 entries a row
-//     where refined, 47; through LDS 81; to 8 x 8 x 16, 4096 a row, 2.8 ms; through
-//     LDS 87).  Between 4 and 6 windows FP64 is still faster through LDS (to 50 x 50
-//     x 100, 45 a row, 80 against 93), FP32 is not (58 either way, one field 24
-//     against 47);
-//   - at most kShort entries a row on average: from memory, kShortBatch at a time,
-//     since a batch of eight repeats the gathers of a row's one or two entries (from
-//     32 x 32 x 64 cells to the refined grid, one a row, 9; through LDS 15).  With the
-//     line at four a row, four fields would gain up to 13 % and one would lose 5 %.
+// three ways by the mean number of entries per row (us for four FP32 fields of a 64 x
+// 64 x 128 grid with a refined quarter, unless stated):
+//   - up to kLong: in windows through LDS, read with 16-byte loads, batches of kBatch
+//     (to 85 x 85 x 171 cells, 46; from memory 62);
+//   - more: each thread reads its entries from memory, since a window holds few rows
+//     and only their threads would work (to 32 x 32 x 64 cells, 64 entries a row where
+//     refined, 47; through LDS 81; to 8 x 8 x 16, 4096 a row, 2.8 ms; through LDS 87).
+//     Between 32 and 48 FP64 is still faster through LDS (to 50 x 50 x 100, 45 a row, 80
+//     against 93), FP32 is not (58 either way, one field 24 against 47);
+//   - at most kShort: from memory, kShortBatch at a time, since a batch of eight repeats
+//     the gathers of a row's one or two entries (from 32 x 32 x 64 cells to the refined
+//     grid, one a row, 9; through LDS 15).  With the line at four a row, four fields
+//     would gain up to 13 % and one would lose 5 %.
 constexpr int kBatch = 8;
 constexpr int kWindow = 2048;   // entries in LDS: the 8 per row that a 2 x 2 x 2 overlap has
-template <typename T> constexpr int kWindows = sizeof(T) == 8 ? 6 : 4;
+template <typename T> constexpr int kLong = sizeof(T) == 8 ? 48 : 32;
 constexpr int kShort = 2, kShortBatch = 2;
 
 // Entries [c0, c0 + kWindow) of p into s, 16 bytes per load; c0 a multiple of 4,
@@ -57,8 +56,9 @@ __device__ __forceinline__ void stage_window(const X *__restrict__ p, int64_t c0
     }
 }
 
-// Entries [j0, j1) of one row added to acc (col and w in LDS or in memory).
-template <int BATCH, typename T, int SM, int NF, typename J>
+// Entries [j0, j1) of one row added to acc.  The entries are in memory, and their
+// weights loaded with the values, or in LDS.
+template <int BATCH, bool LDS, typename T, int SM, int NF, typename J>
 __device__ __forceinline__ void add_entries(const int32_t *col, const T *w, J j0, J j1, const T *__restrict__ src,
                                             int64_t ns, FmaSum<T, SM> (&acc)[NF]) {
     using S = typename FmaSum<T, SM>::W;
@@ -68,24 +68,26 @@ __device__ __forceinline__ void add_entries(const int32_t *col, const T *w, J j0
         for (int u = 0; u < BATCH; ++u) {
             const J i = j + u < j1 ? j + u : j;
             const int64_t c = col[i];
-            wj[u] = w[i];
+            if constexpr (!LDS) wj[u] = w[i];
 #pragma unroll
             for (int k = 0; k < NF; ++k) v[u][k] = src[k * ns + c];
         }
         __builtin_amdgcn_sched_barrier(0);   // every load of the batch before the first sum
 #pragma unroll
         for (int u = 0; u < BATCH; ++u)
-            if (j + u < j1)
+            if (j + u < j1) {
+                const S wu = S(LDS ? w[j + u] : wj[u]);
 #pragma unroll
-                for (int k = 0; k < NF; ++k) acc[k].add(S(wj[u]), S(v[u][k]));
+                for (int k = 0; k < NF; ++k) acc[k].add(wu, S(v[u][k]));
+            }
     }
 }
 
 // Fields NF blockIdx.y .. NF blockIdx.y + NF - 1.
 template <typename T, int SM, int NF>
-__global__ __launch_bounds__(kBlock) void k_boxmap(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
-                                                   const T *__restrict__ w, int64_t nr, int64_t ns,
-                                                   const T *__restrict__ src, T *__restrict__ dst) {
+__global__ __launch_bounds__(kBlock) void k_boxmap(
+    const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const T *__restrict__ w, int64_t nr, int64_t ns,
+    int64_t nnz, const T *__restrict__ src, T *__restrict__ dst) {
     __shared__ __align__(16) int32_t scol[kWindow];
     __shared__ __align__(16) T sw[kWindow];
     src += (int64_t)NF * blockIdx.y * ns;
@@ -96,19 +98,21 @@ __global__ __launch_bounds__(kBlock) void k_boxmap(const int64_t *__restrict__ r
     const int64_t b = mine ? rowptr[r] : 0, e = mine ? rowptr[r + 1] : 0;
     const int64_t w0 = rowptr[r0] & ~(int64_t)3, w1 = rowptr[r1];
     FmaSum<T, SM> acc[NF];
-    if (w1 - w0 > kWindows<T> * kWindow) {   // uniform over the workgroup
-        add_entries<kBatch>(col, w, b, e, src, ns, acc);
-    } else if (w1 - w0 <= kShort * kBlock) {
-        add_entries<kShortBatch>(col, w, b, e, src, ns, acc);
+    const int64_t run = w1 - rowptr[r0], rows = r1 - r0;   // uniform over the workgroup
+    if (run > kLong<T> * rows) {
+        add_entries<kBatch, false>(col, w, b, e, src, ns, acc);
+    } else if (run <= kShort * rows) {
+        add_entries<kShortBatch, false>(col, w, b, e, src, ns, acc);
     } else {
+        const int64_t end = ((w1 + 3) & ~(int64_t)3) < nnz ? (w1 + 3) & ~(int64_t)3 : nnz;   // whole 16-byte loads
         for (int64_t c0 = w0; c0 < w1; c0 += kWindow) {
             if (c0 != w0) __syncthreads();   // the previous window has been read
-            stage_window(col, c0, w1, scol);
-            stage_window(w, c0, w1, sw);
+            stage_window(col, c0, end, scol);
+            stage_window(w, c0, end, sw);
             __syncthreads();
             const int j0 = (int)((b > c0 ? b : c0) - c0);
             const int j1 = (int)((e < c0 + kWindow ? e : c0 + kWindow) - c0);
-            add_entries<kBatch>(scol, sw, j0, j1, src, ns, acc);
+            add_entries<kBatch, true>(scol, sw, j0, j1, src, ns, acc);
         }
     }
     if (mine)
@@ -338,7 +342,7 @@ static void launch_boxmap(const couple_boxmap *m, const void *src, void *dst, in
     const unsigned blocks = (unsigned)((m->nr + kBlock - 1) / kBlock);
     auto group = [&](auto nc, int first, int groups) {
         hipLaunchKernelGGL((k_boxmap<T, SM, decltype(nc)::value>), dim3(blocks, (unsigned)groups), dim3(kBlock), 0, st,
-                           m->rowptr, m->col, (const T *)m->w, m->nr, m->ns, (const T *)src + first * m->ns,
+                           m->rowptr, m->col, (const T *)m->w, m->nr, m->ns, m->nnz, (const T *)src + first * m->ns,
                            (T *)dst + first * m->nr);
     };
     const int rest = nf % 4;

@@ -17,6 +17,9 @@ BOX = (1.0, 1.0, 2.0)
     ((24, 24, 24), (11, 9, 9)),     # some 40: five windows, FP64 through LDS and FP32 not
     ((5, 4, 3), (20, 16, 15)),      # one entry a row
     ((5, 4, 3), (22, 17, 13)),      # one to eight, about two
+    ((24, 24, 24), (2, 2, 1)),      # four receivers: 3456 entries each
+    ((9, 9, 9), (3, 3, 1)),         # nine of some 81 entries
+    ((4, 4, 4), (2, 2, 1)),         # four of sixteen
 ])
 @pytest.mark.parametrize("refined", [False, True])
 @pytest.mark.parametrize("fields", [1, 4, 7])
