@@ -68,7 +68,7 @@ def step_alg_bytes(n, ncell, nfine, fsz, sort_passes):
 
 # Marks of the library's kernel timing -> the kernel names rocprofv3 reports.
 PROFILE_NAMES = {
-    "restrict_lookup": "cpl::k_restrict_brick<float, 4, 2>",
+    "restrict_lookup": "cpl::k_restrict_brick<float, 4, 2, 2>",
     "restrict_p": "cpl::k_restrict_planes<float, 2, 3, 4, false>",
     "restrict": "cpl::k_restrict_planes<float, 2, 0, 4, false>",
     "prolong": "cpl::k_prolong<float, 4>",
@@ -191,8 +191,9 @@ def trace_summary(csv_path):
         rows = list(csv.DictReader(f))
     lines = ["| kernel | calls | avg us | min us | max us | share of traced GPU time |", "|---|---|---|---|---|---|"]
     for r in rows:
-        n = re.sub(r"\(.*", "", r["Name"]).replace("void ", "").strip()
-        if not n.startswith("cpl::"):
+        n = r["Name"].replace("void ", "").replace("(anonymous namespace)::k_", "k_")
+        n = re.sub(r"\(.*", "", n).strip()
+        if not n.startswith(("cpl::", "k_remap")):
             continue
         lines.append(f"| `{n}` | {r['Calls']} | {float(r['AverageNs']) / 1e3:.1f} | {float(r['MinNs']) / 1e3:.1f} | "
                      f"{float(r['MaxNs']) / 1e3:.1f} | {float(r['Percentage']):.1f}% |")
